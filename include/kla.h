@@ -54,8 +54,10 @@
  *              outside).  Under KLA_CHECK=1 the walks of the chunked forward
  *              and backward record whether any of those products was not
  *              finite, and the call synchronises and returns KLA_ERR_RANGE.
- *              The token-recurrent path (fp32 inputs at dk or dv of 64 or 128)
- *              and the per-channel entry points have no such limit.
+ *              fp32 inputs at dk or dv of 64 or 128 have no such limit (past 64
+ *              tokens they run in fp64 chunks too, and a call in which a chunk
+ *              leaves fp64's range is redone token by token, on the device), nor
+ *              have the per-channel entry points.
  *   Empty    : with T == 0 the per-token pointers may be NULL; the final
  *              belief is then the initial one and its gradients pass through.
  *   Errors   : return codes only; on any error nothing has been enqueued
@@ -104,10 +106,11 @@ size_t kla_forward_workspace(const kla_desc* desc);
  * the precision walk's state after the chunk's first 16 tokens (chunked layout:
  * bf16 inputs with dk >= 32 and dv >= 32, the shapes whose backward is
  * chunked); the precision and information state at every chunk start in fp64
- * (fp32 inputs with dk and dv in {16, 32}, the chunked fp64 path); else the
- * precision after every token and the information state before every 64th
- * token (fp32; fp64 for fp32 inputs, whose token-recurrent kernels accumulate
- * in fp64).  Both calls pick the layout by the same rule, so a context from
+ * (fp32 inputs with dk and dv in {16, 32}, or of more than 64 tokens: the
+ * chunked fp64 paths); else the precision after every token and the information
+ * state before every 64th token (fp32; fp64 for fp32 inputs, whose
+ * token-recurrent kernels accumulate in fp64).  A context of more than 64 tokens
+ * at widths of 64 or 128 has room for either layout.  Both calls pick the layout by the same rule, so a context from
  * kla_forward always fits kla_backward. */
 size_t kla_saved_bytes(const kla_desc* desc);
 
@@ -170,9 +173,11 @@ kla_status kla_backward(const kla_desc* desc,
  * freed or synchronised per call).
  *
  *   saved: required (T > 0): the context is read, never recomputed here.
- *   Returns KLA_ERR_WORKSPACE when kla_backward_workspace(desc, 1) exceeds
+ *   Returns KLA_ERR_WORKSPACE when the shape cannot work in
  *   KLA_NOALLOC_SCRATCH_BYTES (64 MiB: the LM-layer shape B8 T2048 H16 d128 bf16
- *   needs 8 MiB, the state-tracking shape B64 T512 H4 d32 fp32 256 bytes).
+ *   needs 8 MiB, the state-tracking shape B64 T512 H4 d32 fp32 256 bytes).  The
+ *   chunk-parallel fp32 backward, whose kla_backward_workspace(desc, 1) is up to
+ *   192 MiB, takes the sequence in smaller windows here.
  *   Calls that overlap on one GPU share its workspace and race: order them on one
  *   stream.  With KLA_CHECK=1 the call synchronises, which graph capture forbids.
  */

@@ -508,6 +508,11 @@ def _check_pc(q, k, v, a, p, r):
             raise ValueError(f"{name} must be a contiguous {shape} tensor in q's dtype")
 
 
+def _pc_workspace(desc: _Desc) -> int:
+    """kla_forward_workspace without the work memory that only the chunk-parallel fp32 forward uses."""
+    return kla_forward_workspace(desc) if desc.dtype == KLA_BF16 else 256
+
+
 def kla_forward_pc(q, k, v, a, p, r, lam0=None, eta0=None, *, want_var: bool = False,
                    want_state: bool = True, save: bool = False, y=None) -> dict:
     """Filter with one observation precision per value channel: q, k, a, p
@@ -529,7 +534,7 @@ def kla_forward_pc(q, k, v, a, p, r, lam0=None, eta0=None, *, want_var: bool = F
     etaT = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_state else None
     nsaved = int(lib.kla_saved_pc_bytes(ctypes.byref(desc))) if save else 0
     saved = torch.empty(max(nsaved, 1), dtype=torch.uint8, device=dev) if save else None
-    nws = kla_forward_workspace(desc)
+    nws = _pc_workspace(desc)
     ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
     st = lib.kla_forward_pc(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(r), _p(lam0), _p(eta0),
                             _p(y), _p(yvar), _p(lamT), _p(etaT), _p(saved if nsaved else None), _p(ws), nws,
@@ -845,7 +850,7 @@ def kla_forward_pc_ou(q, k, v, a, p, delta, r, lam0=None, eta0=None, *, want_var
     etaT = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_state else None
     nsaved = int(lib.kla_saved_pc_bytes(ctypes.byref(desc))) if save else 0
     saved = torch.empty(max(nsaved, 1), dtype=torch.uint8, device=dev) if save else None
-    nws = kla_forward_workspace(desc)
+    nws = _pc_workspace(desc)
     ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
     st = lib.kla_forward_pc_ou(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(delta), _p(r), _p(lam0),
                                _p(eta0), _p(y), _p(yvar), _p(lamT), _p(etaT), _p(saved if nsaved else None), _p(ws),

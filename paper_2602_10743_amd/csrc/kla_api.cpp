@@ -88,20 +88,47 @@ extern "C" {
 
 size_t kla_forward_workspace(const kla_desc* desc) {
     if (check_desc(desc) != KLA_OK) return 0;
-    // validation flag, then the segment-parallel forward's carries when the shape takes it
-    return kAlign + round_up(kla::forward_segmented_workspace(shape_of(desc)));
+    const kla::Shape s = shape_of(desc);
+    // validation flag and range flag, then the work memory of the segment-parallel or the
+    // chunk-parallel forward when the shape takes it
+    if (kla::c64p_supported(s)) {
+        const size_t a = kla::c64p_fwd_workspace(s, false), b = kla::c64p_fwd_workspace(s, true);
+        return kAlign + round_up(a > b ? a : b);
+    }
+    return kAlign + round_up(kla::forward_segmented_workspace(s));
 }
 
 size_t kla_saved_bytes(const kla_desc* desc) {
     if (check_desc(desc) != KLA_OK) return 0;
     const kla::Shape s = shape_of(desc);
     if (saves_chunked(s)) return kla::chunked_saved_bytes(s);
+    if (kla::c64p_supported(s)) return kla::c64p_saved_bytes(s);
     return kla::c64_supported(s) ? kla::c64_saved_bytes(s) : kla::recurrent_saved_bytes(s);
 }
 
-size_t kla_backward_workspace(const kla_desc* desc, int with_saved) {
+}  // extern "C"
+
+namespace {
+
+// What the per-channel forwards ask for: the validation flag (and, for bf16 shapes, no less
+// than kla_forward_workspace); the chunk-parallel path's work memory is not theirs.
+size_t pc_forward_workspace(const kla_desc* desc) {
+    return kAlign + round_up(kla::forward_segmented_workspace(shape_of(desc)));
+}
+
+// least: the smallest workspace the backward can work in (with a saved context)
+size_t backward_workspace(const kla_desc* desc, int with_saved, bool least) {
     if (check_desc(desc) != KLA_OK) return 0;
     const kla::Shape s = shape_of(desc);
+    if (kla::c64p_supported(s)) {
+        size_t work = kla::c64p_bwd_workspace(s, least);
+        if (with_saved) return kAlign + round_up(work);
+        // the context is recomputed: saved states plus a scratch output, the forward's work memory shared
+        const size_t fwd = kla::c64p_fwd_workspace(s, true);
+        if (fwd > work) work = fwd;
+        return kAlign + round_up(work) + round_up(kla::c64p_saved_bytes(s)) +
+               round_up((size_t)s.B * s.T * s.H * s.dv * sizeof(float));
+    }
     if (kla::chunked_bwd_supported(s)) {
         size_t bytes = kAlign + round_up(kla::chunked_bwd_workspace(s));
         if (!with_saved) {  // the context is recomputed: saved states plus a scratch output
@@ -124,9 +151,25 @@ size_t kla_backward_workspace(const kla_desc* desc, int with_saved) {
     return bytes;
 }
 
-}  // extern "C"
+}  // namespace
+
+extern "C" size_t kla_backward_workspace(const kla_desc* desc, int with_saved) {
+    return backward_workspace(desc, with_saved, false);
+}
 
 namespace {
+
+// The forward of the chunk-parallel fp64 path.  At widths above 32 the token-recurrent
+// forward is launched behind it: it overwrites everything if a chunk left the walk's range,
+// and returns at once otherwise.  spare: device memory for the range flag without a saved context.
+hipError_t forward_c64p(const kla::Shape& s, const kla::FwdArgs& a, void* saved, void* work, int* spare,
+                        hipStream_t stream) {
+    const bool wide = kla::c64p_wide(s);
+    int* flag = wide ? spare : a.range_flag;
+    const hipError_t e = kla::launch_forward_c64p(s, a, saved, work, flag, stream);
+    if (e != hipSuccess || !wide) return e;
+    return kla::launch_forward_recurrent(s, a, saved, stream, saved ? kla::c64p_flag(s, saved) : flag);
+}
 
 // The forward behind both gate forms: per-token abar / pbar in a.a, a.p, or OU
 // parameters in a.ou_a, a.ou_p, a.ou_d.
@@ -159,6 +202,8 @@ kla_status forward_impl(const kla_desc* desc, const kla::FwdArgs& a, bool ou, vo
         e = kla::launch_forward_segmented(s, fa, static_cast<char*>(ws) + kAlign, stream);
     else if (chunked)
         e = kla::launch_forward_chunked(s, fa, saved, stream);
+    else if (kla::c64p_supported(s))
+        e = forward_c64p(s, fa, saved, static_cast<char*>(ws) + kAlign, static_cast<int*>(ws) + 16, stream);
     else if (c64)
         e = kla::launch_forward_c64(s, fa, saved, stream);
     else
@@ -181,7 +226,7 @@ size_t ou_part_bytes(const kla::Shape& s) {
 // are summed into parts at the end of the workspace and reduced into the
 // parameter gradients da, dp, dd.
 kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const void* saved, float* da, float* dp,
-                         float* dd, void* ws, size_t ws_bytes, hipStream_t stream) {
+                         float* dd, void* ws, size_t ws_bytes, hipStream_t stream, bool least = false) {
     kla_status st = check_desc(desc);
     if (st != KLA_OK) return st;
     if (ou && (!a.ou_a || !a.ou_p || !a.ou_d || !da || !dp || !dd)) return KLA_ERR_NULL;
@@ -194,7 +239,7 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
                      (const void*)a.ou_d, (void*)da, (void*)dp, (void*)dd))
         return KLA_ERR_ALIGN;
     const size_t need = ou ? kla_backward_ou_workspace(desc, saved != nullptr)
-                           : kla_backward_workspace(desc, saved != nullptr);
+                           : backward_workspace(desc, saved != nullptr, least);
     if (!ws || ws_bytes < need) return KLA_ERR_WORKSPACE;
     const kla::Shape s = shape_of(desc);
     const bool check = check_mode();
@@ -217,6 +262,20 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
             saved = ctx;
         }
         e = kla::launch_backward_chunked(s, a, saved, work, stream);
+    } else if (kla::c64p_supported(s)) {
+        if (!saved) {   // the forward's work memory comes before the context, the backward's takes its place
+            const size_t fwd = kla::c64p_fwd_workspace(s, true), bwd = kla::c64p_bwd_workspace(s, false);
+            char* ctx = work + round_up(fwd > bwd ? fwd : bwd);
+            void* yscratch = ctx + round_up(kla::c64p_saved_bytes(s));
+            kla::FwdArgs f{a.q, a.k, a.v, a.a, a.p, a.r, a.lam0, a.eta0, yscratch, nullptr, nullptr, nullptr,
+                           a.ou_a, a.ou_p, a.ou_d, a.range_flag};
+            e = forward_c64p(s, f, ctx, work, nullptr, stream);
+            if (e != hipSuccess) return KLA_ERR_HIP;
+            saved = ctx;
+        }
+        e = kla::launch_backward_c64p(s, a, saved, work, least, a.range_flag, stream);
+        if (e == hipSuccess && kla::c64p_wide(s))
+            e = kla::launch_backward_recurrent(s, a, saved, work, stream, kla::c64p_flag(s, saved));
     } else if (kla::c64_supported(s)) {
         if (!saved) {
             char* ctx = work;
@@ -246,6 +305,18 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
     if (e != hipSuccess) return KLA_ERR_HIP;
     return check && (kla::chunked_bwd_supported(s) || kla::c64_supported(s)) ? range_status(ws, stream) : KLA_OK;
 }
+
+}  // namespace
+
+namespace kla {
+size_t backward_least_workspace(const kla_desc* desc) { return backward_workspace(desc, 1, true); }
+kla_status backward_least(const kla_desc* desc, const BwdArgs& a, const void* saved, void* ws, size_t ws_bytes,
+                          hipStream_t stream) {
+    return backward_impl(desc, a, false, saved, nullptr, nullptr, nullptr, ws, ws_bytes, stream, true);
+}
+}  // namespace kla
+
+namespace {
 
 kla_status decode_impl(int32_t S, int32_t H, int32_t dk, int32_t dv, int32_t dtype, const kla::DecodeArgs& a,
                        bool ou, hipStream_t stream) {
@@ -338,7 +409,7 @@ kla_status kla_forward_pc(const kla_desc* desc, const void* q, const void* k, co
     if (!all_aligned(q, k, v, abar, pbar, r, (const void*)lam0, (const void*)eta0, y, (void*)yvar, (void*)lamT,
                      (void*)etaT, saved, ws))
         return KLA_ERR_ALIGN;
-    if (!ws || ws_bytes < kla_forward_workspace(desc)) return KLA_ERR_WORKSPACE;
+    if (!ws || ws_bytes < pc_forward_workspace(desc)) return KLA_ERR_WORKSPACE;
     const kla::Shape s = shape_of(desc);
     if (check_mode()) {
         st = validate(s, s.T, q, k, v, abar, pbar, r, lam0, eta0, ws, stream, nullptr, nullptr, nullptr, true);
@@ -400,7 +471,7 @@ kla_status kla_forward_pc_ou(const kla_desc* desc, const void* q, const void* k,
     if (!all_aligned(q, k, v, (const void*)a, (const void*)p, (const void*)delta, r, (const void*)lam0,
                      (const void*)eta0, y, (void*)yvar, (void*)lamT, (void*)etaT, saved, ws))
         return KLA_ERR_ALIGN;
-    if (!ws || ws_bytes < kla_forward_workspace(desc)) return KLA_ERR_WORKSPACE;
+    if (!ws || ws_bytes < pc_forward_workspace(desc)) return KLA_ERR_WORKSPACE;
     const kla::Shape s = shape_of(desc);
     if (check_mode()) {
         st = validate(s, s.T, q, k, v, nullptr, nullptr, r, lam0, eta0, ws, stream, a, p, delta, true);

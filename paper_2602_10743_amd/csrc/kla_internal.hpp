@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "kla.h"
+
 namespace kla {
 
 struct Shape {
@@ -53,11 +55,13 @@ struct DecodeArgs {
 // bytes, in the arithmetic type) is the precision after every token, lam_t
 // [B, T, H, dk], followed by the information state before every 64th token,
 // [B, H, ceil(T / 64), dk, dv]: optional for the forward, required by the backward.
+// run_if: device flag; the kernels return at once, writing nothing, while it is 0 (NULL: always run).
 size_t recurrent_saved_bytes(const Shape& s);
-hipError_t launch_forward_recurrent(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st);
+hipError_t launch_forward_recurrent(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st,
+                                    const int* run_if = nullptr);
 size_t backward_recurrent_workspace(const Shape& s);
 hipError_t launch_backward_recurrent(const Shape& s, const BwdArgs& a, const void* saved, void* ws,
-                                     hipStream_t st);
+                                     hipStream_t st, const int* run_if = nullptr);
 // bytes per element of the recurrent backward's OU parts (the arithmetic type)
 size_t recurrent_ou_part_bytes(const Shape& s);
 hipError_t launch_decode_step(const Shape& s, const DecodeArgs& a, hipStream_t st);
@@ -72,6 +76,21 @@ size_t c64_saved_bytes(const Shape& s);
 hipError_t launch_forward_c64(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st);
 hipError_t launch_backward_c64(const Shape& s, const BwdArgs& a, const void* saved, hipStream_t st);
 
+// Chunk-parallel fp64 path for fp32 storage (chunk64_par.hip).  Saved context: as
+// chunk64.hip's, at widths above 32 (c64p_wide) followed by a range flag.  flag: at those
+// widths device memory the forward clears and sets when a chunk leaves the walk's range
+// (with a saved context its own flag, c64p_flag, is used instead); at the others as
+// range_flag.  least: the backward works in c64p_bwd_workspace(s, true) bytes.
+bool c64p_supported(const Shape& s);
+bool c64p_wide(const Shape& s);
+size_t c64p_saved_bytes(const Shape& s);
+size_t c64p_fwd_workspace(const Shape& s, bool save);
+size_t c64p_bwd_workspace(const Shape& s, bool least);
+const int* c64p_flag(const Shape& s, const void* saved);
+hipError_t launch_forward_c64p(const Shape& s, const FwdArgs& a, void* saved, void* ws, int* flag, hipStream_t st);
+hipError_t launch_backward_c64p(const Shape& s, const BwdArgs& a, const void* saved, void* ws, bool least, int* flag,
+                                hipStream_t st);
+
 // Chunked MFMA path (bf16 storage, dk >= 32).
 bool chunked_supported(const Shape& s);
 size_t chunked_saved_bytes(const Shape& s);
@@ -84,6 +103,11 @@ hipError_t launch_backward_chunked(const Shape& s, const BwdArgs& a, const void*
 int forward_segments(const Shape& s);
 size_t forward_segmented_workspace(const Shape& s);
 hipError_t launch_forward_segmented(const Shape& s, const FwdArgs& a, void* ws, hipStream_t st);
+// kla_backward with a saved context in at most KLA_NOALLOC_SCRATCH_BYTES of workspace where the
+// shape allows it (kla_api.cpp): the bytes it needs, and the call
+size_t backward_least_workspace(const kla_desc* desc);
+kla_status backward_least(const kla_desc* desc, const BwdArgs& a, const void* saved, void* ws, size_t ws_bytes,
+                          hipStream_t stream);
 // value side of the chunked backward (dv, deta0); saved_lam: lam at every 32-token chunk start
 hipError_t launch_backward_dv(const Shape& s, const BwdArgs& a, const float* saved_lam, hipStream_t st);
 // token-sum parts of the OU gate gradients that the chunked / recurrent backward leave

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kla.h"
+#include "kla_internal.hpp"
 
 namespace {
 
@@ -46,9 +47,11 @@ extern "C" kla_status kla_backward_noalloc(const kla_desc* desc, const void* q, 
                                            hipStream_t stream) {
     if (!desc) return KLA_ERR_NULL;
     if (!saved && desc->T > 0) return KLA_ERR_NULL;   // the context is not recomputed here
-    if (kla_backward_workspace(desc, 1) > (size_t)KLA_NOALLOC_SCRATCH_BYTES) return KLA_ERR_WORKSPACE;
+    if (kla::backward_least_workspace(desc) > (size_t)KLA_NOALLOC_SCRATCH_BYTES) return KLA_ERR_WORKSPACE;
     void* ws = device_scratch();
     if (!ws) return KLA_ERR_HIP;
-    return kla_backward(desc, q, k, v, abar, pbar, r, lam0, eta0, saved, dy, dyvar, dlamT, detaT, dq, dk, dv, dabar,
-                        dpbar, dr, dlam0, deta0, ws, (size_t)KLA_NOALLOC_SCRATCH_BYTES, stream);
+    kla::BwdArgs a{q,  k,  v,  abar,  pbar,  r,  lam0, eta0,  dy, dlamT,
+                   detaT, dq, dk, dv, dabar, dpbar, dr, dlam0, deta0};
+    a.dyvar = dyvar;
+    return kla::backward_least(desc, a, saved, ws, (size_t)KLA_NOALLOC_SCRATCH_BYTES, stream);
 }

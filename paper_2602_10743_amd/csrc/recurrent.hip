@@ -160,7 +160,9 @@ struct FwdLay {
 
 template <typename S, int DK, int DV>
 __global__ __launch_bounds__(kFwdThreads<DK>) void fwd_recurrent_kernel(Shape s, FwdArgs g,
-                                                                        typename acc<S>::type* saved_lam) {
+                                                                        typename acc<S>::type* saved_lam,
+                                                                        const int* __restrict__ run_if) {
+    if (run_if && *run_if == 0) return;
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
     using L = FwdLay<S, DK, DV>;
@@ -404,7 +406,9 @@ __global__ __launch_bounds__(kFwdThreads<DK>) void fwd_recurrent_kernel(Shape s,
 template <typename S, int DK, int DV>
 __global__ __launch_bounds__(kThreads) void bwd_sweep1_kernel(Shape s, BwdArgs g, const typename acc<S>::type* slam,
                                                                typename acc<S>::type* wdqt,
-                                                               typename acc<S>::type* wPT) {
+                                                               typename acc<S>::type* wPT,
+                                                               const int* __restrict__ run_if) {
+    if (run_if && *run_if == 0) return;
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
     constexpr int NT = 16, DL = 16, DPER = DV / DL;
@@ -612,7 +616,8 @@ struct Sweep2Cfg : Sweep2Lay<DK, DV, sweep2_nth<DK, DV, A>(), sweep2_tb<DK, DV, 
 template <typename S, int DK, int DV>
 __global__ __launch_bounds__((Sweep2Cfg<DK, DV, typename acc<S>::type>::NTH)) void bwd_sweep2_kernel(
     Shape s, BwdArgs g, const typename acc<S>::type* wlam, const typename acc<S>::type* wdqt,
-    const typename acc<S>::type* wPT, typename acc<S>::type* ou_part) {
+    const typename acc<S>::type* wPT, typename acc<S>::type* ou_part, const int* __restrict__ run_if) {
+    if (run_if && *run_if == 0) return;
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
     using C = Sweep2Cfg<DK, DV, A>;
@@ -1025,21 +1030,21 @@ hipError_t allow_lds(K kern, size_t bytes) {
 
 template <typename S, int DK, int DV>
 struct FwdL {
-    static hipError_t run(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st) {
+    static hipError_t run(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st, const int* run_if) {
         using A = typename acc<S>::type;
         using L = FwdLay<S, DK, DV>;
         auto kern = fwd_recurrent_kernel<S, DK, DV>;
         static const hipError_t attr = allow_lds(kern, L::BYTES);
         if (attr != hipSuccess) return attr;
         const unsigned grid = (unsigned)(s.B * s.H * (DV / L::DVT));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(L::NTH), L::BYTES, st, s, a, static_cast<A*>(saved));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(L::NTH), L::BYTES, st, s, a, static_cast<A*>(saved), run_if);
         return hipGetLastError();
     }
 };
 
 template <typename S, int DK, int DV>
 struct BwdL {
-    static hipError_t run(const Shape& s, const BwdArgs& a, const void* saved, void* ws, hipStream_t st) {
+    static hipError_t run(const Shape& s, const BwdArgs& a, const void* saved, void* ws, hipStream_t st, const int* run_if) {
         using A = typename acc<S>::type;
         if (!saved) return hipErrorInvalidValue;
         const A* slam = static_cast<const A*>(saved);
@@ -1051,7 +1056,7 @@ struct BwdL {
         const unsigned grid1 = (unsigned)(s.B * s.H * (DK / 16) * n_checkpoints(s.T));
         if (grid1 > 0)
             hipLaunchKernelGGL((bwd_sweep1_kernel<S, DK, DV>), dim3(grid1), dim3(kThreads), 0, st, s, a, slam, wdqt,
-                               wPT);
+                               wPT, run_if);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         using C = Sweep2Cfg<DK, DV, A>;
@@ -1059,7 +1064,7 @@ struct BwdL {
         static const hipError_t attr = allow_lds(kern, C::BYTES);
         if (attr != hipSuccess) return attr;
         hipLaunchKernelGGL(kern, dim3(s.B * s.H), dim3(C::NTH), C::BYTES, st, s, a, slam, wdqt, wPT,
-                           static_cast<A*>(a.ou_part));
+                           static_cast<A*>(a.ou_part), run_if);
         return hipGetLastError();
     }
 };
@@ -1078,8 +1083,8 @@ size_t recurrent_saved_bytes(const Shape& s) {
     return (saved_lam_elems(s) + (size_t)s.B * s.H * n_checkpoints(s.T) * s.dk * s.dv) * acc_bytes(s);
 }
 
-hipError_t launch_forward_recurrent(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st) {
-    return dispatch<FwdL>(s, a, saved, st);
+hipError_t launch_forward_recurrent(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st, const int* run_if) {
+    return dispatch<FwdL>(s, a, saved, st, run_if);
 }
 
 // one part per batch row: the recurrent backward walks a whole (b, h) in one workgroup
@@ -1093,8 +1098,8 @@ size_t backward_recurrent_workspace(const Shape& s) {
 }
 
 hipError_t launch_backward_recurrent(const Shape& s, const BwdArgs& a, const void* saved, void* ws,
-                                     hipStream_t st) {
-    return dispatch<BwdL>(s, a, saved, ws, st);
+                                     hipStream_t st, const int* run_if) {
+    return dispatch<BwdL>(s, a, saved, ws, st, run_if);
 }
 
 hipError_t launch_decode_step(const Shape& s, const DecodeArgs& a, hipStream_t st) {

@@ -217,3 +217,26 @@ def test_saved_context_layout_follows_the_backward(lib):
         assert K.kla_backward_workspace(_desc(B, T, H, dk2, dv2, 0), False) >= with_ctx + c64 + B * T * H * dv2 * 4
     rec64 = (B * T * H * 64 + B * H * nck * 64 * 32) * 8
     assert K.kla_saved_bytes(_desc(B, T, H, 64, 32, 0)) == rec64
+
+
+def test_chunk_parallel_fp32_contexts_and_workspaces(lib):
+    """fp32 inputs past 64 tokens: the context holds the chunk states and, at widths above 32,
+    room for the token-recurrent layout and a flag; workspaces are bounded; the allocation-free
+    backward takes what it took when that path needed only the recurrent kernels' workspace."""
+    import paper_2602_10743_amd as K
+    for B, T, H, dk, dv in ((1, 65, 2, 64, 32), (2, 2048, 15, 64, 64), (1, 100, 1, 128, 16)):
+        nc, nck = (T + 31) // 32, (T + 63) // 64
+        par = B * H * dk * (nc + (nc + 1) * dv) * 8
+        rec = (B * T * H * dk + B * H * nck * dk * dv) * 8
+        assert K.kla_saved_bytes(_desc(B, T, H, dk, dv, 0)) == (max(par, rec) + 255) // 256 * 256 + 256
+    for B, T, H, d in ((64, 4096, 16, 128), (1, 1 << 20, 1, 128), (8, 2048, 16, 64)):
+        rec = (B * T * H * d + B * H * d) * 8
+        assert K.kla_forward_workspace(_desc(B, T, H, d, d, 0)) <= (192 << 20) + 512
+        assert K.kla_backward_workspace(_desc(B, T, H, d, d, 0), True) <= max(192 << 20, rec) + 512
+    fake = ctypes.c_void_p(0x10000)   # aligned, never dereferenced: without a device the call ends before any launch
+    ptrs = [fake] * 6 + [None, None, fake, fake, None, None, None] + [fake] * 6 + [None, None]
+    if not __import__("torch").cuda.is_available():
+        near = K._Desc(1, 65000, 1, 128, 128, 0)     # recurrent workspace just under 64 MiB
+        assert lib.kla_backward_noalloc(ctypes.byref(near), *ptrs, None) != 5
+    over = K._Desc(1, 66000, 1, 128, 128, 0)
+    assert lib.kla_backward_noalloc(ctypes.byref(over), *ptrs, None) == 5        # KLA_ERR_WORKSPACE, as before
