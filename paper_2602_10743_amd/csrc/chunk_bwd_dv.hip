@@ -29,7 +29,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void bwd_dv_kernel(Shape 
                                                                           const float* __restrict__ saved_lam) {
     using Cfg = ChunkCfg<DK, DV>;
     constexpr int DVT = Cfg::DVT, NTILE = Cfg::NTILE, DCW = Cfg::DCW, NDT = Cfg::NDT, NSW = Cfg::NSW;
-    constexpr int NRT = Cfg::NRT, KSN = Cfg::KSN, LQ = Cfg::LQ;
+    constexpr int NRT = Cfg::NRT, KSN = Cfg::KSN;
     extern __shared__ __align__(16) unsigned char smem[];
 
     int bh, tile;
@@ -69,6 +69,9 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void bwd_dv_kernel(Shape 
                 G[rt][dt][rr] =
                     g.detaT ? g.detaT[((size_t)bh * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] : 0.f;
 
+    // detaT has arrived: without this the loop would wait for it at the first use of G, and with
+    // it, every round, for all stores of the round before
+    wait_vm_all();
     for (int it = 0; it <= nchunk; ++it) {
         if (it >= 1) {
             const int c = nchunk - it;   // the chunk the scan waves walked in the previous round
@@ -99,11 +102,11 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void bwd_dv_kernel(Shape 
             f32x4 A00 = zero4(), A10 = zero4(), A11 = zero4();
 #pragma unroll
             for (int ks = 0; ks < KSN; ++ks) {
-                const int o0 = l16 * LQ + 32 * ks + 8 * g4, o1 = o0 + 16 * LQ + kQPad;
-                const bf16x8 q0h = lds8(sQH + o0), q0l = lds8(sQL + o0);
-                const bf16x8 q1h = lds8(sQH + o1), q1l = lds8(sQL + o1);
-                const bf16x8 k0h = lds8(sKH + o0), k0l = lds8(sKL + o0);
-                const bf16x8 k1h = lds8(sKH + o1), k1l = lds8(sKL + o1);
+                const int n0 = 32 * ks + 8 * g4;
+                const bf16x8 q0h = nt_tr8(sQH, n0, n0 + 4, 0, l16), q0l = nt_tr8(sQL, n0, n0 + 4, 0, l16);
+                const bf16x8 q1h = nt_tr8(sQH, n0, n0 + 4, 16, l16), q1l = nt_tr8(sQL, n0, n0 + 4, 16, l16);
+                const bf16x8 k0h = nt_tr8(sKH, n0, n0 + 4, 0, l16), k0l = nt_tr8(sKL, n0, n0 + 4, 0, l16);
+                const bf16x8 k1h = nt_tr8(sKH, n0, n0 + 4, 16, l16), k1l = nt_tr8(sKL, n0, n0 + 4, 16, l16);
                 A00 = mfma3(q0h, q0l, k0h, k0l, A00);
                 A10 = mfma3(q1h, q1l, k0h, k0l, A10);
                 A11 = mfma3(q1h, q1l, k1h, k1l, A11);
@@ -133,9 +136,9 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void bwd_dv_kernel(Shape 
                 bf16x8 kbh[2], kbl[2];
 #pragma unroll
                 for (int jt = 0; jt < 2; ++jt) {
-                    const int ko = (16 * jt + l16) * LQ + jt * kQPad + 32 * ks + 4 * g4;
-                    kbh[jt] = lds4x2(sKH + ko, sKH + ko + 16);
-                    kbl[jt] = lds4x2(sKL + ko, sKL + ko + 16);
+                    const int n0 = 32 * ks + 4 * g4;
+                    kbh[jt] = nt_tr8(sKH, n0, n0 + 16, 16 * jt, l16);
+                    kbl[jt] = nt_tr8(sKL, n0, n0 + 16, 16 * jt, l16);
                 }
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
@@ -145,30 +148,25 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void bwd_dv_kernel(Shape 
                     for (int jt = 0; jt < 2; ++jt) vacc[dt][jt] = mfma3(gh, gl, kbh[jt], kbl[jt], vacc[dt][jt]);
                 }
             }
-            // dv[t, d .. d+3] for t = 16 jt + l16, d = dm0 + 16 dt + 4 g4
+            // dv[t, d .. d+3] for t = 16 jt + l16, d = dm0 + 16 dt + 4 g4; rows past the chunk's last
+            // token fall outside the buffer
+            const rsrc_t rdv = make_rsrc(dv + (row0 * H + h) * DV + dm0, (uint32_t)((nt - 1) * H * DV + DCW) * 2);
 #pragma unroll
-            for (int jt = 0; jt < 2; ++jt) {
-                const int t = 16 * jt + l16;
-                if (t < nt) {
+            for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        const uint2 pk{cvt_pk_bf16(vacc[dt][jt][0], vacc[dt][jt][1]),
-                                       cvt_pk_bf16(vacc[dt][jt][2], vacc[dt][jt][3])};
-                        *reinterpret_cast<uint2*>(dv + ((row0 + t) * H + h) * DV + dm0 + 16 * dt + 4 * g4) = pk;
-                    }
-                }
-            }
+                for (int dt = 0; dt < NDT; ++dt)
+                    buf_st64(uint2{cvt_pk_bf16(vacc[dt][jt][0], vacc[dt][jt][1]),
+                                   cvt_pk_bf16(vacc[dt][jt][2], vacc[dt][jt][3])},
+                             rdv, (uint32_t)((16 * jt + l16) * H * DV + 16 * dt + 4 * g4) * 2);
 
             // ---- G <- Qp^T dY + Gs
-            const int tpad = g4 >= 2 ? kQPad : 0;   // tile rows 8 g4 .. 8 g4 + 7 past row 16
             bf16x8 yb[NDT];   // dY rows t = 8 g4 .. 8 g4 + 7 of column d
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) yb[dt] = lds_tr8(sDY, DVT, 8 * g4, 8 * g4 + 4, dl0 + 16 * dt, l16);
 #pragma unroll
             for (int rt = 0; rt < NRT; ++rt) {
                 // Qp^T rows n = 16 rt + l16, tokens 8 g4 .. 8 g4 + 7
-                const bf16x8 qth = lds_tr8(sQH + tpad, LQ, 8 * g4, 8 * g4 + 4, 16 * rt, l16);
-                const bf16x8 qtl = lds_tr8(sQL + tpad, LQ, 8 * g4, 8 * g4 + 4, 16 * rt, l16);
+                const bf16x8 qth = nt_row8(sQH, 16 * rt + l16, g4), qtl = nt_row8(sQL, 16 * rt + l16, g4);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) G[rt][dt] = mfma2a(qth, qtl, yb[dt], G[rt][dt]);
             }

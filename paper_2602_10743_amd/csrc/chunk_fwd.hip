@@ -23,12 +23,12 @@
 namespace kla {
 namespace {
 
-template <int DK, int DV, bool YV, bool TI, bool NOY>
+template <int DK, int DV, bool YV, bool TI, bool NOY, bool SAVE>
 __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Shape s, FwdArgs g, float* saved_lam,
                                                                          float* saved_H) {
     using Cfg = ChunkCfg<DK, DV>;
     constexpr int DVT = Cfg::DVT, NTILE = Cfg::NTILE, DCW = Cfg::DCW, NDT = Cfg::NDT, NSW = Cfg::NSW;
-    constexpr int SW = Cfg::SW, NRT = Cfg::NRT, KSN = Cfg::KSN, LQ = Cfg::LQ;
+    constexpr int SW = Cfg::SW, NRT = Cfg::NRT, KSN = Cfg::KSN;
     extern __shared__ __align__(16) unsigned char smem[];
 
     const uint16_t* q = static_cast<const uint16_t*>(g.q);
@@ -52,7 +52,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
     if (wave < NSW) {
         // ================================================================ scan waves
         const ScanSrc sc{a, p, k, q, r, v, tile * DVT, seq0, H, h, T, nchunk, bh, g.ou_a, g.ou_p, g.ou_d, g.range_flag};
-        const float x = scan_wave<Cfg, YV, false, TI, NOY>(smem, wave, lane, sc, g.lam0, saved_lam != nullptr);
+        const float x = scan_wave<Cfg, YV, false, TI, NOY>(smem, wave, lane, sc, g.lam0, SAVE);
         if (g.lamT && lane < SW && tile == 0) g.lamT[(size_t)bh * DK + wave * SW + lane] = x;
     } else {
         // ================================================================ MFMA waves
@@ -71,15 +71,22 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                     Hs[rt][dt][rr] =
                         g.eta0 ? g.eta0[((size_t)bh * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] : 0.f;
 
-        // state rows 16 rt .. 16 rt + 15 (this wave's columns) into saved slot `slot`
-        auto save_rows = [&](int slot, int rt) {
-            float* dst = saved_H + ((size_t)bh * (nchunk + 1) + slot) * DK * DV;
+        // state rows 16 rt .. 16 rt + 15 (this wave's columns) into the saved slot behind rs
+        const uint32_t h_voff = (uint32_t)(4 * g4 * DV + dm0 + l16) * 4;
+        auto save_rows = [&](rsrc_t rs, int rt) {
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)
-                    dst[(16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] = Hs[rt][dt][rr];
+                    buf_st32s(Hs[rt][dt][rr], rs, h_voff, (uint32_t)((16 * rt + rr) * DV + 16 * dt) * 4);
         };
+        auto slot_rsrc = [&](int slot) {
+            return make_rsrc(saved_H + ((size_t)bh * (nchunk + 1) + slot) * DK * DV, DK * DV * 4);
+        };
+        // eta0 has arrived: without this the loop would wait for it at the first use of the state,
+        // and with it, every round, for all stores of the round before (65536-token forward without
+        // a saved context: 855 -> 808 us, together with its stores through buffers)
+        wait_vm_all();
         for (int c = 0; c <= nchunk; ++c) {
             const int cc = c - 1;   // the chunk consumed in this round
             if (cc >= 0) {
@@ -98,11 +105,11 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                     f32x4 S00 = zero4(), S01 = zero4(), S11 = zero4();
 #pragma unroll
                     for (int ks = 0; ks < KSN; ++ks) {
-                        const int o0 = l16 * LQ + 32 * ks + 8 * g4, o1 = o0 + 16 * LQ + kQPad;
-                        const bf16x8 k0h = lds8(sKH + o0), k0l = lds8(sKL + o0);
-                        const bf16x8 k1h = lds8(sKH + o1), k1l = lds8(sKL + o1);
-                        const bf16x8 q0h = lds8(sQH + o0), q0l = lds8(sQL + o0);
-                        const bf16x8 q1h = lds8(sQH + o1), q1l = lds8(sQL + o1);
+                        const int n0 = 32 * ks + 8 * g4;
+                        const bf16x8 k0h = nt_tr8(sKH, n0, n0 + 4, 0, l16), k0l = nt_tr8(sKL, n0, n0 + 4, 0, l16);
+                        const bf16x8 k1h = nt_tr8(sKH, n0, n0 + 4, 16, l16), k1l = nt_tr8(sKL, n0, n0 + 4, 16, l16);
+                        const bf16x8 q0h = nt_tr8(sQH, n0, n0 + 4, 0, l16), q0l = nt_tr8(sQL, n0, n0 + 4, 0, l16);
+                        const bf16x8 q1h = nt_tr8(sQH, n0, n0 + 4, 16, l16), q1l = nt_tr8(sQL, n0, n0 + 4, 16, l16);
                         S00 = mfma3(k0h, k0l, q0h, q0l, S00);
                         S01 = mfma3(k0h, k0l, q1h, q1l, S01);
                         S11 = mfma3(k1h, k1l, q1h, q1l, S11);
@@ -132,9 +139,9 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                         bf16x8 qbh[2], qbl[2];
 #pragma unroll
                         for (int it = 0; it < 2; ++it) {
-                            const int qo = (16 * it + l16) * LQ + it * kQPad + 32 * ks + 4 * g4;
-                            qbh[it] = lds4x2(sQH + qo, sQH + qo + 16);
-                            qbl[it] = lds4x2(sQL + qo, sQL + qo + 16);
+                            const int n0 = 32 * ks + 4 * g4;
+                            qbh[it] = nt_tr8(sQH, n0, n0 + 16, 16 * it, l16);
+                            qbl[it] = nt_tr8(sQL, n0, n0 + 16, 16 * it, l16);
                         }
 #pragma unroll
                         for (int dt = 0; dt < NDT; ++dt) {
@@ -145,36 +152,32 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                         }
                         // the chunk-start state goes to the saved context a few rows at a time, between
                         // the products, so that the stores of all workgroups do not come in one burst
-                        if (saved_H) {
-                            save_rows(cc, 2 * ks);
-                            save_rows(cc, 2 * ks + 1);
+                        if constexpr (SAVE) {
+                            const rsrc_t rs = slot_rsrc(cc);
+                            save_rows(rs, 2 * ks);
+                            save_rows(rs, 2 * ks + 1);
                         }
                     }
-                    // y[t, d .. d+3] for t = 16 it + l16, d = dm0 + 16 dt + 4 g4
+                    // y[t, d .. d+3] for t = 16 it + l16, d = dm0 + 16 dt + 4 g4; rows past the chunk's
+                    // last token fall outside the buffer
+                    const rsrc_t ry = make_rsrc(y + (row0 * H + h) * DV + dm0, (uint32_t)((nt - 1) * H * DV + DCW) * 2);
 #pragma unroll
-                    for (int it = 0; it < 2; ++it) {
-                        const int t = 16 * it + l16;
-                        if (t < nt) {
+                    for (int it = 0; it < 2; ++it)
 #pragma unroll
-                            for (int dt = 0; dt < NDT; ++dt) {
-                                const uint2 pk{cvt_pk_bf16(yacc[dt][it][0], yacc[dt][it][1]),
-                                               cvt_pk_bf16(yacc[dt][it][2], yacc[dt][it][3])};
-                                *reinterpret_cast<uint2*>(y + ((row0 + t) * H + h) * DV + dm0 + 16 * dt + 4 * g4) = pk;
-                            }
-                        }
-                    }
+                        for (int dt = 0; dt < NDT; ++dt)
+                            buf_st64(uint2{cvt_pk_bf16(yacc[dt][it][0], yacc[dt][it][1]),
+                                           cvt_pk_bf16(yacc[dt][it][2], yacc[dt][it][3])},
+                                     ry, (uint32_t)((16 * it + l16) * H * DV + 16 * dt + 4 * g4) * 2);
                 }
 
                 // ---- state: H <- diag(P_C) (H + Kn^T V)
-                const int tpad = g4 >= 2 ? kQPad : 0;   // tile rows 8 g4 .. 8 g4 + 7 past row 16
                 bf16x8 vb[NDT];   // V rows t = 8 g4 .. 8 g4 + 7 of column d
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) vb[dt] = lds_tr8(sVS, DVT, 8 * g4, 8 * g4 + 4, dl0 + 16 * dt, l16);
 #pragma unroll
                 for (int rt = 0; rt < NRT; ++rt) {
                     // Kn^T rows n = 16 rt + l16, tokens 8 g4 .. 8 g4 + 7
-                    const bf16x8 kth = lds_tr8(sKH + tpad, LQ, 8 * g4, 8 * g4 + 4, 16 * rt, l16);
-                    const bf16x8 ktl = lds_tr8(sKL + tpad, LQ, 8 * g4, 8 * g4 + 4, 16 * rt, l16);
+                    const bf16x8 kth = nt_row8(sKH, 16 * rt + l16, g4), ktl = nt_row8(sKL, 16 * rt + l16, g4);
                     const float4 dec = *reinterpret_cast<const float4*>(sDec + 16 * rt + 4 * g4);
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) {
@@ -187,7 +190,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                 }
 
                 // the chunk's walk state goes to the saved context (one value tile stores it)
-                if (saved_lam && tile == 0) {
+                if (SAVE && tile == 0) {
                     constexpr int NV4 = kLamRows * DK / 4;
                     const float4* src = reinterpret_cast<const float4*>(buf + Cfg::MIDS);
                     float4* dst = reinterpret_cast<float4*>(saved_lam + ((size_t)bh * nchunk + cc) * kLamRows * DK);
@@ -205,9 +208,11 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
             barrier_lds();
         }
 
-        if (saved_H)   // the final state closes the saved sequence
+        if constexpr (SAVE) {   // the final state closes the saved sequence
+            const rsrc_t rs = slot_rsrc(nchunk);
 #pragma unroll
-            for (int rt = 0; rt < NRT; ++rt) save_rows(nchunk, rt);
+            for (int rt = 0; rt < NRT; ++rt) save_rows(rs, rt);
+        }
         if (g.etaT) {
 #pragma unroll
             for (int rt = 0; rt < NRT; ++rt)
@@ -220,10 +225,10 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
     }
 }
 
-template <int DK, int DV, bool YV, bool TI, bool NOY = false>
+template <int DK, int DV, bool YV, bool TI, bool NOY, bool SAVE>
 hipError_t launch_fwd_v(const Shape& s, const FwdArgs& a, float* saved_lam, float* saved_H, hipStream_t st) {
     using Cfg = ChunkCfg<DK, DV>;
-    auto kern = fwd_chunk_kernel<DK, DV, YV, TI, NOY>;
+    auto kern = fwd_chunk_kernel<DK, DV, YV, TI, NOY, SAVE>;
     // more than 64 KiB of LDS must be opted into once per kernel (thread-safe static init)
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
@@ -233,17 +238,16 @@ hipError_t launch_fwd_v(const Shape& s, const FwdArgs& a, float* saved_lam, floa
     return hipGetLastError();
 }
 
-// the readout variance adds a cross-lane sum per token, so it is a separate
-// instantiation, as are the time-invariant gates and the state-only pass (no y:
-// the segment-parallel forward's first pass)
-template <int DK, int DV>
+// the readout variance adds a cross-lane sum per token and the saved context its stores,
+// so they are separate instantiations, as are the time-invariant gates and the state-only
+// pass (no y: the segment-parallel forward's first pass)
+template <int DK, int DV, bool TI>
 hipError_t launch_fwd(const Shape& s, const FwdArgs& a, float* saved_lam, float* saved_H, hipStream_t st) {
-    if (!a.y) return launch_fwd_v<DK, DV, false, false, true>(s, a, nullptr, nullptr, st);
-    if (a.ou_a)
-        return a.yvar ? launch_fwd_v<DK, DV, true, true>(s, a, saved_lam, saved_H, st)
-                      : launch_fwd_v<DK, DV, false, true>(s, a, saved_lam, saved_H, st);
-    return a.yvar ? launch_fwd_v<DK, DV, true, false>(s, a, saved_lam, saved_H, st)
-                  : launch_fwd_v<DK, DV, false, false>(s, a, saved_lam, saved_H, st);
+    if (saved_H)
+        return a.yvar ? launch_fwd_v<DK, DV, true, TI, false, true>(s, a, saved_lam, saved_H, st)
+                      : launch_fwd_v<DK, DV, false, TI, false, true>(s, a, saved_lam, saved_H, st);
+    return a.yvar ? launch_fwd_v<DK, DV, true, TI, false, false>(s, a, nullptr, nullptr, st)
+                  : launch_fwd_v<DK, DV, false, TI, false, false>(s, a, nullptr, nullptr, st);
 }
 
 }  // namespace
@@ -267,8 +271,12 @@ hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved,
         saved_lam = static_cast<float*>(saved);
         saved_H = saved_lam + (size_t)s.B * s.H * nchunk * kLamRows * s.dk;
     }
-#define KLA_FWD_CASE(DK_, DV_) \
-    if (s.dk == DK_ && s.dv == DV_) return launch_fwd<DK_, DV_>(s, a, saved_lam, saved_H, st);
+#define KLA_FWD_CASE(DK_, DV_)                                                                         \
+    if (s.dk == DK_ && s.dv == DV_) {                                                                  \
+        if (!a.y) return launch_fwd_v<DK_, DV_, false, false, true, false>(s, a, nullptr, nullptr, st); \
+        return a.ou_a ? launch_fwd<DK_, DV_, true>(s, a, saved_lam, saved_H, st)                        \
+                      : launch_fwd<DK_, DV_, false>(s, a, saved_lam, saved_H, st);                      \
+    }
 #define KLA_FWD_ROW(DK_) KLA_FWD_CASE(DK_, 16) KLA_FWD_CASE(DK_, 32) KLA_FWD_CASE(DK_, 64) KLA_FWD_CASE(DK_, 128)
     KLA_FWD_ROW(32) KLA_FWD_ROW(64) KLA_FWD_ROW(128)
 #undef KLA_FWD_ROW

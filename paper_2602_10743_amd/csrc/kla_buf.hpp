@@ -24,6 +24,16 @@ __device__ __forceinline__ uint4 buf_ld128(rsrc_t r, uint32_t voff, uint32_t sof
     return uint4{v[0], v[1], v[2], v[3]};
 }
 
+// Stores through a buffer: a lane whose offset lies past the end stores nothing.  soff: uniform bytes.
+__device__ __forceinline__ void buf_st32s(float v, rsrc_t r, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, soff, 0);
+}
+
+__device__ __forceinline__ void buf_st64(uint2 v, rsrc_t r, uint32_t voff) {
+    typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, r, voff, 0, 0);
+}
+
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // Direct loads into LDS: lane i's 16 bytes land at dst + 16 i (one wave fills

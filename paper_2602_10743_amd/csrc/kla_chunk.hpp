@@ -27,7 +27,7 @@
 // tokens side by side, and the half-1 lanes end at the chunk end.
 //
 // Round i of the chunk loop: the scan waves walk chunk c(i) into exchange
-// buffer i & 1 -- Qp and Kn as split-bf16 [t][n] tiles, the chunk decay P_C,
+// buffer i & 1 -- Qp and Kn as split-bf16 [n][t] tiles, the chunk decay P_C,
 // optionally the per-token variance partials -- and bring that chunk's tile of
 // a per-token value tensor (v or dy) into the same buffer, while the MFMA waves
 // consume buffer (i - 1) & 1.  One LDS-ordering barrier ends each round.  The
@@ -50,14 +50,42 @@ namespace kla {
 
 constexpr int kC = 32;   // tokens per chunk
 
-// LDS placement of the per-chunk [t][...] tiles written by the two halves of a scan
-// wave.  Lane l of a wave works on token rows of half l / 32; the rows 16 apart would
-// otherwise fall on the same LDS banks, so the second 16 rows of every tile start
-// 64 bytes (16 banks) further on: Qp / Kn tiles after kQPad extra halfwords, the
-// staged inputs one spare row of SW = 32 slots later (kSR rows per input).
-constexpr int kQPad = 32;
-constexpr int kSR = kC + 1;
-__device__ __forceinline__ constexpr int srow(int t) { return t + (t >> 4); }
+// Qp and Kn lie slot-major in LDS: element (n, t) of a [slots][kC] bf16 tile, in halfwords.
+// A walk lane holds consecutive tokens of one slot, so it stores 8 of them in one 16-byte
+// write; MFMA operands whose lanes run along the tokens read 8 bytes of a row per 4 tokens
+// or 16 per 8, those whose lanes run along the slots use the transposing read (nt_tr8).
+// Token-major tiles took a 2-byte write per element, four times the LDS instructions of the
+// whole walk: forward 266 -> 259 us, value-side backward 230 -> 213 us (B8 T2048 H16 128 x
+// 128), state-only pass, which is bound by the walk, 544 -> 435 us (65536 tokens).  The 16-byte pieces of a row are swizzled by the slot: eight lanes writing or
+// reading the same piece of eight consecutive slots, and the four rows of a transposing
+// read, fall in distinct banks without padding.
+__device__ __forceinline__ constexpr int nt_off(int n, int t) {
+    return n * kC + (((t >> 3) ^ ((n >> 2) & 3)) << 3) + (t & 7);
+}
+
+// lane s (of 16) receives X(rowA + j, t0 + s) and X(rowB + j, t0 + s), j = 0..3; rows
+// multiples of 4, t0 of 16
+__device__ __forceinline__ bf16x8 nt_tr8(const uint16_t* X, int rowA, int rowB, int t0, int s) {
+    const int t = t0 + 4 * (s & 3);
+    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(X + nt_off(rowA + (s >> 2), t)));
+    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(X + nt_off(rowB + (s >> 2), t)));
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// tokens 8 c .. 8 c + 7 of slot n
+__device__ __forceinline__ bf16x8 nt_row8(const uint16_t* X, int n, int c) { return lds8(X + nt_off(n, 8 * c)); }
+
+// Four tokens of one slot from a token-major tile (rows of ld halfwords): lane s (of 16)
+// receives X[t + j][col0 + s], j = 0..3, as two words of two tokens each.
+__device__ __forceinline__ uint2 tok4(const uint16_t* X, int ld, int t, int col0, int s) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                                         (lds_bf16x4_t*)(X + (t + (s >> 2)) * ld + col0 + 4 * (s & 3))));
+}
+// token i of the four, widened
+__device__ __forceinline__ float tok(const uint2& w, int i) {
+    const uint32_t x = i < 2 ? w.x : w.y;
+    return __uint_as_float(i & 1 ? x & 0xffff0000u : x << 16);
+}
 constexpr int kLamRows = 3;   // saved walk state per chunk and key slot: lam_0, lam_16, P_16
 
 // x of lane l ^ 32, as seen by the lanes of one half: hi32 is valid in lanes 32..63
@@ -84,9 +112,7 @@ struct ChunkCfg {
     static constexpr int NTHR = 64 * (NSW + NMW);
     static constexpr int NRT = DK / 16;
     static constexpr int KSN = DK / 32;
-    static constexpr int LQ = DK + 8;                // row stride of [t][n] tiles (halfwords)
-    static constexpr int QPAD = kQPad;               // extra halfwords before row 16 of a tile
-    static constexpr int QT = kC * LQ + QPAD;        // one [t][n] tile (halfwords)
+    static constexpr int QT = kC * DK;               // one [n][t] tile (halfwords)
     // one exchange buffer (byte offsets)
     static constexpr int QH = 0, QL = QH + QT * 2, KH = QL + QT * 2, KL = KH + QT * 2;
     static constexpr int DEC = KL + QT * 2;          // P_C [DK] fp32
@@ -96,10 +122,10 @@ struct ChunkCfg {
     static constexpr int BUF = VS + kC * DVT * 2;
     static constexpr int NVL = kC * DVT * 2 / 1024;  // 1 KiB wave loads of the value tile
     static constexpr int TPV = kC / NVL;             // tokens per value-tile load
-    // per scan wave: abar, pbar, k, q [2 buffers][4][kSR][SW] bf16 (token t in row
-    // t + t / 16), then r [2][64] and the saved walk state [2][2][64] as words
+    // per scan wave: abar, pbar, k, q [2 buffers][4][kC][SW] bf16, then r [2][64] and the
+    // saved walk state [2][2][64] as words
     static constexpr int STG = 2 * BUF;
-    static constexpr int STG_IN = 4 * kSR * SW * 2;  // one buffer of staged inputs
+    static constexpr int STG_IN = 4 * kC * SW * 2;  // one buffer of staged inputs
     static constexpr int STG_R = 2 * STG_IN, STG_L = STG_R + 2 * 64 * 4;
     static constexpr int STG_WAVE = STG_L + 2 * 128 * 4;
     static constexpr int BYTES = STG + NSW * STG_WAVE;
@@ -122,31 +148,31 @@ __device__ __forceinline__ void xcd_tile_map(int i, int nbh, int ntile, int& bh,
 
 // Outputs of the precision walk in one exchange buffer.
 struct ScanOut {
-    uint16_t *qh, *ql, *kh, *kl;   // [t][n]
+    uint16_t *qh, *ql, *kh, *kl;   // (n, t), see nt_off
     float* dec;                    // P_C [n]
     float* yv;                     // per-token sums of q^2 / lam over this wave's slots
     float* mid;                    // the chunk's walk state [kLamRows][n] (see scan_wave)
 };
 
-// Staged inputs of 8 consecutive tokens for one key slot (raw bf16 / r words;
-// a and p unused with time-invariant gates).
+// Staged inputs of 8 consecutive tokens for one key slot, two tokens per word (a and p
+// unused with time-invariant gates), r as words.
 struct ScanGroup {
-    uint32_t a[8], p[8], k[8], q[8];
+    uint2 a[2], p[2], k[2], q[2];
     uint4 r[2];
 };
 
 template <int SW, bool TI, bool NOQ>
 __device__ __forceinline__ void read_group(ScanGroup& gr, const uint16_t* __restrict__ stg,
                                            const uint32_t* __restrict__ rw, int sl, int t8) {
+    const int c0 = sl & 16, s = sl & 15;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int row = srow(t8 + e);
+    for (int e = 0; e < 2; ++e) {
         if constexpr (!TI) {
-            gr.a[e] = stg[(0 * kSR + row) * SW + sl];
-            gr.p[e] = stg[(1 * kSR + row) * SW + sl];
+            gr.a[e] = tok4(stg + 0 * kC * SW, SW, t8 + 4 * e, c0, s);
+            gr.p[e] = tok4(stg + 1 * kC * SW, SW, t8 + 4 * e, c0, s);
         }
-        gr.k[e] = stg[(2 * kSR + row) * SW + sl];
-        if constexpr (!NOQ) gr.q[e] = stg[(3 * kSR + row) * SW + sl];
+        gr.k[e] = tok4(stg + 2 * kC * SW, SW, t8 + 4 * e, c0, s);
+        if constexpr (!NOQ) gr.q[e] = tok4(stg + 3 * kC * SW, SW, t8 + 4 * e, c0, s);
     }
     gr.r[0] = *reinterpret_cast<const uint4*>(rw + t8);
     gr.r[1] = *reinterpret_cast<const uint4*>(rw + t8 + 4);
@@ -167,7 +193,7 @@ __device__ __forceinline__ float bf16w(uint32_t w) { return __uint_as_float(w <<
 // so neither the 8-token products nor the exchanges between the halves are
 // needed; the return value is then the half's own end lam (the chunk end in
 // half 1 only).
-template <int SW, int LQ, bool YV, bool FULL, bool TI, bool NOQ, bool MID = false>
+template <int SW, bool YV, bool FULL, bool TI, bool NOQ, bool MID = false>
 __device__ __forceinline__ float scan_chunk(const uint16_t* __restrict__ stg, const uint32_t* __restrict__ rw,
                                             int sl, int hf, int n, int nt, float x, const ScanOut& o, float ca,
                                             float cp, float& chk, float& lm, float& pm) {
@@ -181,14 +207,15 @@ __device__ __forceinline__ float scan_chunk(const uint16_t* __restrict__ stg, co
         // (1, 0) and (0, 1), with the product of abar
         float m00 = 1.f, m10 = 0.f, m01 = 0.f, m11 = 1.f, aq = 1.f;
         {
+            ScanGroup pg;
+            read_group<SW, TI, true>(pg, stg, rw, sl, 8 * hf);
             float ta[8], tp[8], tk[8], tr[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int t = 8 * hf + j;
-                ta[j] = TI ? ca : bf16w(stg[(0 * kSR + t) * SW + sl]);
-                tp[j] = TI ? cp : bf16w(stg[(1 * kSR + t) * SW + sl]);
-                tk[j] = bf16w(stg[(2 * kSR + t) * SW + sl]);
-                tr[j] = bf16w(rw[t]);
+                ta[j] = TI ? ca : tok(pg.a[j / 4], j % 4);
+                tp[j] = TI ? cp : tok(pg.p[j / 4], j % 4);
+                tk[j] = tok(pg.k[j / 4], j % 4);
+                tr[j] = bf16w((&pg.r[j / 4].x)[j % 4]);
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -225,16 +252,16 @@ __device__ __forceinline__ float scan_chunk(const uint16_t* __restrict__ stg, co
     for (int g = 0; g < 2; ++g) {
         const ScanGroup& cur = gr[g];
         if (g == 0) read_group<SW, TI, NOQ>(gr[1], stg, rw, sl, tb + 8);
+        uint32_t qh[4], ql[4], kh[4], kl[4];   // 8 tokens, two per word
 #pragma unroll
         for (int j2 = 0; j2 < 4; ++j2) {
             float qp2[2], kn2[2];
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int i = 2 * j2 + e, t = tb + 8 * g + i;
-                const float av = TI ? ca : bf16w(cur.a[i]), pv = TI ? cp : bf16w(cur.p[i]);
-                const float kv = bf16w(cur.k[i]), qv = NOQ ? 0.f : bf16w(cur.q[i]);
-                const uint32_t rword = i < 4 ? (&cur.r[0].x)[i] : (&cur.r[1].x)[i - 4];
-                const float rv = bf16w(rword);
+                const float av = TI ? ca : tok(cur.a[i / 4], i % 4), pv = TI ? cp : tok(cur.p[i / 4], i % 4);
+                const float kv = tok(cur.k[i / 4], i % 4), qv = NOQ ? 0.f : tok(cur.q[i / 4], i % 4);
+                const float rv = bf16w((&cur.r[i / 4].x)[i % 4]);
                 const float kr = kv * rv;
                 const float zn = fmaf(pv, xw, av * av * zw);
                 const float xn = fmaf(kr * kv, zn, xw);
@@ -254,22 +281,16 @@ __device__ __forceinline__ float scan_chunk(const uint16_t* __restrict__ stg, co
                     if (sl == SW - 1) o.yv[t] = ws;
                 }
             }
-            uint32_t qh, ql, kh, kl;
-            if constexpr (!NOQ) split2(qp2[0], qp2[1], qh, ql);
-            split2(kn2[0], kn2[1], kh, kl);
-            const int t = tb + 8 * g + 2 * j2;
-            const int e0 = t * LQ + hf * kQPad + n, e1 = e0 + LQ;   // rows t, t + 1
-            if constexpr (!NOQ) {
-                o.qh[e0] = static_cast<uint16_t>(qh);
-                o.qh[e1] = static_cast<uint16_t>(qh >> 16);
-                o.ql[e0] = static_cast<uint16_t>(ql);
-                o.ql[e1] = static_cast<uint16_t>(ql >> 16);
-            }
-            o.kh[e0] = static_cast<uint16_t>(kh);
-            o.kh[e1] = static_cast<uint16_t>(kh >> 16);
-            o.kl[e0] = static_cast<uint16_t>(kl);
-            o.kl[e1] = static_cast<uint16_t>(kl >> 16);
+            if constexpr (!NOQ) split2(qp2[0], qp2[1], qh[j2], ql[j2]);
+            split2(kn2[0], kn2[1], kh[j2], kl[j2]);
         }
+        const int e0 = nt_off(n, tb + 8 * g);
+        if constexpr (!NOQ) {
+            *reinterpret_cast<uint4*>(o.qh + e0) = uint4{qh[0], qh[1], qh[2], qh[3]};
+            *reinterpret_cast<uint4*>(o.ql + e0) = uint4{ql[0], ql[1], ql[2], ql[3]};
+        }
+        *reinterpret_cast<uint4*>(o.kh + e0) = uint4{kh[0], kh[1], kh[2], kh[3]};
+        *reinterpret_cast<uint4*>(o.kl + e0) = uint4{kl[0], kl[1], kl[2], kl[3]};
     }
     // ---- the half-1 lanes stand at the chunk end; their lam goes to both halves
     const float iz = fast_rcp(zw);
@@ -336,11 +357,11 @@ __device__ __forceinline__ float scan_wave(unsigned char* smem, int wave, int la
         const int t0 = in ? cn * kC : 0, nt = in ? min(kC, T - t0) : 0;
         const size_t e0 = ((sc.seq0 + t0) * H + h) * DK + wave * SW;
         const uint32_t bytes = nt > 0 ? (uint32_t)((nt - 1) * H * DK + SW) * 2 : 0u;
-        uint16_t* stg = reinterpret_cast<uint16_t*>(stw) + bb * 4 * kSR * SW;
+        uint16_t* stg = reinterpret_cast<uint16_t*>(stw) + bb * 4 * kC * SW;
         auto one = [&](const uint16_t* src, int ti) {
             const rsrc_t rs = make_rsrc(src + e0, bytes);
-            buf_ld128_lds(rs, stg + ti * kSR * SW, in_voff);
-            buf_ld128_lds(rs, stg + (ti * kSR + srow(16)) * SW, in_voff + 16 * tok_bytes);
+            buf_ld128_lds(rs, stg + ti * kC * SW, in_voff);
+            buf_ld128_lds(rs, stg + (ti * kC + 16) * SW, in_voff + 16 * tok_bytes);
         };
         if constexpr (!TI) {
             one(sc.a, 0);
@@ -395,13 +416,13 @@ __device__ __forceinline__ float scan_wave(unsigned char* smem, int wave, int la
             o.yv = reinterpret_cast<float*>(buf + Cfg::YVP) + wave * kC;
             o.mid = reinterpret_cast<float*>(buf + Cfg::MIDS);
             const float x0 = x;
-            const uint16_t* stg = reinterpret_cast<const uint16_t*>(stw) + bb * 4 * kSR * SW;
+            const uint16_t* stg = reinterpret_cast<const uint16_t*>(stw) + bb * 4 * kC * SW;
             const uint32_t* rwc = rw + bb * 64;
             if (nt == kC)
-                x = scan_chunk<SW, Cfg::LQ, YV, true, TI, NOQ, REV>(stg, rwc, sl, hf, n, nt, x, o, ca, cp, chk, lm,
+                x = scan_chunk<SW, YV, true, TI, NOQ, REV>(stg, rwc, sl, hf, n, nt, x, o, ca, cp, chk, lm,
                                                                   pm);
             else
-                x = scan_chunk<SW, Cfg::LQ, YV, false, TI, NOQ, REV>(stg, rwc, sl, hf, n, nt, x, o, ca, cp, chk, lm,
+                x = scan_chunk<SW, YV, false, TI, NOQ, REV>(stg, rwc, sl, hf, n, nt, x, o, ca, cp, chk, lm,
                                                                    pm);
             if (!REV && save) {
                 if (hf) {
