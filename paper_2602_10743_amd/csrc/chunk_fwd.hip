@@ -10,8 +10,8 @@
 // v_mfma_f32_16x16x32_bf16 with split-bf16 operands for the fp32 factors
 // (kla_mfma.hpp), accumulating in fp32.
 //
-// One workgroup per (batch, head, value tile of up to 64 channels): scan waves
-// walk chunk c while MFMA waves (16 value channels each, the state H[dk, 16]
+// One workgroup per (batch, head, segment of the sequence, value tile): scan waves
+// walk chunk c while MFMA waves (16 or 32 value channels each, the state H[dk, 16]
 // in registers) consume chunk c - 1 -- attention tiles, readout, y, state
 // update; operands that run across the rows of a tile (Kn^T, V) are read with
 // transposing LDS reads (lds_tr8), so each tile is stored once.  The MFMA
@@ -23,10 +23,13 @@
 namespace kla {
 namespace {
 
-template <int DK, int DV, bool YV, bool TI, bool NOY, bool SAVE>
-__global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Shape s, FwdArgs g, float* saved_lam,
-                                                                         float* saved_H) {
-    using Cfg = ChunkCfg<DK, DV>;
+// Start beliefs (lam0, eta0) are indexed by sequence, or with ns > 1 segments by
+// bh * ns + segment; so are the states a NOY pass leaves in etaT.  Otherwise the last
+// segment writes the final belief.
+template <int DK, int DV, bool WIDE, bool YV, bool TI, bool NOY, bool SAVE>
+__global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void fwd_chunk_kernel(Shape s, Seg sg, FwdArgs g,
+                                                                               float* saved_lam, float* saved_H) {
+    using Cfg = ChunkCfg<DK, DV, WIDE>;
     constexpr int DVT = Cfg::DVT, NTILE = Cfg::NTILE, DCW = Cfg::DCW, NDT = Cfg::NDT, NSW = Cfg::NSW;
     constexpr int SW = Cfg::SW, NRT = Cfg::NRT, KSN = Cfg::KSN;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -39,21 +42,27 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
     const uint16_t* r = static_cast<const uint16_t*>(g.r);
     uint16_t* y = static_cast<uint16_t*>(g.y);
 
-    int bh, tile;
-    xcd_tile_map(blockIdx.x, s.B * s.H, NTILE, bh, tile);
+    int vi, tile;
+    xcd_tile_map(blockIdx.x, s.B * s.H * sg.run, NTILE, vi, tile);
+    const int bh = vi / sg.run, seg = vi % sg.run;
     const int b = bh / s.H, h = bh % s.H;
-    const int H = s.H, T = s.T;
+    const int c0 = seg * sg.lc, nct = (s.T + kC - 1) / kC;   // this segment's first chunk, the sequence's chunks
+    const int H = s.H, T = min(s.T - c0 * kC, sg.lc * kC);
+    const size_t start = (size_t)bh * sg.ns + seg;           // row of the start belief
+    const size_t out = NOY ? start : bh;
+    const bool ends = NOY || seg == sg.ns - 1;               // leaves a final belief
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform role
     const int l16 = lane & 15, g4 = lane >> 4;
     const int nchunk = (T + kC - 1) / kC;
-    const size_t seq0 = (size_t)b * T;   // token index of this sequence's first token
+    const size_t seq0 = (size_t)b * s.T + (size_t)c0 * kC;   // token index of the first token
 
     if (wave < NSW) {
         // ================================================================ scan waves
-        const ScanSrc sc{a, p, k, q, r, v, tile * DVT, seq0, H, h, T, nchunk, bh, g.ou_a, g.ou_p, g.ou_d, g.range_flag};
+        const ScanSrc sc{a, p, k, q, r, v, tile * DVT, seq0, H, h, T, nchunk, start, g.ou_a, g.ou_p, g.ou_d,
+                         g.range_flag};
         const float x = scan_wave<Cfg, YV, false, TI, NOY>(smem, wave, lane, sc, g.lam0, SAVE);
-        if (g.lamT && lane < SW && tile == 0) g.lamT[(size_t)bh * DK + wave * SW + lane] = x;
+        if (g.lamT && ends && lane < SW && tile == 0) g.lamT[out * DK + wave * SW + lane] = x;
     } else {
         // ================================================================ MFMA waves
         const int m = wave - NSW;
@@ -69,7 +78,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)
                     Hs[rt][dt][rr] =
-                        g.eta0 ? g.eta0[((size_t)bh * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] : 0.f;
+                        g.eta0 ? g.eta0[(start * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] : 0.f;
 
         // state rows 16 rt .. 16 rt + 15 (this wave's columns) into the saved slot behind rs
         const uint32_t h_voff = (uint32_t)(4 * g4 * DV + dm0 + l16) * 4;
@@ -81,7 +90,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                     buf_st32s(Hs[rt][dt][rr], rs, h_voff, (uint32_t)((16 * rt + rr) * DV + 16 * dt) * 4);
         };
         auto slot_rsrc = [&](int slot) {
-            return make_rsrc(saved_H + ((size_t)bh * (nchunk + 1) + slot) * DK * DV, DK * DV * 4);
+            return make_rsrc(saved_H + ((size_t)bh * (nct + 1) + c0 + slot) * DK * DV, DK * DV * 4);
         };
         // eta0 has arrived: without this the loop would wait for it at the first use of the state,
         // and with it, every round, for all stores of the round before (65536-token forward without
@@ -193,7 +202,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
                 if (SAVE && tile == 0) {
                     constexpr int NV4 = kLamRows * DK / 4;
                     const float4* src = reinterpret_cast<const float4*>(buf + Cfg::MIDS);
-                    float4* dst = reinterpret_cast<float4*>(saved_lam + ((size_t)bh * nchunk + cc) * kLamRows * DK);
+                    float4* dst = reinterpret_cast<float4*>(saved_lam + ((size_t)bh * nct + c0 + cc) * kLamRows * DK);
                     for (int i = m * 64 + lane; i < NV4; i += Cfg::NMW * 64) dst[i] = src[i];
                 }
 
@@ -208,46 +217,56 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV>::NTHR)) void fwd_chunk_kernel(Sha
             barrier_lds();
         }
 
-        if constexpr (SAVE) {   // the final state closes the saved sequence
+        if (SAVE && ends) {   // the final state closes the saved sequence
             const rsrc_t rs = slot_rsrc(nchunk);
 #pragma unroll
             for (int rt = 0; rt < NRT; ++rt) save_rows(rs, rt);
         }
-        if (g.etaT) {
+        if (g.etaT && ends) {
 #pragma unroll
             for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr)
-                        g.etaT[((size_t)bh * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] = Hs[rt][dt][rr];
+                        g.etaT[(out * DK + 16 * rt + 4 * g4 + rr) * DV + dm0 + 16 * dt + l16] = Hs[rt][dt][rr];
         }
     }
 }
 
-template <int DK, int DV, bool YV, bool TI, bool NOY, bool SAVE>
-hipError_t launch_fwd_v(const Shape& s, const FwdArgs& a, float* saved_lam, float* saved_H, hipStream_t st) {
-    using Cfg = ChunkCfg<DK, DV>;
-    auto kern = fwd_chunk_kernel<DK, DV, YV, TI, NOY, SAVE>;
+template <int DK, int DV, bool WIDE, bool YV, bool TI, bool NOY, bool SAVE>
+hipError_t launch_fwd_v(const Shape& s, const Seg& sg, const FwdArgs& a, float* saved_lam, float* saved_H,
+                        hipStream_t st) {
+    using Cfg = ChunkCfg<DK, DV, WIDE>;
+    auto kern = fwd_chunk_kernel<DK, DV, WIDE, YV, TI, NOY, SAVE>;
     // more than 64 KiB of LDS must be opted into once per kernel (thread-safe static init)
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
     if (attr != hipSuccess) return attr;
-    const unsigned grid = (unsigned)(s.B * s.H * Cfg::NTILE);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NTHR), Cfg::BYTES, st, s, a, saved_lam, saved_H);
+    const unsigned grid = (unsigned)(s.B * s.H * sg.run * Cfg::NTILE);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NTHR), Cfg::BYTES, st, s, sg, a, saved_lam, saved_H);
     return hipGetLastError();
 }
 
 // the readout variance adds a cross-lane sum per token and the saved context its stores,
 // so they are separate instantiations, as are the time-invariant gates and the state-only
 // pass (no y: the segment-parallel forward's first pass)
-template <int DK, int DV, bool TI>
-hipError_t launch_fwd(const Shape& s, const FwdArgs& a, float* saved_lam, float* saved_H, hipStream_t st) {
+template <int DK, int DV, bool WIDE, bool TI>
+hipError_t launch_fwd(const Shape& s, const Seg& sg, const FwdArgs& a, float* saved_lam, float* saved_H,
+                      hipStream_t st) {
+    if (!a.y) return launch_fwd_v<DK, DV, WIDE, false, TI, true, false>(s, sg, a, nullptr, nullptr, st);
     if (saved_H)
-        return a.yvar ? launch_fwd_v<DK, DV, true, TI, false, true>(s, a, saved_lam, saved_H, st)
-                      : launch_fwd_v<DK, DV, false, TI, false, true>(s, a, saved_lam, saved_H, st);
-    return a.yvar ? launch_fwd_v<DK, DV, true, TI, false, false>(s, a, nullptr, nullptr, st)
-                  : launch_fwd_v<DK, DV, false, TI, false, false>(s, a, nullptr, nullptr, st);
+        return a.yvar ? launch_fwd_v<DK, DV, WIDE, true, TI, false, true>(s, sg, a, saved_lam, saved_H, st)
+                      : launch_fwd_v<DK, DV, WIDE, false, TI, false, true>(s, sg, a, saved_lam, saved_H, st);
+    return a.yvar ? launch_fwd_v<DK, DV, WIDE, true, TI, false, false>(s, sg, a, nullptr, nullptr, st)
+                  : launch_fwd_v<DK, DV, WIDE, false, TI, false, false>(s, sg, a, nullptr, nullptr, st);
+}
+
+template <int DK, int DV, bool WIDE>
+hipError_t launch_fwd_ti(const Shape& s, const Seg& sg, const FwdArgs& a, float* saved_lam, float* saved_H,
+                         hipStream_t st) {
+    return a.ou_a ? launch_fwd<DK, DV, WIDE, true>(s, sg, a, saved_lam, saved_H, st)
+                  : launch_fwd<DK, DV, WIDE, false>(s, sg, a, saved_lam, saved_H, st);
 }
 
 }  // namespace
@@ -263,7 +282,16 @@ size_t chunked_saved_bytes(const Shape& s) {
     return (size_t)s.B * s.H * s.dk * (kLamRows * nchunk + (nchunk + 1) * (size_t)s.dv) * sizeof(float);
 }
 
-hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st) {
+bool chunked_wide(const Shape& s, int groups) {
+    // dv = 128 in one workgroup per (sequence, segment) instead of two: where that takes fewer
+    // rounds of the chip's 256 CUs (each workgroup fills a CU), the walk's repetition is saved
+    // (a wide round takes 3.6 us against 3.1)
+    const int n = s.B * s.H * groups;
+    return s.dv == 128 && s.dk >= 64 && (2 * n + 255) / 256 > (n + 255) / 256;
+}
+
+hipError_t launch_forward_chunked_seg(const Shape& s, int ns, int lc, int run, const FwdArgs& a, void* saved,
+                                      hipStream_t st) {
     float* saved_lam = nullptr;
     float* saved_H = nullptr;
     if (saved) {
@@ -271,17 +299,22 @@ hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved,
         saved_lam = static_cast<float*>(saved);
         saved_H = saved_lam + (size_t)s.B * s.H * nchunk * kLamRows * s.dk;
     }
-#define KLA_FWD_CASE(DK_, DV_)                                                                         \
-    if (s.dk == DK_ && s.dv == DV_) {                                                                  \
-        if (!a.y) return launch_fwd_v<DK_, DV_, false, false, true, false>(s, a, nullptr, nullptr, st); \
-        return a.ou_a ? launch_fwd<DK_, DV_, true>(s, a, saved_lam, saved_H, st)                        \
-                      : launch_fwd<DK_, DV_, false>(s, a, saved_lam, saved_H, st);                      \
+    const Seg sg{ns, lc, run};
+    if (chunked_wide(s, run)) {
+        if (s.dk == 64) return launch_fwd_ti<64, 128, true>(s, sg, a, saved_lam, saved_H, st);
+        if (s.dk == 128) return launch_fwd_ti<128, 128, true>(s, sg, a, saved_lam, saved_H, st);
     }
+#define KLA_FWD_CASE(DK_, DV_) \
+    if (s.dk == DK_ && s.dv == DV_) return launch_fwd_ti<DK_, DV_, false>(s, sg, a, saved_lam, saved_H, st);
 #define KLA_FWD_ROW(DK_) KLA_FWD_CASE(DK_, 16) KLA_FWD_CASE(DK_, 32) KLA_FWD_CASE(DK_, 64) KLA_FWD_CASE(DK_, 128)
     KLA_FWD_ROW(32) KLA_FWD_ROW(64) KLA_FWD_ROW(128)
 #undef KLA_FWD_ROW
 #undef KLA_FWD_CASE
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st) {
+    return launch_forward_chunked_seg(s, 1, (s.T + kC - 1) / kC, 1, a, saved, st);
 }
 
 }  // namespace kla

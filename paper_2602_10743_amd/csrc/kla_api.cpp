@@ -198,8 +198,8 @@ kla_status forward_impl(const kla_desc* desc, const kla::FwdArgs& a, bool ou, vo
     // layout the backward reads (saves_chunked)
     const bool chunked = saved ? saves_chunked(s) : kla::chunked_supported(s);
     const bool c64 = kla::c64_supported(s);
-    if (!saved && !ou && kla::forward_segments(s) > 1)
-        e = kla::launch_forward_segmented(s, fa, static_cast<char*>(ws) + kAlign, stream);
+    if (chunked && kla::forward_segments(s) > 1)
+        e = kla::launch_forward_segmented(s, fa, saved, static_cast<char*>(ws) + kAlign, stream);
     else if (chunked)
         e = kla::launch_forward_chunked(s, fa, saved, stream);
     else if (kla::c64p_supported(s))

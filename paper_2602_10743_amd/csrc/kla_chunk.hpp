@@ -99,12 +99,20 @@ __device__ __forceinline__ Swap32 swap32(float x) {
     return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
-template <int DK_, int DV_>
+// A sequence as ns segments of lc chunks (the last one shorter), each a workgroup (set) of
+// its own, of which the first `run` are run; {1, all chunks, 1} walks it whole.
+struct Seg {
+    int ns, lc, run;
+};
+
+// WIDE (dv = 128): all value channels in one workgroup, 32 per MFMA wave, so the precision
+// walk and the attention tiles are formed once per head instead of once per 64 channels.
+template <int DK_, int DV_, bool WIDE = false>
 struct ChunkCfg {
     static constexpr int DK = DK_, DV = DV_;
-    static constexpr int DVT = DV < 64 ? DV : 64;    // value channels per workgroup
+    static constexpr int DVT = WIDE ? DV : DV < 64 ? DV : 64;   // value channels per workgroup
     static constexpr int NTILE = DV / DVT;
-    static constexpr int DCW = 16;                   // value channels per MFMA wave
+    static constexpr int DCW = WIDE ? 32 : 16;       // value channels per MFMA wave
     static constexpr int NDT = DCW / 16;
     static constexpr int NMW = DVT / DCW;            // MFMA waves
     static constexpr int SW = 32;                    // key slots per scan wave
@@ -130,7 +138,8 @@ struct ChunkCfg {
     static constexpr int STG_WAVE = STG_L + 2 * 128 * 4;
     static constexpr int BYTES = STG + NSW * STG_WAVE;
     static_assert(DK >= 32 && DK % 32 == 0, "chunked path needs dk >= 32");
-    static_assert(DVT % 16 == 0 && NVL >= 1 && NVL * TPV == kC, "value tile sizes");
+    static_assert(DVT % 16 == 0 && NVL >= 1 && NVL * TPV == kC && NVL < 8 * NSW, "value tile sizes");
+    static_assert(!WIDE || (DV == 128 && DK >= 64), "wide value tiles");
     static_assert(BYTES <= 160 * 1024, "LDS budget of one workgroup");
 };
 
@@ -309,8 +318,9 @@ struct ScanSrc {
     const uint16_t *a, *p, *k, *q, *r;   // [B, T, H, DK] (r: [B, T, H])
     const uint16_t* tile;                 // per-token value tensor [B, T, H, DV] staged per chunk
     int tcol0;                            // first column of the value tile
-    size_t seq0;                          // b * T
-    int H, h, T, nchunk, bh;
+    size_t seq0;                          // index of the first token
+    int H, h, T, nchunk;                  // T tokens in nchunk chunks
+    size_t lam_row;                       // row of lam_in: this walk's start, or (backwards) its first chunk's
     const float *oa = nullptr, *op = nullptr, *od = nullptr;   // OU parameters [H, DK] (TI)
     int* range_flag = nullptr;   // set to 1 when the walk leaves fp32 range, or none
 };
@@ -337,7 +347,7 @@ __device__ __forceinline__ float scan_wave(unsigned char* smem, int wave, int la
     float x = 1.f;                              // lam at the chunk start
     float chk = 0.f;                            // range check of the walk (scan_chunk)
     float lm = 0.f, pm = 0.f;                   // half 1: lam_16, P_16 of the chunk walked last
-    if (!REV && lam_in) x = lam_in[(size_t)sc.bh * DK + n];
+    if (!REV && lam_in) x = lam_in[sc.lam_row * DK + n];
     float ca = 0.f, cp = 0.f;                   // time-invariant gates of slot n
     if constexpr (TI) ou_gates(sc.oa[h * DK + n], sc.op[h * DK + n], sc.od[h * DK + n], ca, cp);
     unsigned char* stw = smem + Cfg::STG + wave * Cfg::STG_WAVE;
@@ -372,7 +382,7 @@ __device__ __forceinline__ float scan_wave(unsigned char* smem, int wave, int la
         const rsrc_t rr = make_rsrc(sc.r + (sc.seq0 + t0) * H + h, nt > 0 ? (uint32_t)((nt - 1) * H + 1) * 2 : 0u);
         buf_ld16_lds(rr, rw + bb * 64, (uint32_t)lane * H * 2);
         if constexpr (REV) {
-            const rsrc_t rl = make_rsrc(lam_in + ((size_t)sc.bh * nchunk + (in ? cn : 0)) * kLamRows * DK + wave * SW,
+            const rsrc_t rl = make_rsrc(lam_in + (sc.lam_row + (in ? cn : 0)) * kLamRows * DK + wave * SW,
                                         in ? (uint32_t)(2 * DK + SW) * 4 : 0u);
             buf_ld32_lds(rl, lw + bb * 128, (uint32_t)(hf * DK + sl) * 4);
             buf_ld32_lds(rl, lw + bb * 128 + 64, (uint32_t)(2 * DK + sl) * 4);

@@ -98,11 +98,17 @@ hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved,
 bool chunked_bwd_supported(const Shape& s);
 size_t chunked_bwd_workspace(const Shape& s);
 hipError_t launch_backward_chunked(const Shape& s, const BwdArgs& a, const void* saved, void* ws, hipStream_t st);
-// Segment-parallel chunked forward for few long sequences (no saved context): the number of
-// segments (1: not used), its workspace and launch.
+// Whether dv = 128 runs as one workgroup per head and segment (groups: segments run).
+bool chunked_wide(const Shape& s, int groups);
+// The chunked forward over the first `run` of ns segments of lc chunks, each from its own start
+// belief (lam0, eta0 [B H ns]).  Without y only the segments' final states (etaT [B H ns]).
+hipError_t launch_forward_chunked_seg(const Shape& s, int ns, int lc, int run, const FwdArgs& a, void* saved,
+                                      hipStream_t st);
+// Segment-parallel chunked forward for few sequences: the number of segments (1: not used), its
+// workspace and launch.
 int forward_segments(const Shape& s);
 size_t forward_segmented_workspace(const Shape& s);
-hipError_t launch_forward_segmented(const Shape& s, const FwdArgs& a, void* ws, hipStream_t st);
+hipError_t launch_forward_segmented(const Shape& s, const FwdArgs& a, void* saved, void* ws, hipStream_t st);
 // kla_backward with a saved context in at most KLA_NOALLOC_SCRATCH_BYTES of workspace where the
 // shape allows it (kla_api.cpp): the bytes it needs, and the call
 size_t backward_least_workspace(const kla_desc* desc);

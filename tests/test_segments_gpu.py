@@ -1,0 +1,85 @@
+"""The segment-parallel bf16 forward and backward (few sequences, csrc/chunk_seg.hip) against
+the fp64 oracle: ragged lengths, segments of one chunk, the last segment of one token, wide
+and 64-channel value tiles, per-token and OU gates, with and without a saved context.
+
+Tolerances as in test_parity_gpu.py: bf16 outputs 2e-2, fp32 beliefs and variances 1e-4
+(etaT, whose products are split-bf16: 2e-2)."""
+import numpy as np
+import pytest
+
+import kla_inputs as K
+import oracle
+from kla_testutil import TOL, log, rel_err, rel_err_sum, to_np, to_torch
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TOKEN = ("q", "k", "v", "a", "p", "r")
+
+
+@pytest.fixture(scope="module")
+def kla():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_10743_amd as lib
+    lib._load()
+    return lib
+
+
+def _f32(x):
+    return torch.tensor(np.asarray(x, dtype=np.float32), device=DEV)
+
+
+def _check(got, ref, names, tol):
+    for n in names:
+        x = to_np(got[n])
+        assert np.all(np.isfinite(x)), f"{n} not finite"
+        r = K.quantise(ref[n], "bf16") if n == "y" else ref[n]
+        e = rel_err(x, r)
+        assert e <= tol, f"{n}: {e:.2e}"
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv", [
+    (1, 705, 2, 128, 128),   # wide tiles; a last segment of one token
+    (1, 1000, 1, 64, 128),   # wide tiles, segments of one chunk
+    (2, 513, 3, 64, 64), (1, 640, 2, 32, 32), (1, 799, 1, 32, 128), (3, 900, 20, 64, 32), (1, 600, 2, 128, 16)])
+@pytest.mark.parametrize("ou", [False, True])
+def test_against_oracle(kla, B, T, H, dk, dv, ou):
+    log(f"segments B{B} T{T} H{H} dk{dk} dv{dv} ou={ou}")
+    case = K.random_case(B, T, H, dk, dv, "bf16", seed=T + dk, dist="lm")
+    g = np.random.default_rng(T)
+    q32 = lambda x: x.astype(np.float32).astype(np.float64)
+    lam0, eta0 = q32(0.5 + g.random((B, H, dk))), q32(g.standard_normal((B, H, dk, dv)))
+    dlamT, detaT = q32(g.standard_normal((B, H, dk))), q32(g.standard_normal((B, H, dk, dv)))
+    dyvar = q32(g.standard_normal((B, T, H)))
+    x = {n: to_torch(case[n], "bf16", DEV) for n in TOKEN + ("dy",)}
+    if ou:
+        P = K.ou_params(H, dk, seed=T)
+        Pd = [P[n].astype(np.float64) for n in ("a", "p", "delta")]
+        pt = [_f32(P[n]) for n in ("a", "p", "delta")]
+        fa = (x["q"], x["k"], x["v"], *pt, x["r"], _f32(lam0), _f32(eta0))
+        oa = (case["q"], case["k"], case["v"], *Pd, case["r"], lam0, eta0)
+        fwd, bwd, ofwd = kla.kla_forward_ou, kla.kla_backward_ou, oracle.forward_ou
+        rg = oracle.backward_ou(*oa, case["dy"], dlamT, detaT, dyvar=dyvar, with_mass=True)
+        tok = ("dq", "dk", "dv", "dr")
+    else:
+        fa = tuple(x[n] for n in TOKEN) + (_f32(lam0), _f32(eta0))
+        oa = tuple(case[n] for n in TOKEN) + (lam0, eta0)
+        fwd, bwd, ofwd = kla.kla_forward, kla.kla_backward, oracle.forward
+        rg = oracle.backward(*oa, case["dy"], dlamT, detaT, dyvar=dyvar)
+        tok = ("dq", "dk", "dv", "da", "dp", "dr")
+    ref = ofwd(*oa)
+    for save in (False, True):
+        out = fwd(*fa, want_var=True, save=save)
+        _check(out, ref, ("y", "etaT"), TOL["bf16"])
+        _check(out, ref, ("yvar", "lamT"), TOL["f32"])
+    if dv == 16:
+        return   # its saved context and backward are the token-recurrent ones
+    for saved in (out["saved"], None):
+        got = bwd(*fa, x["dy"], _f32(dlamT), _f32(detaT), saved=saved, dyvar=_f32(dyvar))
+        _check(got, rg, tok + ("dlam0", "deta0"), TOL["bf16"])
+        if ou:
+            for n in ("da", "dp", "ddelta"):
+                e = rel_err_sum(to_np(got[n]), rg[n], rg["mass_" + n])
+                assert e <= TOL["bf16"], f"{n}: {e:.2e}"
