@@ -152,15 +152,23 @@ __device__ __forceinline__ void buf_st32(float v, rsrc_t r, uint32_t voff) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, 0, 0);
 }
 
-template <int DK, int DV, bool TI, bool YG>
-__global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, BwdArgs g,
+// SPLIT (segments of few sequences, which run side by side): the precision adjoint c that a
+// segment starts from is not known yet, so phase 5 is left to bwd_grad_kernel: dqt and dkh go
+// to xy [B H][chunk][2][kC][dk] and the chunk's composed adjoint step, with the exact change
+// of S, to coef [B H][chunk][4][dk].  gend: the adjoints of the segments' last states.
+template <int DK, int DV, bool TI, bool YG, bool SPLIT>
+__global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, Seg sg, BwdArgs g,
                                                                        const float* __restrict__ saved_lam,
                                                                        const float* __restrict__ saved_H,
-                                                                       float* __restrict__ dr_part) {
+                                                                       float* __restrict__ dr_part,
+                                                                       const float* __restrict__ gend,
+                                                                       float* __restrict__ xy,
+                                                                       float* __restrict__ coef) {
     using Cfg = DkCfg<DK, DV>;
     constexpr int NP = Cfg::NP, NW = Cfg::NW, KSD = Cfg::KSD, NRD = Cfg::NRD, LQ2 = Cfg::LQ2, LX = Cfg::LX;
     constexpr int NG = Cfg::NG;
-    constexpr int NST = TI ? 3 : 5;   // gradient stores per round: dq, dk(, dabar, dpbar) and dr
+    // stores per round: dq, dk(, dabar, dpbar) and dr; SPLIT: dqt, dkh of 4 tokens, two of coef
+    constexpr int NST = SPLIT ? 10 : TI ? 3 : 5;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) uint16_t s_out[NP * 4 * kC * 16];
     __shared__ __align__(16) float s_drc[NP * kC * 17];
@@ -173,10 +181,12 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     const uint16_t* vv = static_cast<const uint16_t*>(g.v);
     const uint16_t* dy = static_cast<const uint16_t*>(g.dy);
 
-    int bh, ntile;
-    xcd_tile_map(blockIdx.x, s.B * s.H, Cfg::NNT, bh, ntile);
+    int vi, ntile;
+    xcd_tile_map(blockIdx.x, s.B * s.H * sg.ns, Cfg::NNT, vi, ntile);
+    const int bh = vi / sg.ns, seg = vi % sg.ns;
     const int b = bh / s.H, h = bh % s.H;
-    const int H = s.H, T = s.T;
+    const int c0 = seg * sg.lc, nct = (s.T + kC - 1) / kC;   // this segment's first chunk, the sequence's chunks
+    const int H = s.H, T = min(s.T - c0 * kC, sg.lc * kC);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pr = wave % NP, e = wave / NP;     // pair, half of the chunk (a pair shares a SIMD)
@@ -184,17 +194,19 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     const int nl = l16, gg = 4 * e + g4;         // walk lanes: slot, token group (tokens 4 gg .. 4 gg + 3)
     const int n0w = ntile * Cfg::NTN + 16 * pr;  // the pair's first key slot
     const int nchunk = (T + kC - 1) / kC;
-    const size_t seq0 = (size_t)b * T;
-    const size_t nbt = (size_t)s.B * T * H;
+    const size_t seq0 = (size_t)b * s.T + (size_t)c0 * kC;
+    const size_t row_c0 = (size_t)bh * nct + c0;       // the first chunk's row of the per-chunk arrays
+    const size_t slot_c0 = (size_t)bh * (nct + 1) + c0;   // and its slot of the saved states
+    const size_t nbt = (size_t)s.B * s.T * H;
     unsigned char* wb = smem + Cfg::PAIR0 + pr * Cfg::PAIR;
     const uint32_t tok_k = (uint32_t)H * DK * 2;   // bytes between tokens of a [.., H, DK] tensor
     const uint32_t tok_v = (uint32_t)H * DV * 2;
 
     // ---- carries of the reverse recursions (every lane of both waves holds its slot's values)
-    float cT = g.dlamT ? g.dlamT[(size_t)bh * DK + n0w + nl] : 0.f;
+    float cT = !SPLIT && g.dlamT ? g.dlamT[(size_t)bh * DK + n0w + nl] : 0.f;
     float ST = 0.f;
-    if (g.detaT) {   // final-state term sum_d detaT H_T, split over the four lane groups
-        const float* HT = saved_H + (((size_t)bh * (nchunk + 1) + nchunk) * DK + n0w + nl) * DV;
+    if (!SPLIT && g.detaT) {   // final-state term sum_d detaT H_T, split over the four lane groups
+        const float* HT = saved_H + ((slot_c0 + nchunk) * DK + n0w + nl) * DV;
         const float* dT = g.detaT + ((size_t)bh * DK + n0w + nl) * DV;
         for (int d = g4 * (DV / 4); d < (g4 + 1) * (DV / 4); ++d) ST += dT[d] * HT[d];
     }
@@ -211,12 +223,13 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     }
 
     // G^T[d, n] for d = 16 rd + 4 g4 + rr, n = n0w + l16 (carried by wave 1 of the pair)
+    const float* gsrc = SPLIT ? gend + (size_t)vi * DK * DV : g.detaT ? g.detaT + (size_t)bh * DK * DV : nullptr;
     f32x4 GT[NRD];
 #pragma unroll
     for (int rd = 0; rd < NRD; ++rd)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr)
-            GT[rd][rr] = (e == 1 && g.detaT) ? g.detaT[((size_t)bh * DK + n0w + l16) * DV + 16 * rd + 4 * g4 + rr] : 0.f;
+            GT[rd][rr] = (e == 1 && gsrc) ? gsrc[(size_t)(n0w + l16) * DV + 16 * rd + 4 * g4 + rr] : 0.f;
 
     // ---- requests of chunk cn into buffer bb (chunks outside the sequence: empty, writing
     // zeros), one load per part so that they can be spread over a round:
@@ -248,7 +261,7 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 buf_ld32_lds(rv, wb + Cfg::GV + bb * 256, (uint32_t)lane * H * 4);
             } else {
                 // lanes 16 i + l: row i of the saved walk state (lam_0, lam_16, P_16) for slot n0w + l
-                const rsrc_t rl = make_rsrc(saved_lam + ((size_t)bh * nchunk + (in ? cn : 0)) * kLamRows * DK + n0w,
+                const rsrc_t rl = make_rsrc(saved_lam + (row_c0 + (in ? cn : 0)) * kLamRows * DK + n0w,
                                             in ? (uint32_t)(2 * DK + 16) * 4 : 0u);
                 buf_ld32_lds(rl, wb + Cfg::LW + bb * 256, (uint32_t)((lane >> 4) * DK + (lane & 15)) * 4);
             }
@@ -277,7 +290,7 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             // saved chunk-start state rows H0[n0w + l16][32 ks + 8 g4 .. + 7] (wave 0, for X)
             float4 h0[KSD][2];
             if constexpr (E == 0) {
-                const float* H0 = saved_H + (((size_t)bh * (nchunk + 1) + c) * DK + n0w + l16) * DV;
+                const float* H0 = saved_H + ((slot_c0 + c) * DK + n0w + l16) * DV;
 #pragma unroll
                 for (int ks = 0; ks < KSD; ++ks) {
                     h0[ks][0] = *reinterpret_cast<const float4*>(H0 + 32 * ks + 8 * g4);
@@ -567,16 +580,21 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 w_[j] = w;
                 al_[j] = al;
                 be_[j] = be;
-                dq_[j] = fmaf(2.f, qg, dqt) * ilam;
-                rdk_[j] = rv * dkh;
-                kr2_[j] = 2.f * kh;
-                ia_[j] = ia;
-                a2r2_[j] = 2.f * av * rho2;
-                lp_[j] = lam_p;
-                den_[j] = den;
-                lpr2_[j] = lam_p * rho2;
-                kdk_[j] = kv * dkh;
-                kk_[j] = kv * kv;
+                if constexpr (SPLIT) {
+                    dq_[j] = ok ? dqt : 0.f;
+                    kdk_[j] = ok ? dkh : 0.f;
+                } else {
+                    dq_[j] = fmaf(2.f, qg, dqt) * ilam;
+                    rdk_[j] = rv * dkh;
+                    kr2_[j] = 2.f * kh;
+                    ia_[j] = ia;
+                    a2r2_[j] = 2.f * av * rho2;
+                    lp_[j] = lam_p;
+                    den_[j] = den;
+                    lpr2_[j] = lam_p * rho2;
+                    kdk_[j] = kv * dkh;
+                    kk_[j] = kv * kv;
+                }
                 Cm = al * Cm - be * Dm - (al * w + be * u);
                 Bm = al * Bm - be;
                 Am = al * Am;
@@ -602,6 +620,33 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             qs[(gg * 4 + 3) * 16 + nl] = Dm;
             barrier_lds();   // the group summaries are in
 
+            if constexpr (SPLIT) {
+                // dqt, dkh of the lane's tokens, and the chunk's composed step: A, B from wave 0, C and
+                // the change of S from wave 1
+                float* xo = xy + (row_c0 + c) * 2 * kC * DK;
+                const rsrc_t rx = make_rsrc(xo, 2 * kC * DK * 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t vo = (uint32_t)((4 * gg + j) * DK + n0w + nl) * 4;
+                    buf_st32s(dq_[j], rx, vo, 0);
+                    buf_st32s(kdk_[j], rx, vo, kC * DK * 4);
+                }
+                float Ac = 1.f, Bc = 0.f, Cc = 0.f, Dc = 0.f;
+#pragma unroll
+                for (int q2 = NG - 1; q2 >= 0; --q2) {
+                    const float A2 = qs[(q2 * 4 + 0) * 16 + nl], B2 = qs[(q2 * 4 + 1) * 16 + nl];
+                    const float C2 = qs[(q2 * 4 + 2) * 16 + nl], D2 = qs[(q2 * 4 + 3) * 16 + nl];
+                    Cc = fmaf(A2, Cc, fmaf(B2, Dc, C2));
+                    Bc = fmaf(A2, Bc, B2);
+                    Ac *= A2;
+                    Dc += D2;
+                }
+                const rsrc_t rc = make_rsrc(coef + (row_c0 + c) * 4 * DK, 4 * DK * 4);
+                const uint32_t vo = g4 == 0 ? (uint32_t)(2 * E * DK + n0w + nl) * 4 : 4 * DK * 4;   // other lanes: dropped
+                buf_st32s(E == 0 ? Ac : Cc, rc, vo, 0);
+                buf_st32s(E == 0 ? Bc : sWT[nl] - sWT[16 + nl], rc, vo, DK * 4);
+                return;
+            }
             // ================================================================ phase 5
             // carries into this group (through the later groups) and out of the chunk; S leaves
             // the chunk with the chunk's exact total, not the sum of its tokens' terms
@@ -693,6 +738,7 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     }
     wait_vm_all();   // the requests for the chunk before the first have landed before exit
     if (g.range_flag && !(fabsf(chk) <= 3.0e38f)) *g.range_flag = 1;
+    if (SPLIT) return;
     if (g.dlam0 && e == 0 && g4 == 0) g.dlam0[(size_t)bh * DK + n0w + nl] = cT;
     if constexpr (TI) {   // part e * B + b of the token sums: the wave's four token groups added
         sum_da += __shfl_xor(sum_da, 16, 64);
@@ -722,14 +768,15 @@ template <int DK, int DV, bool TI, bool YG>
 hipError_t launch_dk(const Shape& s, const BwdArgs& a, const float* saved_lam, const float* saved_H, float* dr_part,
                      hipStream_t st) {
     using Cfg = DkCfg<DK, DV>;
-    auto kern = bwd_dk_kernel<DK, DV, TI, YG>;
+    auto kern = bwd_dk_kernel<DK, DV, TI, YG, false>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
     if (attr != hipSuccess) return attr;
-    hipError_t e = launch_backward_dv(s, a, saved_lam, st);
+    const int nct = (s.T + kC - 1) / kC;
+    hipError_t e = launch_backward_dv(s, 1, nct, false, a, saved_lam, nullptr, nullptr, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(s.B * s.H * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s, a,
-                       saved_lam, saved_H, dr_part);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(s.B * s.H * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s, Seg{1, nct, 1},
+                       a, saved_lam, saved_H, dr_part, nullptr, nullptr, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t n = (size_t)s.B * s.T * s.H;
@@ -741,6 +788,342 @@ hipError_t launch_dk(const Shape& s, const BwdArgs& a, const float* saved_lam, c
     return e;
 }
 
+// ---- the segment-parallel backward of few sequences
+//   1. every segment's but the first's own contribution to the adjoint of the state before it
+//      (bwd_dv_kernel without dV), 2. their scan to the adjoint of every segment's last state,
+//   3. dV and, in 4., the contractions of the key side over all segments at once (SPLIT),
+//   5. a scan of the chunks' adjoint steps for (c, S) at the chunk ends, 6. the gradients.
+struct BwdCut {
+    int ns, lc;
+};
+
+// Microseconds per chunk round at 128 x 128: value side 3.3 (3.8 wide), its state-only pass 2.0,
+// key side 7.4 (SPLIT 6.6); the gradient kernel 1.1 ns per token and head; the other kernels and
+// launches 40.  One workgroup per CU, as in the forward.
+BwdCut bwd_cut(const Shape& s) {
+    const int nct = (s.T + kC - 1) / kC, bh = s.B * s.H, nnt = s.dk / 64 > 0 ? s.dk / 64 : 1, ntile = s.dv == 128 ? 2 : 1;
+    BwdCut c{1, nct};
+    if (nct < 4) return c;
+    auto rounds = [](int wg) { return (wg + 255) / 256; };
+    auto dv_us = [&](int ns) { return chunked_wide(s, ns) ? 3.8 * rounds(bh * ns) : 3.3 * rounds(bh * ns * ntile); };
+    double best = 0.92 * nct * (dv_us(1) + 7.4 * rounds(bh * nnt));
+    for (int wg : {256 / (bh * ntile), 256 / (bh * nnt), 256 / bh}) {
+        if (wg < 2) continue;
+        const int lc = (nct + wg - 1) / wg, ns = (nct + lc - 1) / lc;
+        if (ns < 2) continue;
+        const double cost = lc * (2.0 + dv_us(ns) + 6.6 * rounds(bh * ns * nnt)) + 40.0 + 1.1e-3 * bh * s.T * s.dk / 128;
+        if (cost < best) {
+            best = cost;
+            c = BwdCut{ns, lc};
+        }
+    }
+    return c;
+}
+
+// Per element: the adjoint of every segment's last state, in place of the segments' own
+// contributions (slots 1 .. ns - 1 of g), from detaT.
+__global__ __launch_bounds__(256) void bwd_state_scan_kernel(int nbh, int DK, int DV, int ns,
+                                                             const float* __restrict__ pseg,
+                                                             const float* __restrict__ detaT, float* __restrict__ g) {
+    const size_t per = (size_t)DK * DV, i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (size_t)nbh * per) return;
+    const size_t e = i % per, bh = i / per;
+    const int n = (int)(e / DV);
+    float x = detaT ? detaT[i] : 0.f;
+    float* o = g + bh * ns * per + e;
+    const float* pn = pseg + bh * ns * DK + n;
+    constexpr int U = 8;
+    for (int s0 = ns - 1; s0 >= 0; s0 -= U) {
+        float u[U], p[U];
+#pragma unroll
+        for (int m = 0; m < U; ++m) {
+            const int sgi = max(s0 - m, 1);
+            u[m] = o[(size_t)sgi * per];
+            p[m] = pn[(size_t)sgi * DK];
+        }
+#pragma unroll
+        for (int m = 0; m < U; ++m)
+            if (s0 - m >= 0) {
+                o[(size_t)(s0 - m) * per] = x;
+                x = fmaf(p[m], x, u[m]);
+            }
+    }
+}
+
+// (c, S) at the end of every chunk, into rows 0 and 1 of its coef, carried in fp64 along the
+// sequence; from dlamT and sum_d detaT H_T.  One thread per (b, h, slot); the steps of U
+// chunks are loaded while those of the U after are applied.
+__global__ __launch_bounds__(64) void bwd_carry_kernel(int nbh, int DK, int DV, int nct, float* __restrict__ coef,
+                                                       const float* __restrict__ saved_H,
+                                                       const float* __restrict__ dlamT,
+                                                       const float* __restrict__ detaT, float* __restrict__ dlam0) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nbh * DK) return;
+    const int n = i % DK, bh = i / DK;
+    double c = dlamT ? (double)dlamT[i] : 0.0, S = 0.0;
+    if (detaT) {
+        const float* hT = saved_H + (((size_t)bh * (nct + 1) + nct) * DK + n) * DV;
+        const float* d = detaT + (size_t)i * DV;
+        for (int m = 0; m < DV; m += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(hT + m), y = *reinterpret_cast<const float4*>(d + m);
+            S += (double)x.x * y.x + (double)x.y * y.y + (double)x.z * y.z + (double)x.w * y.w;
+        }
+    }
+    float* cf = coef + (size_t)bh * nct * 4 * DK + n;
+    constexpr int U = 8;
+    float b[U][4], nx[U][4];
+    auto load = [&](float (&d)[U][4], int j0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d[u][r] = cf[((size_t)max(j0 - u, 0) * 4 + r) * DK];
+    };
+    load(nx, nct - 1);
+    for (int j0 = nct - 1; j0 >= 0; j0 -= U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b[u][r] = nx[u][r];
+        load(nx, j0 - U);   // rows of other chunks than those written below
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j0 - u >= 0) {
+                float* o = cf + (size_t)(j0 - u) * 4 * DK;
+                o[0] = (float)c;
+                o[DK] = (float)S;
+                c = fma((double)b[u][0], c, fma((double)b[u][1], S, (double)b[u][2]));
+                S += b[u][3];
+            }
+    }
+    if (dlam0) dlam0[i] = (float)c;
+}
+
+// The gradients of one chunk's tokens from dqt, dkh and (c, S) at its end: phases 1, 2, 4 and 5
+// of bwd_dk_kernel for lanes = (slot, group of 8 tokens), one workgroup per (b, h, chunk), so
+// dr is complete here.  HBM bound: 24 bytes per (token, slot) with per-token gates.
+// TI: the chunk's sums of the gate gradients go to ous [B H][chunk][2][dk].
+template <int DK, bool TI, bool YG>
+__global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, BwdArgs g, const float* __restrict__ saved_lam,
+                                                          const float* __restrict__ xy,
+                                                          const float* __restrict__ coef, float* __restrict__ ous) {
+    constexpr int NG = 4, TPG = 8, NT = NG * DK;
+    __shared__ float qs[NG][4][DK];
+    __shared__ float sR[kC][DK + 1];
+    const int nct = (s.T + kC - 1) / kC, c = blockIdx.x % nct, bh = blockIdx.x / nct;
+    const int H = s.H, b = bh / H, h = bh % H, tid = threadIdx.x, n = tid % DK, gq = tid / DK;
+    const int nt = min(kC, s.T - c * kC);
+    const size_t tok0 = (size_t)b * s.T + (size_t)c * kC, row = (size_t)bh * nct + c;
+    const size_t k0 = (tok0 * H + h) * DK;
+    const uint32_t kbytes = (uint32_t)((nt - 1) * H * DK + DK) * 2;
+    const rsrc_t rk = make_rsrc(static_cast<const uint16_t*>(g.k) + k0, kbytes);
+    const rsrc_t rq = make_rsrc(static_cast<const uint16_t*>(g.q) + k0, kbytes);
+    const rsrc_t ra = make_rsrc(TI ? static_cast<const uint16_t*>(g.k) : static_cast<const uint16_t*>(g.a) + k0, TI ? 0u : kbytes);
+    const rsrc_t rp = make_rsrc(TI ? static_cast<const uint16_t*>(g.k) : static_cast<const uint16_t*>(g.p) + k0, TI ? 0u : kbytes);
+    const rsrc_t rr = make_rsrc(static_cast<const uint16_t*>(g.r) + tok0 * H + h, (uint32_t)((nt - 1) * H + 1) * 2);
+    const rsrc_t rg = make_rsrc(YG ? g.dyvar + tok0 * H + h : nullptr, YG ? (uint32_t)((nt - 1) * H + 1) * 4 : 0u);
+    float ca = 0.f, cp = 0.f;
+    if constexpr (TI) ou_gates(g.ou_a[h * DK + n], g.ou_p[h * DK + n], g.ou_d[h * DK + n], ca, cp);
+    // the lane's tokens; past the sequence end they enter as the identity step
+    float av[TPG], pv[TPG], kv[TPG], qv[TPG], rv[TPG], gv[TPG], dqt[TPG], dkh[TPG];
+    const float* xo = xy + row * 2 * kC * DK;
+#pragma unroll
+    for (int j = 0; j < TPG; ++j) {
+        const int t = gq * TPG + j;
+        const uint32_t vo = (uint32_t)(t * H * DK + n) * 2;
+        const bool ok = t < nt;
+        av[j] = ok ? (TI ? ca : bf16_to_f32(buf_ld16(ra, vo, 0))) : 1.f;
+        pv[j] = TI ? (ok ? cp : 0.f) : bf16_to_f32(buf_ld16(rp, vo, 0));
+        kv[j] = bf16_to_f32(buf_ld16(rk, vo, 0));
+        qv[j] = bf16_to_f32(buf_ld16(rq, vo, 0));
+        rv[j] = bf16_to_f32(buf_ld16(rr, (uint32_t)(t * H) * 2, 0));
+        gv[j] = YG ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, (uint32_t)(t * H) * 4, 0, 0)) : 0.f;
+        dqt[j] = xo[t * DK + n];
+        dkh[j] = xo[(kC + t) * DK + n];
+    }
+    const float* lw = saved_lam + row * kLamRows * DK + n;
+    const bool half = gq >= 2;
+    float x = half ? lw[DK] : lw[0], z = 1.f;
+    float cc = coef[row * 4 * DK + n], SS = coef[(row * 4 + 1) * DK + n];
+    // the transfer of the lane's group, handed to the next group of its half
+    {
+        float x0 = 1.f, z0 = 0.f, x1 = 0.f, z1 = 1.f;
+#pragma unroll
+        for (int j = 0; j < TPG; ++j) {
+            const float a2 = av[j] * av[j], phi = kv[j] * kv[j] * rv[j];
+            const float z0n = fmaf(pv[j], x0, a2 * z0), z1n = fmaf(pv[j], x1, a2 * z1);
+            x0 = fmaf(phi, z0n, x0);
+            x1 = fmaf(phi, z1n, x1);
+            z0 = z0n;
+            z1 = z1n;
+        }
+        qs[gq][0][n] = x0;
+        qs[gq][1][n] = z0;
+        qs[gq][2][n] = x1;
+        qs[gq][3][n] = z1;
+    }
+    __syncthreads();
+    if (gq & 1) {
+        const float m00 = qs[gq - 1][0][n], m10 = qs[gq - 1][1][n], m01 = qs[gq - 1][2][n], m11 = qs[gq - 1][3][n];
+        const float xn = fmaf(m00, x, m01 * z), zn = fmaf(m10, x, m11 * z);
+        x = xn;
+        z = zn;
+    }
+    __syncthreads();   // the transfers are read
+    float lp[TPG], il[TPG], rho[TPG], den[TPG];
+    {
+        float izp = fast_rcp(z), lam = x * izp;
+#pragma unroll
+        for (int j = 0; j < TPG; ++j) {
+            const float kr = kv[j] * rv[j];
+            const float zn = fmaf(pv[j], x, av[j] * av[j] * z);
+            const float xn = fmaf(kr * kv[j], zn, x);
+            const float iz = fast_rcp(zn);
+            lp[j] = lam;
+            lam = xn * iz;
+            il[j] = zn * fast_rcp(xn);
+            rho[j] = z * iz;
+            den[j] = zn * izp;
+            izp = iz;
+            x = xn;
+            z = zn;
+        }
+    }
+    // pass 1
+    float Am = 1.f, Bm = 0.f, Cm = 0.f, Dm = 0.f, u_[TPG], w_[TPG];
+#pragma unroll
+    for (int j = TPG - 1; j >= 0; --j) {
+        const float qi = qv[j] * il[j], qg = YG ? qv[j] * gv[j] : 0.f, rho2 = rho[j] * rho[j];
+        const float u = qi * dqt[j] - rv[j] * kv[j] * dkh[j], w = qi * (dqt[j] + qg) * il[j];
+        const float al = av[j] * av[j] * rho2, be = pv[j] * rho[j];
+        u_[j] = u;
+        w_[j] = w;
+        Cm = al * Cm - be * Dm - (al * w + be * u);
+        Bm = al * Bm - be;
+        Am = al * Am;
+        Dm = Dm + u;
+    }
+    qs[gq][0][n] = Am;
+    qs[gq][1][n] = Bm;
+    qs[gq][2][n] = Cm;
+    qs[gq][3][n] = Dm;
+    __syncthreads();
+#pragma unroll
+    for (int g2 = NG - 1; g2 >= 1; --g2) {   // through the later groups
+        const bool use = g2 > gq;
+        const float cn = fmaf(qs[g2][0][n], cc, fmaf(qs[g2][1][n], SS, qs[g2][2][n]));
+        cc = use ? cn : cc;
+        SS = use ? SS + qs[g2][3][n] : SS;
+    }
+    // pass 2
+    const rsrc_t oq = make_rsrc(static_cast<uint16_t*>(g.dq) + k0, kbytes), ok_ = make_rsrc(static_cast<uint16_t*>(g.dk) + k0, kbytes);
+    const rsrc_t oa = make_rsrc(TI ? static_cast<uint16_t*>(g.dq) : static_cast<uint16_t*>(g.da) + k0, TI ? 0u : kbytes);
+    const rsrc_t op = make_rsrc(TI ? static_cast<uint16_t*>(g.dq) : static_cast<uint16_t*>(g.dp) + k0, TI ? 0u : kbytes);
+    float sum_da = 0.f, sum_dp = 0.f;
+#pragma unroll
+    for (int j = TPG - 1; j >= 0; --j) {
+        const int t = gq * TPG + j;
+        const float qg = YG ? qv[j] * gv[j] : 0.f, rho2 = rho[j] * rho[j];
+        SS += u_[j];
+        const float gl = cc - w_[j];
+        const float drho = fmaf(gl, lp[j], SS * den[j]);
+        const float dav = fmaf(-2.f * av[j] * rho2, drho, SS * fast_rcp(av[j]));
+        const float dpv = -lp[j] * rho2 * drho;
+        sR[t][n] = fmaf(kv[j] * kv[j], gl, kv[j] * dkh[j]);
+        cc = fmaf(av[j] * av[j] * rho2, gl, -pv[j] * rho[j] * SS);
+        const uint32_t vo = (uint32_t)(t * H * DK + n) * 2;   // tokens past the end fall outside
+        __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(fmaf(2.f, qg, dqt[j]) * il[j]), oq, vo, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(fmaf(2.f * kv[j] * rv[j], gl, rv[j] * dkh[j])), ok_, vo, 0, 0);
+        if constexpr (TI) {
+            if (t < nt) {
+                sum_da += dav;
+                sum_dp += dpv;
+            }
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(dav), oa, vo, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(dpv), op, vo, 0, 0);
+        }
+    }
+    if constexpr (TI) {
+        __syncthreads();   // the summaries are read
+        qs[gq][0][n] = sum_da;
+        qs[gq][1][n] = sum_dp;
+    }
+    __syncthreads();
+    {   // dr: the sum over the slots, NT / kC lanes per token
+        constexpr int L = NT / kC;
+        const int t = tid / L, l = tid % L;
+        float acc = 0.f;
+#pragma unroll
+        for (int m = l; m < DK; m += L) acc += sR[t][m];
+#pragma unroll
+        for (int of = L / 2; of; of /= 2) acc += __shfl_xor(acc, of, 64);
+        if (l == 0 && t < nt) static_cast<uint16_t*>(g.dr)[(tok0 + t) * H + h] = f32_to_bf16(acc);
+    }
+    if constexpr (TI)
+        if (gq < 2) ous[(row * 2 + gq) * DK + n] = (qs[0][gq][n] + qs[1][gq][n]) + (qs[2][gq][n] + qs[3][gq][n]);
+}
+
+// The two OU parts of a batch row (chunked_ou_parts): the chunk sums of its even and odd chunks.
+__global__ __launch_bounds__(64) void bwd_ou_kernel(int nbh, int H, int B, int DK, int nct,
+                                                    const float* __restrict__ ous, float* __restrict__ part) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nbh * 4 * DK) return;
+    const int n = i % DK, q = i / DK % 2, par = i / (2 * DK) % 2, bh = i / (4 * DK), b = bh / H, h = bh % H;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int c = par; c < nct; c += 2) acc += ous[(((size_t)bh * nct + c) * 2 + q) * DK + n];
+    part[(size_t)q * 2 * nbh * DK + ((size_t)(par * B + b) * H + h) * DK + n] = acc;
+}
+
+size_t seg_bytes(const Shape& s, const BwdCut& c) {
+    const size_t nbh = (size_t)s.B * s.H, nct = (s.T + kC - 1) / kC, f = sizeof(float);
+    return nbh * c.ns * s.dk * (s.dv + 1) * f + nbh * nct * s.dk * (2 * kC + 4 + 2) * f + 5 * 256;
+}
+
+template <int DK, int DV, bool TI, bool YG>
+hipError_t launch_seg(const Shape& s, const BwdCut& cut, const BwdArgs& a, const float* saved_lam, const float* saved_H,
+                      void* ws, hipStream_t st) {
+    using Cfg = DkCfg<DK, DV>;
+    auto kern = bwd_dk_kernel<DK, DV, TI, YG, true>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
+    if (attr != hipSuccess) return attr;
+    const int nbh = s.B * s.H, nct = (s.T + kC - 1) / kC;
+    auto carve = [&](size_t count) {
+        float* p = static_cast<float*>(ws);
+        ws = static_cast<char*>(ws) + (count * sizeof(float) + 255) / 256 * 256;
+        return p;
+    };
+    float* gend = carve((size_t)nbh * cut.ns * DK * DV);
+    float* pseg = carve((size_t)nbh * cut.ns * DK);
+    float* xy = carve((size_t)nbh * nct * 2 * kC * DK);
+    float* coef = carve((size_t)nbh * nct * 4 * DK);
+    float* ous = carve((size_t)nbh * nct * 2 * DK);
+    hipError_t e = launch_backward_dv(s, cut.ns, cut.lc, true, a, saved_lam, gend, pseg, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bwd_state_scan_kernel, dim3((unsigned)(((size_t)nbh * DK * DV + 255) / 256)), dim3(256), 0, st,
+                       nbh, DK, DV, cut.ns, pseg, a.detaT, gend);
+    if ((e = launch_backward_dv(s, cut.ns, cut.lc, false, a, saved_lam, gend, pseg, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nbh * cut.ns * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s,
+                       Seg{cut.ns, cut.lc, cut.ns}, a, saved_lam, saved_H, nullptr, gend, xy, coef);
+    hipLaunchKernelGGL(bwd_carry_kernel, dim3((unsigned)((nbh * DK + 63) / 64)), dim3(64), 0, st, nbh, DK, DV, nct, coef,
+                       saved_H, a.dlamT, a.detaT, a.dlam0);
+    hipLaunchKernelGGL((bwd_grad_kernel<DK, TI, YG>), dim3((unsigned)(nbh * nct)), dim3(4 * DK), 0, st, s, a, saved_lam,
+                       xy, coef, ous);
+    if (TI)
+        hipLaunchKernelGGL(bwd_ou_kernel, dim3((unsigned)((nbh * 4 * DK + 63) / 64)), dim3(64), 0, st, nbh, s.H, s.B, DK,
+                           nct, ous, static_cast<float*>(a.ou_part));
+    return hipGetLastError();
+}
+
+template <int DK, int DV, bool TI, bool YG>
+hipError_t launch_either(const Shape& s, const BwdArgs& a, const float* saved_lam, const float* saved_H, void* ws,
+                         size_t limit, hipStream_t st) {
+    const BwdCut cut = bwd_cut(s);
+    if (cut.ns > 1 && seg_bytes(s, cut) <= limit) return launch_seg<DK, DV, TI, YG>(s, cut, a, saved_lam, saved_H, ws, st);
+    return launch_dk<DK, DV, TI, YG>(s, a, saved_lam, saved_H, static_cast<float*>(ws), st);
+}
+
 }  // namespace
 
 bool chunked_bwd_supported(const Shape& s) { return s.bf16 && s.dk >= 32 && s.dv >= 32; }
@@ -748,21 +1131,28 @@ bool chunked_bwd_supported(const Shape& s) { return s.bf16 && s.dk >= 32 && s.dv
 // one part per (wave of a pair, batch row)
 int chunked_ou_parts(const Shape& s) { return 2 * s.B; }
 
-// per-pair dr partials: dk / 16 of them per token
-size_t chunked_bwd_workspace(const Shape& s) { return (size_t)(s.dk / 16) * s.B * s.T * s.H * sizeof(float); }
+// the segment-parallel form's buffers, or per-pair dr partials: dk / 16 of them per token
+size_t chunked_bwd_workspace(const Shape& s, size_t limit) {
+    const BwdCut cut = bwd_cut(s);
+    if (cut.ns > 1) {
+        const size_t b = seg_bytes(s, cut);
+        if (b <= limit) return b;
+    }
+    return (size_t)(s.dk / 16) * s.B * s.T * s.H * sizeof(float);
+}
 
-hipError_t launch_backward_chunked(const Shape& s, const BwdArgs& a, const void* saved, void* ws, hipStream_t st) {
+hipError_t launch_backward_chunked(const Shape& s, const BwdArgs& a, const void* saved, void* ws, size_t limit,
+                                   hipStream_t st) {
     const size_t nchunk = (size_t)(s.T + kC - 1) / kC;
     const float* saved_lam = static_cast<const float*>(saved);
     const float* saved_H = saved_lam + (size_t)s.B * s.H * nchunk * kLamRows * s.dk;
-    float* dr_part = static_cast<float*>(ws);
 #define KLA_DK_CASE(DK_, DV_)                                                    \
     if (s.dk == DK_ && s.dv == DV_) {                                            \
         if (a.dyvar)                                                             \
-            return a.ou_a ? launch_dk<DK_, DV_, true, true>(s, a, saved_lam, saved_H, dr_part, st) \
-                          : launch_dk<DK_, DV_, false, true>(s, a, saved_lam, saved_H, dr_part, st); \
-        return a.ou_a ? launch_dk<DK_, DV_, true, false>(s, a, saved_lam, saved_H, dr_part, st)     \
-                      : launch_dk<DK_, DV_, false, false>(s, a, saved_lam, saved_H, dr_part, st);    \
+            return a.ou_a ? launch_either<DK_, DV_, true, true>(s, a, saved_lam, saved_H, ws, limit, st) \
+                          : launch_either<DK_, DV_, false, true>(s, a, saved_lam, saved_H, ws, limit, st); \
+        return a.ou_a ? launch_either<DK_, DV_, true, false>(s, a, saved_lam, saved_H, ws, limit, st)     \
+                      : launch_either<DK_, DV_, false, false>(s, a, saved_lam, saved_H, ws, limit, st);    \
     }
 #define KLA_DK_ROW(DK_) KLA_DK_CASE(DK_, 32) KLA_DK_CASE(DK_, 64) KLA_DK_CASE(DK_, 128)
     KLA_DK_ROW(32) KLA_DK_ROW(64) KLA_DK_ROW(128)

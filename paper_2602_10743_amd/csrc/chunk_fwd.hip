@@ -44,7 +44,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void fwd_chunk_kern
 
     int vi, tile;
     xcd_tile_map(blockIdx.x, s.B * s.H * sg.run, NTILE, vi, tile);
-    const int bh = vi / sg.run, seg = vi % sg.run;
+    const int bh = vi / sg.run, seg = sg.first + vi % sg.run;
     const int b = bh / s.H, h = bh % s.H;
     const int c0 = seg * sg.lc, nct = (s.T + kC - 1) / kC;   // this segment's first chunk, the sequence's chunks
     const int H = s.H, T = min(s.T - c0 * kC, sg.lc * kC);

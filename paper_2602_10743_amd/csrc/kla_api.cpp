@@ -110,6 +110,10 @@ size_t kla_saved_bytes(const kla_desc* desc) {
 
 namespace {
 
+// Bytes the chunked backward may take for running segments side by side; the allocation-free
+// entry point has its static workspace (less the flags).
+size_t bwd_limit(bool least) { return least ? (size_t)KLA_NOALLOC_SCRATCH_BYTES - kAlign : SIZE_MAX; }
+
 // What the per-channel forwards ask for: the validation flag (and, for bf16 shapes, no less
 // than kla_forward_workspace); the chunk-parallel path's work memory is not theirs.
 size_t pc_forward_workspace(const kla_desc* desc) {
@@ -130,7 +134,7 @@ size_t backward_workspace(const kla_desc* desc, int with_saved, bool least) {
                round_up((size_t)s.B * s.T * s.H * s.dv * sizeof(float));
     }
     if (kla::chunked_bwd_supported(s)) {
-        size_t bytes = kAlign + round_up(kla::chunked_bwd_workspace(s));
+        size_t bytes = kAlign + round_up(kla::chunked_bwd_workspace(s, bwd_limit(least)));
         if (!with_saved) {  // the context is recomputed: saved states plus a scratch output
             const size_t elt = s.bf16 ? 2 : 4;
             bytes += round_up(kla::chunked_saved_bytes(s)) + round_up((size_t)s.B * s.T * s.H * s.dv * elt);
@@ -253,7 +257,7 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
     hipError_t e;
     if (kla::chunked_bwd_supported(s)) {
         if (!saved) {
-            char* ctx = work + round_up(kla::chunked_bwd_workspace(s));
+            char* ctx = work + round_up(kla::chunked_bwd_workspace(s, bwd_limit(least)));
             void* yscratch = ctx + round_up(kla::chunked_saved_bytes(s));
             kla::FwdArgs f{a.q, a.k, a.v, a.a, a.p, a.r, a.lam0, a.eta0, yscratch, nullptr, nullptr, nullptr,
                            a.ou_a, a.ou_p, a.ou_d, a.range_flag};
@@ -261,7 +265,7 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
             if (e != hipSuccess) return KLA_ERR_HIP;
             saved = ctx;
         }
-        e = kla::launch_backward_chunked(s, a, saved, work, stream);
+        e = kla::launch_backward_chunked(s, a, saved, work, bwd_limit(least), stream);
     } else if (kla::c64p_supported(s)) {
         if (!saved) {   // the forward's work memory comes before the context, the backward's takes its place
             const size_t fwd = kla::c64p_fwd_workspace(s, true), bwd = kla::c64p_bwd_workspace(s, false);

@@ -100,9 +100,9 @@ __device__ __forceinline__ Swap32 swap32(float x) {
 }
 
 // A sequence as ns segments of lc chunks (the last one shorter), each a workgroup (set) of
-// its own, of which the first `run` are run; {1, all chunks, 1} walks it whole.
+// its own, of which `run` from `first` on are run; {1, all chunks, 1} walks it whole.
 struct Seg {
-    int ns, lc, run;
+    int ns, lc, run, first = 0;
 };
 
 // WIDE (dv = 128): all value channels in one workgroup, 32 per MFMA wave, so the precision
