@@ -1,10 +1,12 @@
 """Kalman Linear Attention filter layer on MI355X (gfx950): Python binding.
 
-A thin ctypes binding over ``libkla.so`` whose functions carry the names of the
-C ABI in ``include/kla.h``.  It only marshals arguments: it checks shapes and
-dtypes, allocates outputs and workspace through torch (device memory and
-streams are all torch is used for) and passes raw device pointers and the
-current HIP stream to the library, where every step of the filter runs.
+A thin binding over ``libkla.so`` whose functions carry the names of the C ABI in
+``include/kla.h``.  It only marshals arguments: it checks shapes and dtypes,
+allocates outputs and workspace through torch (device memory and streams are all
+torch is used for) and passes raw device pointers and the current HIP stream to
+the library, where every step of the filter runs.  The filter layer's forward,
+backward and decode step do this in C++ (``_kla_torch.so``, csrc/binding.cpp), the
+other entry points through ctypes.
 
 There is no fallback: if the HIP library is missing or the tensors are not on
 a GPU, every entry point raises.
@@ -47,7 +49,22 @@ class _Desc(ctypes.Structure):
 
 
 _lib = None
+_ext = None
 _VP = ctypes.c_void_p
+
+
+def _native():
+    """The native part of the binding (csrc/binding.cpp)."""
+    global _ext
+    if _ext is None:
+        _load()
+        try:
+            from . import _kla_torch
+        except ImportError as e:
+            raise ImportError(f"KLA native binding not built or not loadable: {e} "
+                              "(build it with `python paper_2602_10743_amd/build.py`)") from e
+        _ext = _kla_torch
+    return _ext
 
 
 def _load():
@@ -143,26 +160,6 @@ def _desc(q: torch.Tensor, v: torch.Tensor) -> _Desc:
     return _Desc(B, T, H, dk, v.shape[-1], _DTYPES[q.dtype])
 
 
-def _check_inputs(q, k, v, a, p, r):
-    if not q.is_cuda:
-        raise ValueError("KLA tensors must live on a GPU; the layer has no CPU path")
-    if q.dtype not in _DTYPES:
-        raise TypeError(f"unsupported dtype {q.dtype}; use float32 or bfloat16")
-    if q.dim() != 4:
-        raise ValueError("q must be [B, T, H, dk]")
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    for name, t, shape in (("k", k, (B, T, H, dk)), ("a", a, (B, T, H, dk)), ("p", p, (B, T, H, dk)),
-                           ("v", v, (B, T, H, dv)), ("r", r, (B, T, H))):
-        if tuple(t.shape) != shape:
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
-        if t.dtype != q.dtype or t.device != q.device:
-            raise ValueError(f"{name} must share q's dtype and device")
-    for name, t in (("q", q), ("k", k), ("v", v), ("a", a), ("p", p), ("r", r)):
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-
-
 def _f32(t, shape, dev, name):
     if t is None:
         return None
@@ -189,29 +186,24 @@ def kla_forward(q, k, v, a, p, r, lam0=None, eta0=None, *, want_var: bool = Fals
     r: [B, T, H] (all one dtype, fp32 or bf16).  lam0 [B, H, dk], eta0
     [B, H, dk, dv] fp32 or None (prior 1 and 0).  Returns y and, as asked,
     yvar, the final belief (lamT, etaT) and the saved context for backward."""
-    lib = _load()
-    _check_inputs(q, k, v, a, p, r)
-    dev = q.device
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    lam0 = _f32(lam0, (B, H, dk), dev, "lam0")
-    eta0 = _f32(eta0, (B, H, dk, dv), dev, "eta0")
-    desc = _desc(q, v)
-    if y is None:
-        y = torch.empty((B, T, H, dv), dtype=q.dtype, device=dev)
-    yvar = torch.empty((B, T, H), dtype=torch.float32, device=dev) if want_var else None
-    lamT = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if want_state else None
-    etaT = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_state else None
-    nsaved = kla_saved_bytes(desc) if save else 0
-    saved = torch.empty(max(nsaved, 1), dtype=torch.uint8, device=dev) if save else None
-    nws = kla_forward_workspace(desc)
-    ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
-    st = lib.kla_forward(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(r), _p(lam0), _p(eta0),
-                         _p(y), _p(yvar), _p(lamT), _p(etaT), _p(saved if nsaved else None), _p(ws), nws,
-                         _stream(dev))
-    if st != 0:
-        raise KLAError(st, "kla_forward")
-    return {"y": y, "yvar": yvar, "lamT": lamT, "etaT": etaT, "saved": saved if nsaved else None}
+    out = _native().forward(q, k, v, a, p, None, r, lam0, eta0, y, want_var, want_state, save)
+    return _outputs(out, "kla_forward")
+
+
+def _outputs(out, where: str) -> dict:
+    if isinstance(out, int):
+        raise KLAError(out, where)
+    return {"y": out[0], "yvar": out[1], "lamT": out[2], "etaT": out[3], "saved": out[4]}
+
+
+def _grads(out, where: str) -> dict:
+    if isinstance(out, int):
+        raise KLAError(out, where)
+    g = {"dq": out[0], "dk": out[1], "dv": out[2], "da": out[3], "dp": out[4], "dr": out[5]}
+    if len(out) == 9:
+        g["ddelta"] = out[8]
+    g["dlam0"], g["deta0"] = out[6], out[7]
+    return g
 
 
 def kla_backward(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=None, *, saved=None,
@@ -220,33 +212,8 @@ def kla_backward(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=None, *, sa
     (dy, dyvar [B, T, H] fp32 or None, dlamT, detaT); returns dq, dk, dv, da, dp,
     dr in the input dtype and, when asked, dlam0 [B, H, dk] and deta0
     [B, H, dk, dv] in fp32."""
-    lib = _load()
-    _check_inputs(q, k, v, a, p, r)
-    dev = q.device
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    lam0 = _f32(lam0, (B, H, dk), dev, "lam0")
-    eta0 = _f32(eta0, (B, H, dk, dv), dev, "eta0")
-    dlamT = _f32(dlamT, (B, H, dk), dev, "dlamT")
-    detaT = _f32(detaT, (B, H, dk, dv), dev, "detaT")
-    dyvar = _f32(dyvar, (B, T, H), dev, "dyvar")
-    if tuple(dy.shape) != (B, T, H, dv) or dy.dtype != q.dtype or not dy.is_contiguous():
-        raise ValueError("dy must be a contiguous [B, T, H, dv] tensor in the input dtype")
-    desc = _desc(q, v)
-    out = {n: torch.empty_like(x) for n, x in (("dq", q), ("dk", k), ("dv", v), ("da", a), ("dp", p), ("dr", r))}
-    dlam0 = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if want_init_grads else None
-    deta0 = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_init_grads else None
-    nws = kla_backward_workspace(desc, saved is not None)
-    ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
-    st = lib.kla_backward(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(r), _p(lam0), _p(eta0),
-                          _p(saved), _p(dy), _p(dyvar), _p(dlamT), _p(detaT), _p(out["dq"]), _p(out["dk"]), _p(out["dv"]),
-                          _p(out["da"]), _p(out["dp"]), _p(out["dr"]), _p(dlam0), _p(deta0), _p(ws), nws,
-                          _stream(dev))
-    if st != 0:
-        raise KLAError(st, "kla_backward")
-    out["dlam0"] = dlam0
-    out["deta0"] = deta0
-    return out
+    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False)
+    return _grads(out, "kla_backward")
 
 
 def kla_backward_noalloc(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=None, *, saved,
@@ -254,55 +221,17 @@ def kla_backward_noalloc(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=Non
     """kla_backward through the library's per-GPU static workspace (the entry point for
     callers that cannot allocate; only the outputs are allocated here, by torch).  A saved
     context from kla_forward(save=True) is required."""
-    lib = _load()
-    _check_inputs(q, k, v, a, p, r)
-    dev = q.device
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    lam0 = _f32(lam0, (B, H, dk), dev, "lam0")
-    eta0 = _f32(eta0, (B, H, dk, dv), dev, "eta0")
-    dlamT = _f32(dlamT, (B, H, dk), dev, "dlamT")
-    detaT = _f32(detaT, (B, H, dk, dv), dev, "detaT")
-    dyvar = _f32(dyvar, (B, T, H), dev, "dyvar")
-    if tuple(dy.shape) != (B, T, H, dv) or dy.dtype != q.dtype or not dy.is_contiguous():
-        raise ValueError("dy must be a contiguous [B, T, H, dv] tensor in the input dtype")
-    desc = _desc(q, v)
-    out = {n: torch.empty_like(x) for n, x in (("dq", q), ("dk", k), ("dv", v), ("da", a), ("dp", p), ("dr", r))}
-    dlam0 = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if want_init_grads else None
-    deta0 = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_init_grads else None
-    st = lib.kla_backward_noalloc(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(r), _p(lam0), _p(eta0),
-                                  _p(saved), _p(dy), _p(dyvar), _p(dlamT), _p(detaT), _p(out["dq"]), _p(out["dk"]),
-                                  _p(out["dv"]), _p(out["da"]), _p(out["dp"]), _p(out["dr"]), _p(dlam0), _p(deta0),
-                                  _stream(dev))
-    if st != 0:
-        raise KLAError(st, "kla_backward_noalloc")
-    out["dlam0"] = dlam0
-    out["deta0"] = deta0
-    return out
+    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, True)
+    return _grads(out, "kla_backward_noalloc")
 
 
 def kla_decode_step(q, k, v, a, p, r, lam, eta, *, want_var: bool = False, y=None) -> dict:
     """One token for S sequences: q, k, a, p [S, H, dk]; v [S, H, dv]; r [S, H];
     lam [S, H, dk] and eta [S, H, dk, dv] fp32 are updated in place."""
-    lib = _load()
-    if not q.is_cuda or q.dtype not in _DTYPES:
-        raise ValueError("decode inputs must be fp32/bf16 GPU tensors")
-    S, H, dk = q.shape
-    dv = v.shape[-1]
-    for name, t, shape in (("k", k, (S, H, dk)), ("a", a, (S, H, dk)), ("p", p, (S, H, dk)),
-                           ("v", v, (S, H, dv)), ("r", r, (S, H))):
-        if tuple(t.shape) != shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous {shape} tensor in q's dtype")
-    _f32(lam, (S, H, dk), q.device, "lam")
-    _f32(eta, (S, H, dk, dv), q.device, "eta")
-    if y is None:
-        y = torch.empty((S, H, dv), dtype=q.dtype, device=q.device)
-    yvar = torch.empty((S, H), dtype=torch.float32, device=q.device) if want_var else None
-    st = lib.kla_decode_step(S, H, dk, dv, _DTYPES[q.dtype], _p(q), _p(k), _p(v), _p(a), _p(p), _p(r),
-                             _p(lam), _p(eta), _p(y), _p(yvar), _stream(q.device))
-    if st != 0:
-        raise KLAError(st, "kla_decode_step")
-    return {"y": y, "yvar": yvar, "lam": lam, "eta": eta}
+    out = _native().decode_step(q, k, v, a, p, None, r, lam, eta, y, want_var)
+    if isinstance(out, int):
+        raise KLAError(out, "kla_decode_step")
+    return {"y": out[0], "yvar": out[1], "lam": lam, "eta": eta}
 
 
 def _split_grads(q, v, want_var, grads):
@@ -326,6 +255,7 @@ class KLAFilter(torch.autograd.Function):
         ctx.save_for_backward(q, k, v, a, p, r, lam0, eta0)
         ctx.saved_ctx = out["saved"]
         ctx.want_var = want_var
+        ctx.set_materialize_grads(False)   # an unused output's gradient stays None: nothing to fill or read
         if want_var:
             return out["y"], out["yvar"], out["lamT"], out["etaT"]
         return out["y"], out["lamT"], out["etaT"]
@@ -347,30 +277,6 @@ def kla_filter(q, k, v, a, p, r, lam0=None, eta0=None, *, want_var: bool = False
 
 # ---- OU gates: time-invariant a, p, delta [H, dk] fp32 in place of per-token abar, pbar
 
-def _check_ou(a, p, delta, H, dk, dev):
-    for name, t in (("a", a), ("p", p), ("delta", delta)):
-        _f32(t, (H, dk), dev, name)
-
-
-def _check_inputs_ou(q, k, v, r):
-    if not q.is_cuda:
-        raise ValueError("KLA tensors must live on a GPU; the layer has no CPU path")
-    if q.dtype not in _DTYPES:
-        raise TypeError(f"unsupported dtype {q.dtype}; use float32 or bfloat16")
-    if q.dim() != 4:
-        raise ValueError("q must be [B, T, H, dk]")
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    for name, t, shape in (("k", k, (B, T, H, dk)), ("v", v, (B, T, H, dv)), ("r", r, (B, T, H))):
-        if tuple(t.shape) != shape:
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
-        if t.dtype != q.dtype or t.device != q.device:
-            raise ValueError(f"{name} must share q's dtype and device")
-    for name, t in (("q", q), ("k", k), ("v", v), ("r", r)):
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-
-
 def kla_backward_ou_workspace(desc: _Desc, with_saved: bool) -> int:
     return int(_load().kla_backward_ou_workspace(ctypes.byref(desc), int(bool(with_saved))))
 
@@ -378,90 +284,24 @@ def kla_backward_ou_workspace(desc: _Desc, with_saved: bool) -> int:
 def kla_forward_ou(q, k, v, a, p, delta, r, lam0=None, eta0=None, *, want_var: bool = False,
                    want_state: bool = True, save: bool = False, y=None) -> dict:
     """kla_forward with the gates of the OU parameters a, p, delta [H, dk] fp32."""
-    lib = _load()
-    _check_inputs_ou(q, k, v, r)
-    dev = q.device
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    _check_ou(a, p, delta, H, dk, dev)
-    lam0 = _f32(lam0, (B, H, dk), dev, "lam0")
-    eta0 = _f32(eta0, (B, H, dk, dv), dev, "eta0")
-    desc = _desc(q, v)
-    if y is None:
-        y = torch.empty((B, T, H, dv), dtype=q.dtype, device=dev)
-    yvar = torch.empty((B, T, H), dtype=torch.float32, device=dev) if want_var else None
-    lamT = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if want_state else None
-    etaT = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_state else None
-    nsaved = kla_saved_bytes(desc) if save else 0
-    saved = torch.empty(max(nsaved, 1), dtype=torch.uint8, device=dev) if save else None
-    nws = kla_forward_workspace(desc)
-    ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
-    st = lib.kla_forward_ou(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(delta), _p(r), _p(lam0),
-                            _p(eta0), _p(y), _p(yvar), _p(lamT), _p(etaT), _p(saved if nsaved else None), _p(ws),
-                            nws, _stream(dev))
-    if st != 0:
-        raise KLAError(st, "kla_forward_ou")
-    return {"y": y, "yvar": yvar, "lamT": lamT, "etaT": etaT, "saved": saved if nsaved else None}
+    out = _native().forward(q, k, v, a, p, delta, r, lam0, eta0, y, want_var, want_state, save)
+    return _outputs(out, "kla_forward_ou")
 
 
 def kla_backward_ou(q, k, v, a, p, delta, r, lam0, eta0, dy, dlamT=None, detaT=None, *, saved=None,
                     want_init_grads: bool = True, dyvar=None) -> dict:
     """Gradients of kla_forward_ou (dyvar as in kla_backward): dq, dk, dv, dr in
     the input dtype; da, dp, ddelta [H, dk] fp32; dlam0, deta0 in fp32 when asked."""
-    lib = _load()
-    _check_inputs_ou(q, k, v, r)
-    dev = q.device
-    B, T, H, dk = q.shape
-    dv = v.shape[-1]
-    _check_ou(a, p, delta, H, dk, dev)
-    lam0 = _f32(lam0, (B, H, dk), dev, "lam0")
-    eta0 = _f32(eta0, (B, H, dk, dv), dev, "eta0")
-    dlamT = _f32(dlamT, (B, H, dk), dev, "dlamT")
-    detaT = _f32(detaT, (B, H, dk, dv), dev, "detaT")
-    dyvar = _f32(dyvar, (B, T, H), dev, "dyvar")
-    if tuple(dy.shape) != (B, T, H, dv) or dy.dtype != q.dtype or not dy.is_contiguous():
-        raise ValueError("dy must be a contiguous [B, T, H, dv] tensor in the input dtype")
-    desc = _desc(q, v)
-    out = {n: torch.empty_like(x) for n, x in (("dq", q), ("dk", k), ("dv", v), ("dr", r))}
-    for n in ("da", "dp", "ddelta"):
-        out[n] = torch.empty((H, dk), dtype=torch.float32, device=dev)
-    dlam0 = torch.empty((B, H, dk), dtype=torch.float32, device=dev) if want_init_grads else None
-    deta0 = torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_init_grads else None
-    nws = kla_backward_ou_workspace(desc, saved is not None)
-    ws = torch.empty(max(nws, 1), dtype=torch.uint8, device=dev)
-    st = lib.kla_backward_ou(ctypes.byref(desc), _p(q), _p(k), _p(v), _p(a), _p(p), _p(delta), _p(r), _p(lam0),
-                             _p(eta0), _p(saved), _p(dy), _p(dyvar), _p(dlamT), _p(detaT), _p(out["dq"]),
-                             _p(out["dk"]),
-                             _p(out["dv"]), _p(out["da"]), _p(out["dp"]), _p(out["ddelta"]), _p(out["dr"]),
-                             _p(dlam0), _p(deta0), _p(ws), nws, _stream(dev))
-    if st != 0:
-        raise KLAError(st, "kla_backward_ou")
-    out["dlam0"] = dlam0
-    out["deta0"] = deta0
-    return out
+    out = _native().backward(q, k, v, a, p, delta, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False)
+    return _grads(out, "kla_backward_ou")
 
 
 def kla_decode_step_ou(q, k, v, a, p, delta, r, lam, eta, *, want_var: bool = False, y=None) -> dict:
     """kla_decode_step with the gates of the OU parameters a, p, delta [H, dk] fp32."""
-    lib = _load()
-    if not q.is_cuda or q.dtype not in _DTYPES:
-        raise ValueError("decode inputs must be fp32/bf16 GPU tensors")
-    S, H, dk = q.shape
-    dv = v.shape[-1]
-    for name, t, shape in (("k", k, (S, H, dk)), ("v", v, (S, H, dv)), ("r", r, (S, H))):
-        if tuple(t.shape) != shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous {shape} tensor in q's dtype")
-    _check_ou(a, p, delta, H, dk, q.device)
-    _f32(lam, (S, H, dk), q.device, "lam")
-    _f32(eta, (S, H, dk, dv), q.device, "eta")
-    if y is None:
-        y = torch.empty((S, H, dv), dtype=q.dtype, device=q.device)
-    yvar = torch.empty((S, H), dtype=torch.float32, device=q.device) if want_var else None
-    st = lib.kla_decode_step_ou(S, H, dk, dv, _DTYPES[q.dtype], _p(q), _p(k), _p(v), _p(a), _p(p), _p(delta),
-                                _p(r), _p(lam), _p(eta), _p(y), _p(yvar), _stream(q.device))
-    if st != 0:
-        raise KLAError(st, "kla_decode_step_ou")
-    return {"y": y, "yvar": yvar, "lam": lam, "eta": eta}
+    out = _native().decode_step(q, k, v, a, p, delta, r, lam, eta, y, want_var)
+    if isinstance(out, int):
+        raise KLAError(out, "kla_decode_step_ou")
+    return {"y": out[0], "yvar": out[1], "lam": lam, "eta": eta}
 
 
 class KLAFilterOU(torch.autograd.Function):
@@ -473,6 +313,7 @@ class KLAFilterOU(torch.autograd.Function):
         ctx.save_for_backward(q, k, v, a, p, delta, r, lam0, eta0)
         ctx.saved_ctx = out["saved"]
         ctx.want_var = want_var
+        ctx.set_materialize_grads(False)   # an unused output's gradient stays None: nothing to fill or read
         if want_var:
             return out["y"], out["yvar"], out["lamT"], out["etaT"]
         return out["y"], out["lamT"], out["etaT"]

@@ -1,0 +1,69 @@
+"""The native binding refuses what the entry points do not take, with the exception types and
+messages of the Python layer, before anything is launched."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+def _inputs(dev, B=1, T=8, H=2, dk=32, dv=16, dtype=torch.float32):
+    z = lambda *s: torch.full(s, 0.5, device=dev, dtype=dtype)
+    return [z(B, T, H, dk), z(B, T, H, dk), z(B, T, H, dv), z(B, T, H, dk), z(B, T, H, dk), z(B, T, H)]
+
+
+def test_cpu_tensors_are_refused():
+    import paper_2602_10743_amd as K
+    x = _inputs("cpu")
+    with pytest.raises(ValueError, match="must live on a GPU"):
+        K.kla_forward(*x)
+    with pytest.raises(ValueError, match="must live on a GPU"):
+        K.kla_backward(*x, None, None, x[2])
+    with pytest.raises(ValueError, match="GPU tensors"):
+        K.kla_decode_step(*[t[:, 0] for t in x], torch.ones(1, 2, 32), torch.zeros(1, 2, 32, 16))
+
+
+@pytest.mark.gpu
+def test_bad_tensors_are_refused():
+    import paper_2602_10743_amd as K
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = "cuda:0"
+    x = _inputs(dev)
+
+    def bad(i, t, exc, match):
+        y = list(x)
+        y[i] = t
+        with pytest.raises(exc, match=match):
+            K.kla_forward(*y)
+
+    bad(0, x[0].double(), TypeError, "unsupported dtype torch.float64|unsupported dtype torch.Double")
+    bad(0, x[0][0], ValueError, r"q must be \[B, T, H, dk\]")
+    bad(1, x[1][:, :4].contiguous(), ValueError, r"k has shape \(1, 4, 2, 32\), expected \(1, 8, 2, 32\)")
+    bad(3, x[3].bfloat16(), ValueError, "a must share q's dtype and device")
+    bad(2, x[2].transpose(1, 2).contiguous().transpose(1, 2), ValueError, "v must be contiguous")
+    bad(5, x[5].cpu(), ValueError, "r must share q's dtype and device")
+    with pytest.raises(ValueError, match=r"lam0 must be a contiguous float32 tensor of shape \(1, 2, 32\) on cuda:0"):
+        K.kla_forward(*x, torch.ones(2, 32, device=dev))
+    with pytest.raises(ValueError, match="dy must be a contiguous"):
+        K.kla_backward(*x, None, None, x[0])
+    wide = [t.repeat_interleave(2, -1)[..., :24].contiguous() if t.dim() == 4 else t for t in x]   # widths of 24
+    with pytest.raises(K.KLAError) as e:
+        K.kla_forward(*wide)
+    assert e.value.status == 2   # KLA_ERR_SHAPE
+    with pytest.raises(ValueError, match="k must be a contiguous"):
+        K.kla_decode_step(x[0][:, 0], x[1][:, 0, :1], x[2][:, 0], x[3][:, 0], x[4][:, 0], x[5][:, 0],
+                          torch.ones(1, 2, 32, device=dev), torch.zeros(1, 2, 32, 16, device=dev))
+
+
+@pytest.mark.gpu
+def test_unused_outputs_have_no_gradient():
+    """Gradients through y alone, through lamT alone and through both agree with their sum."""
+    import paper_2602_10743_amd as K
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = [t.clone().requires_grad_(True) for t in _inputs("cuda:0", T=70)]
+    y, lamT, etaT = K.kla_filter(*x)
+    gy = torch.autograd.grad(y.sum(), x, retain_graph=True)
+    gl = torch.autograd.grad(lamT.sum(), x, retain_graph=True)
+    both = torch.autograd.grad(y.sum() + lamT.sum(), x)
+    for a, b, c in zip(gy, gl, both):
+        assert torch.allclose(a + b, c, rtol=1e-5, atol=1e-5 * float(c.abs().max() + 1))
