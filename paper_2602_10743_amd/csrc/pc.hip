@@ -51,7 +51,6 @@
 namespace kla {
 namespace {
 
-constexpr int kNG = 8;    // lanes sharing one value channel, each with every 8th key slot
 constexpr int kTB = 16;   // tokens per staged block
 constexpr int kCK = 8;    // tokens between checkpoints of the belief (saved context)
 // The key-slot parts of the backward, [tile][4][B T H dk] fp32, lie part_stride(n)
@@ -61,30 +60,50 @@ constexpr int kCK = 8;    // tokens between checkpoints of the belief (saved con
 constexpr int kKPad = 320;
 __host__ __device__ inline size_t part_stride(size_t n) { return n + kKPad; }
 
-template <typename A>
-__device__ __forceinline__ A sum8(A x) {   // over the 8 lanes of a channel
+// over the LG lanes of a channel, valid in the last of them
+template <int LG, typename A>
+__device__ __forceinline__ A lane_sum(A x) {
+    static_assert(LG == 8 || LG == 16 || LG == 32 || LG == 64, "lanes of a channel");
     x += dpp<0xB1, 0xf>(x);    // quad_perm [1,0,3,2]
     x += dpp<0x4E, 0xf>(x);    // quad_perm [2,3,0,1]
     x += dpp<0x141, 0xf>(x);   // row_half_mirror
+    if constexpr (LG >= 16) x += dpp<0x140, 0xf>(x);   // row_mirror
+    if constexpr (LG >= 32) x += dpp<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+    if constexpr (LG == 64) x += dpp<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
     return x;
 }
 
-// One workgroup per (b, h, CT value channels); lane l of the workgroup owns
-// channel d0 + l / 8 and key slots n = l % 8 + 8 i.  Per block of kTB tokens the
-// key-side inputs (abar, pbar, k, q as fp32 [t][n]) and the channel inputs
-// (r, v as [t][c]) are staged in LDS, the elements are updated, the partial
-// readouts summed over the 8 lanes of a channel and y, yvar written from LDS.
-template <typename S, int DK, int DV, bool TI>
-__global__ __launch_bounds__(8 * (DV < 32 ? DV : 32)) void fwd_pc_kernel(Shape s, FwdArgs g,
-                                                                       typename acc<S>::type* ck) {
+// Forward: lanes per channel and channels per workgroup.  A lane walks DK / LG elements of
+// its channel, so the more lanes the shorter every token's step and the more waves run:
+// FEW (the channels of all heads do not fill the chip with 8 lanes each) takes up to 64, otherwise
+// 8, whose sums over the lanes are the cheapest.
+template <int DK, int DV, bool FEW>
+struct PcFwd {
+    static constexpr int LG = FEW ? (DK < 64 ? DK : 64) : 8;
+    static constexpr int CT = FEW ? 256 / LG < DV ? 256 / LG : DV : DV < 32 ? DV : 32;
+    static constexpr int NTHR = LG * CT;
+};
+
+// One workgroup per (b, h, CT value channels); lane l of the workgroup owns channel
+// d0 + l / LG and key slots n = l % LG + LG i.  Per block of kTB tokens the key-side inputs
+// (abar, pbar, k, q as fp32 [t][n]) and the channel inputs (r, v as [t][c]) are staged in
+// LDS (FEW: fetched into registers a block ahead and double-buffered; otherwise the CU's other
+// workgroups hide the wait and the registers are better spent on them); the elements are updated,
+// the partial readouts summed over the lanes of a channel and y, yvar written from LDS.
+// Bound by VALU issue where the channels fill the chip (18 slots per element) and by the
+// latency of a token's step where they do not: B2 T1024 H8 64 x 64 on 8 lanes per channel (128
+// waves, loads waited for in every block) 838 us, on 32 lanes 229, on 64 193 us.
+template <typename S, int DK, int DV, bool TI, bool FEW>
+__global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shape s, FwdArgs g,
+                                                                         typename acc<S>::type* ck) {
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
-    constexpr int CT = DV < 32 ? DV : 32;
-    constexpr int NTHR = kNG * CT;
-    constexpr int NPER = DK / kNG;
-    __shared__ float4 s_k[kTB][DK];
-    __shared__ float2 s_v[kTB][CT];
-    __shared__ float s_y[kTB][CT], s_w[kTB][CT];
+    using P = PcFwd<DK, DV, FEW>;
+    constexpr int CT = P::CT, LG = P::LG, NTHR = P::NTHR, NPER = DK / LG;
+    constexpr int NB = FEW ? 2 : 1;   // staging buffers
+    __shared__ float4 s_k[NB][kTB][DK];
+    __shared__ float2 s_v[NB][kTB][CT];
+    __shared__ float s_y[NB][kTB][CT], s_w[NB][kTB][CT];
     __shared__ float s_junk[2][NTHR];   // the writes of the lanes that do not hold a channel's sum
 
     const T_ *q = static_cast<const T_*>(g.q), *k = static_cast<const T_*>(g.k), *v = static_cast<const T_*>(g.v);
@@ -93,16 +112,17 @@ __global__ __launch_bounds__(8 * (DV < 32 ? DV : 32)) void fwd_pc_kernel(Shape s
     const int ntile = DV / CT;
     const int bh = blockIdx.x / ntile, d0 = (blockIdx.x % ntile) * CT;
     const int b = bh / s.H, h = bh % s.H;
-    const int tid = threadIdx.x, ng = tid % kNG, c = tid / kNG, d = d0 + c;
+    const int tid = threadIdx.x, ng = tid % LG, c = tid / LG, d = d0 + c;
+    const bool want_w = g.yvar != nullptr;
 
     A lam[NPER], eta[NPER], ga[NPER], gp[NPER];
 #pragma unroll
     for (int i = 0; i < NPER; ++i) {
-        const size_t o = ((size_t)bh * DK + ng + kNG * i) * DV + d;
+        const size_t o = ((size_t)bh * DK + ng + LG * i) * DV + d;
         lam[i] = g.lam0 ? (A)g.lam0[o] : A(1);
         eta[i] = g.eta0 ? (A)g.eta0[o] : A(0);
         if constexpr (TI) {
-            const size_t og = ((size_t)h * DK + ng + kNG * i) * DV + d;
+            const size_t og = ((size_t)h * DK + ng + LG * i) * DV + d;
             ou_gates(g.ou_a[og], g.ou_p[og], g.ou_d[og], ga[i], gp[i]);
         }
     }
@@ -110,34 +130,70 @@ __global__ __launch_bounds__(8 * (DV < 32 ? DV : 32)) void fwd_pc_kernel(Shape s
     const int nseg = (s.T + kCK - 1) / kCK;
     A* ck_lam = ck;
     A* ck_eta = ck ? ck + (size_t)s.B * s.H * nseg * DK * DV : nullptr;
-    for (int t0 = 0; t0 < s.T; t0 += kTB) {
-        const int nt = min(kTB, s.T - t0);
-        for (int idx = tid; idx < nt * DK; idx += NTHR) {
-            const int t = idx / DK, n = idx % DK;
-            const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DK + n;
-            s_k[t][n] = TI ? make_float4(0.f, 0.f, ld(k, o), ld(q, o)) : make_float4(ld(a, o), ld(p, o), ld(k, o), ld(q, o));
-        }
-        for (int idx = tid; idx < nt * CT; idx += NTHR) {
-            const int t = idx / CT, cc = idx % CT;
-            const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DV + d0 + cc;
-            s_v[t][cc] = make_float2(ld(r, o), ld(v, o));
-        }
-        __syncthreads();
-        for (int t = 0; t < nt; ++t) {
-            if (ck && (t0 + t) % kCK == 0) {
+    // a block's inputs, indices clamped to its last token so that every load is issued
+    constexpr int KPT = (kTB * DK + NTHR - 1) / NTHR, VPT = (kTB * CT + NTHR - 1) / NTHR;
+    float4 nk[KPT];
+    float2 nv[VPT];
+    auto fetch = [&](int t0) {
+        const int tl = min(kTB, s.T - t0) - 1;
 #pragma unroll
-                for (int i = 0; i < NPER; ++i) {
-                    const size_t o = (((size_t)bh * nseg + (t0 + t) / kCK) * DK + ng + kNG * i) * DV + d;
-                    ck_lam[o] = lam[i];
-                    ck_eta[o] = eta[i];
-                }
+        for (int m = 0; m < KPT; ++m) {
+            const int idx = min(tid + NTHR * m, kTB * DK - 1), t = min(idx / DK, tl), n = idx % DK;
+            const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DK + n;
+            nk[m] = TI ? make_float4(0.f, 0.f, ld(k, o), ld(q, o)) : make_float4(ld(a, o), ld(p, o), ld(k, o), ld(q, o));
+        }
+#pragma unroll
+        for (int m = 0; m < VPT; ++m) {
+            const int idx = min(tid + NTHR * m, kTB * CT - 1), t = min(idx / CT, tl), cc = idx % CT;
+            const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DV + d0 + cc;
+            nv[m] = make_float2(ld(r, o), ld(v, o));
+        }
+    };
+    auto store = [&](int t0, int bb) {   // the outputs of the block from t0
+        const int nt = min(kTB, s.T - t0);
+#pragma unroll
+        for (int m = 0; m < VPT; ++m) {
+            const int idx = tid + NTHR * m, t = idx / CT, cc = idx % CT;
+            if (t < nt) {
+                const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DV + d0 + cc;
+                st(y, o, s_y[bb][t][cc]);
+                if (want_w) g.yvar[o] = s_w[bb][t][cc];
             }
-            const float2 rv = s_v[t][c];
+        }
+    };
+    wait_vm_all();   // the carries are complete before the block loop
+    if (FEW && s.T > 0) fetch(0);
+    for (int t0 = 0; t0 < s.T; t0 += kTB) {
+        const int nt = min(kTB, s.T - t0), bb = FEW ? (t0 / kTB) & 1 : 0;
+        if constexpr (!FEW) {
+            if (t0 > 0) {
+                barrier_lds();   // the last block's outputs are in, its inputs no longer read
+                store(t0 - kTB, 0);
+            }
+            fetch(t0);
+        }
+#pragma unroll
+        for (int m = 0; m < KPT; ++m) {
+            const int idx = tid + NTHR * m;
+            if (KPT * NTHR == kTB * DK || idx < kTB * DK) s_k[bb][idx / DK][idx % DK] = nk[m];
+        }
+#pragma unroll
+        for (int m = 0; m < VPT; ++m) {
+            const int idx = tid + NTHR * m;
+            if (VPT * NTHR == kTB * CT || idx < kTB * CT) s_v[bb][idx / CT][idx % CT] = nv[m];
+        }
+        barrier_lds();   // the block's inputs (FEW: and the last block's outputs) are in
+        if constexpr (FEW) {
+            if (t0 > 0) store(t0 - kTB, bb ^ 1);
+            if (t0 + kTB < s.T) fetch(t0 + kTB);
+        }
+        auto token = [&](int t) {
+            const float2 rv = s_v[bb][t][c];
             const A rc = rv.x, krv_s = (A)rv.x * (A)rv.y;   // r v: the evidence k r v over k
             A ya = 0, wa = 0;
 #pragma unroll
             for (int i = 0; i < NPER; ++i) {
-                const float4 in = s_k[t][ng + kNG * i];   // abar, pbar, k, q
+                const float4 in = s_k[bb][t][ng + LG * i];   // abar, pbar, k, q
                 const A ax = TI ? ga[i] : (A)in.x, py = TI ? gp[i] : (A)in.y, kz = in.z, qw = in.w;
                 const A den = fma(py, lam[i], ax * ax);
                 const A num = fma(kz * kz * rc, den, lam[i]);
@@ -148,26 +204,40 @@ __global__ __launch_bounds__(8 * (DV < 32 ? DV : 32)) void fwd_pc_kernel(Shape s
                 ya = fma(qw, eta[i] * ilam, ya);
                 wa = fma(qw * qw, ilam, wa);
             }
-            ya = sum8(ya);
-            wa = sum8(wa);
-            // every lane writes (no lane mask): the channel's lane 0 its sums, the others a junk slot
-            *(ng == 0 ? &s_y[t][c] : &s_junk[0][tid]) = (float)ya;
-            *(ng == 0 ? &s_w[t][c] : &s_junk[1][tid]) = (float)wa;
+            ya = lane_sum<LG>(ya);
+            // every lane writes (no lane mask): the channel's last lane its sums, the others a junk slot
+            *(ng == LG - 1 ? &s_y[bb][t][c] : &s_junk[0][tid]) = (float)ya;
+            if (want_w) {
+                wa = lane_sum<LG>(wa);
+                *(ng == LG - 1 ? &s_w[bb][t][c] : &s_junk[1][tid]) = (float)wa;
+            }
+        };
+#pragma unroll 1
+        for (int t8 = 0; t8 < nt; t8 += kCK) {
+            if (ck) {
+#pragma unroll
+                for (int i = 0; i < NPER; ++i) {
+                    const size_t o = (((size_t)bh * nseg + (t0 + t8) / kCK) * DK + ng + LG * i) * DV + d;
+                    ck_lam[o] = lam[i];
+                    ck_eta[o] = eta[i];
+                }
+            }
+            if (nt - t8 >= kCK) {
+#pragma unroll 4
+                for (int j = 0; j < kCK; ++j) token(t8 + j);
+            } else {
+                for (int t = t8; t < nt; ++t) token(t);
+            }
         }
-        __syncthreads();
-        for (int idx = tid; idx < nt * CT; idx += NTHR) {
-            const int t = idx / CT, cc = idx % CT;
-            const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DV + d0 + cc;
-            st(y, o, s_y[t][cc]);
-            if (g.yvar) g.yvar[o] = s_w[t][cc];
-        }
-        // the next block's staging overwrites s_k, s_v only after every lane has read them,
-        // and s_y, s_w only after the stores above
-        __syncthreads();
+    }
+    if (s.T > 0) {
+        barrier_lds();
+        const int tl = (s.T - 1) / kTB * kTB;
+        store(tl, FEW ? (tl / kTB) & 1 : 0);
     }
 #pragma unroll
     for (int i = 0; i < NPER; ++i) {
-        const size_t o = ((size_t)bh * DK + ng + kNG * i) * DV + d;
+        const size_t o = ((size_t)bh * DK + ng + LG * i) * DV + d;
         if (g.lamT) g.lamT[o] = (float)lam[i];
         if (g.etaT) g.etaT[o] = (float)eta[i];
     }
@@ -278,17 +348,22 @@ hipError_t dispatch_pc(const Shape& s, A&&... args) {
     return hipErrorInvalidValue;
 }
 
+// Whether the channels of all heads leave the chip's 1024 SIMDs short of a wave each at 8 lanes
+// per channel.
+bool few_channels(const Shape& s) { return (long)s.B * s.H * s.dv * 8 < 64 * 1024; }
+
 template <typename S, int DK, int DV>
 struct FwdPc {
-    static hipError_t run(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
-        constexpr int CT = DV < 32 ? DV : 32;
-        const dim3 grid((unsigned)(s.B * s.H * (DV / CT))), block(kNG * CT);
-        auto* c = static_cast<typename acc<S>::type*>(ck);
-        if (a.ou_a)
-            hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, true>), grid, block, 0, st, s, a, c);
-        else
-            hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, false>), grid, block, 0, st, s, a, c);
+    template <bool TI, bool FEW>
+    static hipError_t go(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
+        using P = PcFwd<DK, DV, FEW>;
+        hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, TI, FEW>), dim3((unsigned)(s.B * s.H * (DV / P::CT))),
+                           dim3(P::NTHR), 0, st, s, a, static_cast<typename acc<S>::type*>(ck));
         return hipGetLastError();
+    }
+    static hipError_t run(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
+        if (few_channels(s)) return a.ou_a ? go<true, true>(s, a, ck, st) : go<false, true>(s, a, ck, st);
+        return a.ou_a ? go<true, false>(s, a, ck, st) : go<false, false>(s, a, ck, st);
     }
 };
 
@@ -305,31 +380,42 @@ struct FwdPc {
 // cross-lane shuffles, and the writes need no lane mask).
 // At dk = 128 a lane's 4 elements keep 72 trajectory values in registers, so the
 // workgroup takes 16 channels (2 waves per SIMD, room for them) instead of 32.
-template <int DK, int DV, typename A = float>
+// FEW (few_bwd: the default workgroups are fewer than half of the CUs): 8 channels (at most 8
+// tiles), up to 64 lanes each, so that a few heads' channels spread over the chip, at the price of
+// more parts to combine (4 channels gain in the kernel what the combine then loses).  B2 T1024 H8
+// 64 x 64: 32 workgroups of 32 channels 1009 us, 128 of 8 (32 lanes) 583, on 64 lanes with one
+// joint sum per segment 477, with a branch-free walk of whole segments 408 us.
+template <int DK, int DV, bool FEW, typename A = float>
 struct PcLanes {
-    static constexpr int LPC = DK < 32 ? DK : 32;
+    static constexpr int LMAX = FEW ? 64 : 32;
+    static constexpr int LPC = DK < LMAX ? DK : LMAX;
     static constexpr int NPER = DK / LPC;
     // fp64 arithmetic doubles the trajectory registers: 16 channels from dk = 64 on
     static constexpr int CBMAX = DK == 128 || (DK == 64 && sizeof(A) == 8) ? 16 : 32;
-    static constexpr int CB = DV < CBMAX ? DV : CBMAX;
+    static constexpr int CBFEW = DV / 8 > 8 ? DV / 8 : 8;
+    static constexpr int CB = FEW ? CBFEW : DV < CBMAX ? DV : CBMAX;
     static constexpr int NTHR = LPC * CB;
+    // tokens whose key-slot values are held for one joint sum: a whole segment where they fit
+    // 64 KiB (two otherwise, in turn): one barrier per segment instead of one per token
+    static constexpr int NRED = FEW && CB * 4 * DK * 4 * kCK <= 64 * 1024 ? kCK : 2;
 };
 
-template <typename S, int DK, int DV, bool TI>
-__global__ __launch_bounds__((PcLanes<DK, DV, typename acc<S>::type>::NTHR)) void bwd_pc_kernel(Shape s, BwdArgs g,
+template <typename S, int DK, int DV, bool TI, bool FEW>
+__global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)) void bwd_pc_kernel(Shape s, BwdArgs g,
                                                                         const typename acc<S>::type* ck,
                                                                         float* kpart) {
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
-    using PL = PcLanes<DK, DV, A>;
+    using PL = PcLanes<DK, DV, FEW, A>;
     constexpr int LPC = PL::LPC, NPER = PL::NPER;
     constexpr int CB = PL::CB;
     constexpr int NTHR = LPC * CB;
-    static_assert(NTHR % 64 == 0 && (LPC == 16 || LPC == 32), "lane layout");
+    constexpr int NRED = PL::NRED;
+    static_assert(NTHR % 64 == 0, "lane layout");
     __shared__ float4 s_k[kCK][DK];        // abar, pbar, k, q
     __shared__ float4 s_c[kCK][CB];        // r, v, dy, dyvar
     __shared__ float2 s_o[kCK][CB];        // dv, dr
-    __shared__ float s_red[2][CB][4][DK];  // per-channel key-slot values of dq, dk, dabar, dpbar
+    __shared__ float s_red[NRED][CB][4][DK];  // per-channel key-slot values of dq, dk, dabar, dpbar
 
     const T_ *q = static_cast<const T_*>(g.q), *k = static_cast<const T_*>(g.k), *v = static_cast<const T_*>(g.v);
     const T_ *a = static_cast<const T_*>(g.a), *p = static_cast<const T_*>(g.p), *r = static_cast<const T_*>(g.r);
@@ -409,98 +495,102 @@ __global__ __launch_bounds__((PcLanes<DK, DV, typename acc<S>::type>::NTHR)) voi
         }
         barrier_lds();   // the segment's inputs are in
         fetch(sg > 0 ? sg - 1 : 0);
-#pragma unroll
-        for (int j = 0; j < kCK; ++j) {
-            const bool ok = j < nt;
-            const float4 cv = s_c[ok ? j : 0][c];
-            const A rc = cv.x, krv = (A)cv.x * (A)cv.y;
-#pragma unroll
-            for (int i = 0; i < NPER; ++i) {
-                const float4 in = s_k[ok ? j : 0][ln + LPC * i];
-                const A ax = TI ? ga[i] : (A)in.x, py = TI ? gp[i] : (A)in.y, kz = in.z;
-                const A den = fma(py, lt[j][i], ax * ax);
-                const A num = fma(kz * kz * rc, den, lt[j][i]);
-                const A R = rcpa(den * num);
-                const A iden = num * R;
-                lt[j + 1][i] = ok ? num * iden : lt[j][i];
-                et[j + 1][i] = ok ? fma(ax * iden, et[j][i], kz * krv) : et[j][i];
-            }
-        }
-        // reverse over the segment's tokens
-#pragma unroll
-        for (int j = kCK - 1; j >= 0; --j) {
-            if (j >= nt) continue;   // uniform: the tail of the last segment
-            const float4 cv = s_c[j][c];   // r, v, gy, gv
-            const A cr = cv.x, cvv = cv.y, gy = cv.z, gv = cv.w;
-            float kq[4][NPER];             // this lane's dq, dk, dabar, dpbar of token j
-            A cdv = 0, cdr = 0;
-#pragma unroll
-            for (int i = 0; i < NPER; ++i) {
-                const float4 in = s_k[j][ln + LPC * i];   // abar, pbar, k, q
-                const A av = TI ? ga[i] : (A)in.x, pv = TI ? gp[i] : (A)in.y, kv = in.z, qv = in.w;
-                const A lp = lt[j][i], lc = lt[j + 1][i], ep = et[j][i], ec = et[j + 1][i];
-                const A den = fma(pv, lp, av * av);
-                const A R = rcpa(lc * den);
-                const A ilc = den * R, rho = lc * R;
-                const A mu = ec * ilc;
-                const A qgy = qv * gy;
-                kq[0][i] = (float)fma(mu, gy, A(2) * qv * gv * ilc);
-                const A gei = fma(qgy, ilc, ge[i]);
-                const A gli = gl[i] - fma(qgy, mu, qv * qv * gv * ilc) * ilc;
-                const A df = gei * ep;
-                const A kr = kv * cr;
-                kq[1][i] = (float)fma(gei, cr * cvv, A(2) * gli * kr);
-                cdr = fma(gei, kv * cvv, fma(gli, kv * kv, cdr));
-                cdv = fma(gei, kr, cdv);
-                const A drho = fma(df, av, gli * lp);
-                const A dden = -drho * rho * rho;
-                if constexpr (TI) {
-                    sum_da[i] += fma(df, rho, A(2) * av * dden);
-                    sum_dp[i] += dden * lp;
-                } else {
-                    kq[2][i] = (float)fma(df, rho, A(2) * av * dden);
-                    kq[3][i] = (float)(dden * lp);
-                }
-                ge[i] = av * rho * gei;
-                gl[i] = fma(gli, rho, pv * dden);
-            }
-            // channel sums over the LPC lanes of the channel
-            if constexpr (LPC == 32) {
-                cdv = half_sum(cdv);
-                cdr = half_sum(cdr);
-            } else {
-                cdv += dpp<0xB1, 0xf>(cdv);
-                cdv += dpp<0x4E, 0xf>(cdv);
-                cdv += dpp<0x141, 0xf>(cdv);
-                cdv += dpp<0x140, 0xf>(cdv);
-                cdr += dpp<0xB1, 0xf>(cdr);
-                cdr += dpp<0x4E, 0xf>(cdr);
-                cdr += dpp<0x141, 0xf>(cdr);
-                cdr += dpp<0x140, 0xf>(cdr);
-            }
-            if (ln == LPC - 1) s_o[j][c] = make_float2((float)cdv, (float)cdr);
-            // key-slot sums over the channels of the workgroup: every channel's values go to
-            // its own LDS row, summed in a fixed order after the barrier
-            float* slot = &s_red[j & 1][c][0][0];
-#pragma unroll
-            for (int qi = 0; qi < NQ; ++qi)
-#pragma unroll
-                for (int i = 0; i < NPER; ++i) slot[qi * DK + ln + LPC * i] = kq[qi][i];
-            barrier_lds();   // the channels' key-slot values of token j are in
-            const size_t tk = ((size_t)b * T + t0 + j) * s.H + h;
-            constexpr int RPT = (NQ * DK + NTHR - 1) / NTHR;
+        // this tile's part of the key-slot sums of tokens j0 .. j0 + n - 1, over its channels in order
+        auto sum_parts = [&](int j0, int n) {
+            constexpr int PER = NQ * DK, RPT = ((NRED == kCK ? kCK : 1) * PER + NTHR - 1) / NTHR;
 #pragma unroll
             for (int m = 0; m < RPT; ++m) {
-                const int idx = tid + NTHR * m;
-                if (RPT * NTHR != NQ * DK && idx >= NQ * DK) continue;
+                const int it = tid + NTHR * m, j = j0 + it / PER, idx = it % PER;
+                if (j >= j0 + n) continue;
                 float acc = 0.f;
 #pragma unroll
-                for (int cc = 0; cc < CB; ++cc) acc += (&s_red[j & 1][cc][0][0])[idx];
-                const int qi = idx / DK, n = idx % DK;
-                kpart[((size_t)tile * 4 + qi) * nkey + tk * DK + n] = acc;
+                for (int cc = 0; cc < CB; ++cc) acc += (&s_red[j % NRED][cc][0][0])[idx];
+                const int qi = idx / DK, nn = idx % DK;
+                const size_t tk = ((size_t)b * T + t0 + j) * s.H + h;
+                kpart[((size_t)tile * 4 + qi) * nkey + tk * DK + nn] = acc;
             }
-        }
-        barrier_lds();   // the channel sums of the segment are in
+        };
+        // FULL: every token valid, so that the tokens' reads and sums overlap
+        auto walk = [&](auto full_tag) {
+            constexpr bool FULL = decltype(full_tag)::value;
+#pragma unroll
+            for (int j = 0; j < kCK; ++j) {
+                const bool ok = FULL || j < nt;
+                const float4 cv = s_c[ok ? j : 0][c];
+                const A rc = cv.x, krv = (A)cv.x * (A)cv.y;
+#pragma unroll
+                for (int i = 0; i < NPER; ++i) {
+                    const float4 in = s_k[ok ? j : 0][ln + LPC * i];
+                    const A ax = TI ? ga[i] : (A)in.x, py = TI ? gp[i] : (A)in.y, kz = in.z;
+                    const A den = fma(py, lt[j][i], ax * ax);
+                    const A num = fma(kz * kz * rc, den, lt[j][i]);
+                    const A R = rcpa(den * num);
+                    const A iden = num * R;
+                    lt[j + 1][i] = ok ? num * iden : lt[j][i];
+                    et[j + 1][i] = ok ? fma(ax * iden, et[j][i], kz * krv) : et[j][i];
+                }
+            }
+            // reverse over the segment's tokens
+#pragma unroll
+            for (int j = kCK - 1; j >= 0; --j) {
+                if (!FULL && j >= nt) continue;   // uniform: the tail of the last segment
+                const float4 cv = s_c[j][c];   // r, v, gy, gv
+                const A cr = cv.x, cvv = cv.y, gy = cv.z, gv = cv.w;
+                float kq[4][NPER];             // this lane's dq, dk, dabar, dpbar of token j
+                A cdv = 0, cdr = 0;
+#pragma unroll
+                for (int i = 0; i < NPER; ++i) {
+                    const float4 in = s_k[j][ln + LPC * i];   // abar, pbar, k, q
+                    const A av = TI ? ga[i] : (A)in.x, pv = TI ? gp[i] : (A)in.y, kv = in.z, qv = in.w;
+                    const A lp = lt[j][i], lc = lt[j + 1][i], ep = et[j][i], ec = et[j + 1][i];
+                    const A den = fma(pv, lp, av * av);
+                    const A R = rcpa(lc * den);
+                    const A ilc = den * R, rho = lc * R;
+                    const A mu = ec * ilc;
+                    const A qgy = qv * gy;
+                    kq[0][i] = (float)fma(mu, gy, A(2) * qv * gv * ilc);
+                    const A gei = fma(qgy, ilc, ge[i]);
+                    const A gli = gl[i] - fma(qgy, mu, qv * qv * gv * ilc) * ilc;
+                    const A df = gei * ep;
+                    const A kr = kv * cr;
+                    kq[1][i] = (float)fma(gei, cr * cvv, A(2) * gli * kr);
+                    cdr = fma(gei, kv * cvv, fma(gli, kv * kv, cdr));
+                    cdv = fma(gei, kr, cdv);
+                    const A drho = fma(df, av, gli * lp);
+                    const A dden = -drho * rho * rho;
+                    if constexpr (TI) {
+                        sum_da[i] += fma(df, rho, A(2) * av * dden);
+                        sum_dp[i] += dden * lp;
+                    } else {
+                        kq[2][i] = (float)fma(df, rho, A(2) * av * dden);
+                        kq[3][i] = (float)(dden * lp);
+                    }
+                    ge[i] = av * rho * gei;
+                    gl[i] = fma(gli, rho, pv * dden);
+                }
+                // channel sums over the LPC lanes of the channel
+                cdv = lane_sum<LPC>(cdv);
+                cdr = lane_sum<LPC>(cdr);
+                if (ln == LPC - 1) s_o[j][c] = make_float2((float)cdv, (float)cdr);
+                // key-slot sums over the channels of the workgroup: every channel's values go to
+                // its own LDS row, summed in a fixed order after the barrier
+                float* slot = &s_red[j % NRED][c][0][0];
+#pragma unroll
+                for (int qi = 0; qi < NQ; ++qi)
+#pragma unroll
+                    for (int i = 0; i < NPER; ++i) slot[qi * DK + ln + LPC * i] = kq[qi][i];
+                if constexpr (NRED < kCK) {
+                    barrier_lds();   // the channels' key-slot values of token j are in
+                    sum_parts(j, 1);
+                }
+            }
+        };
+        if (nt == kCK)
+            walk(std::true_type{});
+        else
+            walk(std::false_type{});
+        barrier_lds();   // the channel sums (and, held for a segment, the key-slot values) are in
+        if constexpr (NRED == kCK) sum_parts(0, nt);
         for (int idx = tid; idx < nt * CB; idx += NTHR) {
             const int t = idx / CB, cc = idx % CB;
             const size_t o = (((size_t)b * T + t0 + t) * s.H + h) * DV + d0 + cc;
@@ -553,29 +643,35 @@ __global__ __launch_bounds__(256) void pc_key_combine_kernel(const float* __rest
     }
 }
 
+// channels per workgroup of the backward by default (PcLanes), and whether it takes fewer
+int pc_cb(const Shape& s) {
+    const int cbmax = s.dk == 128 || (s.dk == 64 && !s.bf16) ? 16 : 32;
+    return s.dv < cbmax ? s.dv : cbmax;
+}
+bool few_bwd(const Shape& s) {
+    return s.B * s.H * (s.dv / pc_cb(s)) < 128;
+}
+
 template <typename S, int DK, int DV>
 struct BwdPc {
-    static hipError_t run(const Shape& s, const BwdArgs& a, const void* ck, float* kpart, hipStream_t st) {
-        using PL = PcLanes<DK, DV, typename acc<S>::type>;
-        constexpr int CB = PL::CB;
-        constexpr int NTHR = PL::NTHR;
-        const dim3 grid((unsigned)(s.B * s.H * (DV / CB))), block(NTHR);
-        auto* c = static_cast<const typename acc<S>::type*>(ck);
-        if (a.ou_a)
-            hipLaunchKernelGGL((bwd_pc_kernel<S, DK, DV, true>), grid, block, 0, st, s, a, c, kpart);
-        else
-            hipLaunchKernelGGL((bwd_pc_kernel<S, DK, DV, false>), grid, block, 0, st, s, a, c, kpart);
+    template <bool TI, bool FEW>
+    static hipError_t go(const Shape& s, const BwdArgs& a, const void* ck, float* kpart, hipStream_t st) {
+        using PL = PcLanes<DK, DV, FEW, typename acc<S>::type>;
+        constexpr int NT = DV / PL::CB;
+        hipLaunchKernelGGL((bwd_pc_kernel<S, DK, DV, TI, FEW>), dim3((unsigned)(s.B * s.H * NT)), dim3(PL::NTHR), 0, st, s,
+                           a, static_cast<const typename acc<S>::type*>(ck), kpart);
         hipError_t e = hipGetLastError();
         const size_t n = (size_t)s.B * s.T * s.H * DK;   // dk is a multiple of 16, n of 4
         if (e != hipSuccess || n == 0) return e;
-        constexpr int NT = DV / CB;
         static_assert(DK % 4 == 0 && (NT == 1 || NT == 2 || NT == 4 || NT == 8), "combine layout");
-        const dim3 cgrid((unsigned)((n / 4 + 255) / 256));
-        if (a.ou_a)   // the gate gradients went to the parameter parts
-            hipLaunchKernelGGL((pc_key_combine_kernel<S, NT, 2>), cgrid, dim3(256), 0, st, kpart, n, a);
-        else
-            hipLaunchKernelGGL((pc_key_combine_kernel<S, NT, 4>), cgrid, dim3(256), 0, st, kpart, n, a);
+        // with OU gates the gate gradients went to the parameter parts
+        hipLaunchKernelGGL((pc_key_combine_kernel<S, NT, TI ? 2 : 4>), dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0,
+                           st, kpart, n, a);
         return hipGetLastError();
+    }
+    static hipError_t run(const Shape& s, const BwdArgs& a, const void* ck, float* kpart, hipStream_t st) {
+        if (few_bwd(s)) return a.ou_a ? go<true, true>(s, a, ck, kpart, st) : go<false, true>(s, a, ck, kpart, st);
+        return a.ou_a ? go<true, false>(s, a, ck, kpart, st) : go<false, false>(s, a, ck, kpart, st);
     }
 };
 
@@ -609,8 +705,7 @@ size_t pc_ou_part_bytes(const Shape& s) {
 }
 
 size_t pc_bwd_workspace(const Shape& s) {
-    const int cbmax = s.dk == 128 || (s.dk == 64 && !s.bf16) ? 16 : 32;   // as PcLanes
-    const int cb = s.dv < cbmax ? s.dv : cbmax;
+    const int cb = few_bwd(s) ? (s.dv / 8 > 8 ? s.dv / 8 : 8) : pc_cb(s);
     return (size_t)(s.dv / cb) * 4 * part_stride((size_t)s.B * s.T * s.H * s.dk) * sizeof(float);
 }
 
