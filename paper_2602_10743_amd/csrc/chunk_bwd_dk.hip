@@ -37,7 +37,7 @@
 //          half (the wave's four 16-lane rows) are chained by lane swaps from
 //          the saved state at the start of the half (lam_0, or lam_16 and
 //          P_16), and each lane walks its 4 tokens from the group start,
-//          writing Qp and Kn ([t][16], split bf16) and keeping lam_t, P_t and
+//          writing Qp and Kn (slot-major, split bf16) and keeping lam_t, P_t and
 //          the reciprocals the adjoint walk needs;
 //   MFMA   split by operand instead: wave 0 forms B^T and X^T (with the chunk's
 //          saved start state H0 in registers), wave 1 forms B and Y^T and
@@ -49,6 +49,15 @@
 // the phases.  The next chunk's inputs go straight into LDS, requested during
 // the first pass of a round's adjoint walk; the chunk's saved state rows come
 // into wave 0's registers at the start of its round.
+//
+// What bounds it is issue: two waves per SIMD walk dependent fp32 chains between barriers,
+// with LDS instructions the largest share.  The per-pair tiles are slot-major (nt_off) so that a lane
+// writes its four tokens with one 8-byte store and reads them with one transposing read, the
+// group summaries are one vector per slot, and the sum over slots for dr is taken in registers:
+// 746 -> 418 LDS instructions in the 128 x 128 kernel.  Reads whose bytes came by direct loads
+// are written out in asm with their own wait, since for the builtin the compiler also waits for
+// every request in flight.  8 sequences of 2048, 16 heads of 128 x 128: 485 -> 440 us; the
+// split kernel at 2 sequences: 95 -> 89 us.
 //
 // TI (gates from OU parameters, the same for every token of a key slot): abar
 // and pbar are formed once per lane and not loaded; dabar and dpbar are not
@@ -74,7 +83,7 @@ struct DkCfg {
     static constexpr int CPR = DV / 8;                      // 16-byte chunks per dY / V row
     static constexpr int TPV = 512 / DV;                    // rows per 1 KiB load of a dY / V tile
     static constexpr int NVL = kC / TPV;                    // 1 KiB loads per dY / V tile
-    static constexpr int LQ2 = 24;                          // row stride of per-pair [t][16] bf16 tiles
+    static constexpr int TQ = 16 * kC * 2;                  // bytes of a per-pair slot-major bf16 tile (nt_off)
     static constexpr int LX = 20;                           // row stride of per-pair [t][16] fp32 tiles
     static constexpr int NG = 8;                            // token groups per chunk (4 tokens each)
     // shared: dY and V tiles [2 buffers][2][kC][DV] (16-byte chunks swizzled by row)
@@ -85,19 +94,19 @@ struct DkCfg {
     static constexpr int RW = STG + 2 * 4 * kC * 16 * 2;            // [2][64] r words
     static constexpr int LW = RW + 2 * 64 * 4;                      // [2][64] walk state: lam_0, lam_16, P_16 [3][16]
     static constexpr int GV = LW + 2 * 64 * 4;                      // [2][64] yvar gradient (fp32)
-    static constexpr int QH = GV + 2 * 64 * 4;                      // Qp, Kn split bf16 [kC][LQ2]
-    static constexpr int QL = QH + kC * LQ2 * 2, KH = QL + kC * LQ2 * 2, KL = KH + kC * LQ2 * 2;
-    static constexpr int XT = KL + kC * LQ2 * 2, YT = XT + kC * LX * 4;   // X, Y fp32 [kC][LX]
-    static constexpr int QS = YT + kC * LX * 4;                     // adjoint group summaries [NG][4][16] fp32
+    static constexpr int QH = GV + 2 * 64 * 4;                      // Qp, Kn split bf16 (slot, t)
+    static constexpr int QL = QH + TQ, KH = QL + TQ, KL = KH + TQ;
+    static constexpr int XT = KL + TQ, YT = XT + kC * LX * 4;   // X, Y fp32 [kC][LX]
+    static constexpr int QS = YT + kC * LX * 4;                     // adjoint group summaries [NG][16][4] fp32
     static constexpr int PC = QS + NG * 4 * 16 * 4;                 // chunk decay P_C [16] fp32
     static constexpr int WT = PC + 16 * 4;                          // chunk totals of the state parts [2][16]
     static constexpr int PAIR = (WT + 2 * 16 * 4 + 15) / 16 * 16;
     static constexpr int BYTES = PAIR0 + NP * PAIR;   // dynamic part
-    // The gradient tiles dq, dk, dabar, dpbar [4][kC][16] bf16 and the dr terms
-    // [kC][17] fp32 of each pair live in separate static arrays: they are read
-    // back while the next chunk's direct-to-LDS loads are in flight, and as
-    // distinct objects they are seen not to alias those loads' destinations.
-    static constexpr int STATIC = NP * (4 * kC * 16 * 2 + kC * 17 * 4);
+    // The gradient tiles dq, dk, dabar, dpbar (slot, t) bf16 of each pair live in a
+    // separate static array: they are read back while the next chunk's direct-to-LDS
+    // loads are in flight, and as a distinct object they are seen not to alias those
+    // loads' destinations.
+    static constexpr int STATIC = NP * 4 * kC * 16 * 2;
     static_assert(DK >= 32 && DK % 16 == 0 && DV >= 32 && DV % 32 == 0, "backward tile sizes");
     static_assert(NVL >= 1 && TPV * CPR == 64, "value tile loads");
     static_assert(4 + 2 * ((NVL + NW - 1) / NW) <= 8, "requests spread over 4 tokens, two each");
@@ -124,14 +133,30 @@ __device__ __forceinline__ bf16x8 lds4x2_swz(const uint16_t* tile, int t, int d0
     return lds4x2(swz<DV>(tile, t, d0), swz<DV>(tile, t, d1));
 }
 
-// lds_tr8 over a swizzled tile: lane s receives tile[rowA + j][col0 + s] and
-// tile[rowB + j][col0 + s], j = 0..3 (col0 a multiple of 16)
-template <int DV>
-__device__ __forceinline__ bf16x8 lds_tr8_swz(const uint16_t* tile, int rowA, int rowB, int col0, int s) {
-    const int col = col0 + 4 * (s & 3);
-    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)swz<DV>(tile, rowA + (s >> 2), col));
-    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)swz<DV>(tile, rowB + (s >> 2), col));
-    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
+
+// byte address of an LDS object, as the DS instructions take it
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// Two operands of lds_tr8 (four transposing reads at the given byte addresses) with their wait
+// written out: as a builtin such a read waits, besides, for every direct load into LDS in flight.
+__device__ __forceinline__ void tr8x2(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1, bf16x8& x, bf16x8& y) {
+    uint64_t p, q, r, t;
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %5\n\t"
+        "ds_read_b64_tr_b16 %2, %6\n\tds_read_b64_tr_b16 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(p), "=&v"(q), "=&v"(r), "=&v"(t) : "v"(a0), "v"(a1), "v"(b0), "v"(b1) : "memory");
+    typedef __attribute__((__vector_size__(2 * sizeof(uint64_t)))) uint64_t u64x2_t;
+    x = __builtin_bit_cast(bf16x8, u64x2_t{p, q});
+    y = __builtin_bit_cast(bf16x8, u64x2_t{r, t});
+}
+
+// 8-byte LDS write through a scalar type (a vector struct's store is taken to alias the direct
+// loads in flight, and waits for them)
+__device__ __forceinline__ void st_b64(uint16_t* p, uint32_t lo, uint32_t hi) {
+    *reinterpret_cast<uint64_t*>(p) = (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
 // sum over each 16-lane row, held by every lane of the row
@@ -165,13 +190,12 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                                                                        float* __restrict__ xy,
                                                                        float* __restrict__ coef) {
     using Cfg = DkCfg<DK, DV>;
-    constexpr int NP = Cfg::NP, NW = Cfg::NW, KSD = Cfg::KSD, NRD = Cfg::NRD, LQ2 = Cfg::LQ2, LX = Cfg::LX;
+    constexpr int NP = Cfg::NP, NW = Cfg::NW, KSD = Cfg::KSD, NRD = Cfg::NRD, LX = Cfg::LX;
     constexpr int NG = Cfg::NG;
     // stores per round: dq, dk(, dabar, dpbar) and dr; SPLIT: dqt, dkh of 4 tokens, two of coef
     constexpr int NST = SPLIT ? 10 : TI ? 3 : 5;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ __align__(16) uint16_t s_out[NP * 4 * kC * 16];
-    __shared__ __align__(16) float s_drc[NP * kC * 17];
 
     const uint16_t* a = static_cast<const uint16_t*>(g.a);
     const uint16_t* p = static_cast<const uint16_t*>(g.p);
@@ -323,15 +347,54 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             float* sPC = reinterpret_cast<float*>(wb + Cfg::PC);
             float* sWT = reinterpret_cast<float*>(wb + Cfg::WT);   // [2][16]: sum_t Qp X0, sum_j Kn Yg
             float* qs = reinterpret_cast<float*>(wb + Cfg::QS);
-            auto in_a = [&](int t) {
-                return TI ? ca : __uint_as_float((uint32_t)stg[(0 * kC + t) * 16 + nl] << 16);
+            // the lane's four tokens 4 gg .. 4 gg + 3, read again in each phase that uses them (one
+            // transposing read per tensor; kept, they would cost nine registers across the phases).
+            // Written out with their wait: for the builtin the compiler would also wait for every
+            // request and store in flight, as the staging area is filled by direct loads.
+            struct Toks {
+                uint2 a, p, k, q;
+                uint4 r;
             };
-            auto in_p = [&](int t) {
-                return TI ? cp : __uint_as_float((uint32_t)stg[(1 * kC + t) * 16 + nl] << 16);
+            const uint32_t tok_at = lds_addr(stg + (4 * gg + (nl >> 2)) * 16 + 4 * (nl & 3));
+            const uint32_t r_at = lds_addr(rw + 4 * gg);
+            static_assert(kC * 16 * 2 == 1024, "staged tensors 1 KiB apart");
+            auto read_toks = [&](auto with_q) {
+                Toks w;
+                uint64_t xa, xp, xk, xq;
+                u32x4_t xr;
+                if constexpr (!TI && decltype(with_q)::value) {
+                    asm volatile(
+                        "ds_read_b64_tr_b16 %0, %5\n\tds_read_b64_tr_b16 %1, %5 offset:1024\n\t"
+                        "ds_read_b64_tr_b16 %2, %5 offset:2048\n\tds_read_b64_tr_b16 %3, %5 offset:3072\n\t"
+                        "ds_read_b128 %4, %6\n\ts_waitcnt lgkmcnt(0)"
+                        : "=&v"(xa), "=&v"(xp), "=&v"(xk), "=&v"(xq), "=&v"(xr) : "v"(tok_at), "v"(r_at) : "memory");
+                    w.q = __builtin_bit_cast(uint2, xq);
+                } else if constexpr (!TI) {
+                    asm volatile(
+                        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:1024\n\t"
+                        "ds_read_b64_tr_b16 %2, %4 offset:2048\n\tds_read_b128 %3, %5\n\ts_waitcnt lgkmcnt(0)"
+                        : "=&v"(xa), "=&v"(xp), "=&v"(xk), "=&v"(xr) : "v"(tok_at), "v"(r_at) : "memory");
+                } else if constexpr (decltype(with_q)::value) {
+                    asm volatile(
+                        "ds_read_b64_tr_b16 %0, %3 offset:2048\n\tds_read_b64_tr_b16 %1, %3 offset:3072\n\t"
+                        "ds_read_b128 %2, %4\n\ts_waitcnt lgkmcnt(0)"
+                        : "=&v"(xk), "=&v"(xq), "=&v"(xr) : "v"(tok_at), "v"(r_at) : "memory");
+                    w.q = __builtin_bit_cast(uint2, xq);
+                } else {
+                    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:2048\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                                 : "=&v"(xk), "=&v"(xr) : "v"(tok_at), "v"(r_at) : "memory");
+                }
+                if constexpr (!TI) {
+                    w.a = __builtin_bit_cast(uint2, xa);
+                    w.p = __builtin_bit_cast(uint2, xp);
+                }
+                w.k = __builtin_bit_cast(uint2, xk);
+                w.r = uint4{xr[0], xr[1], xr[2], xr[3]};
+                return w;
             };
-            auto in_k = [&](int t) { return __uint_as_float((uint32_t)stg[(2 * kC + t) * 16 + nl] << 16); };
-            auto in_q = [&](int t) { return __uint_as_float((uint32_t)stg[(3 * kC + t) * 16 + nl] << 16); };
-            auto in_r = [&](int t) { return __uint_as_float(rw[t] << 16); };
+            auto in_a = [&](const Toks& w, int j) { return TI ? ca : tok(w.a, j); };
+            auto in_p = [&](const Toks& w, int j) { return TI ? cp : tok(w.p, j); };
+            auto in_r = [&](const Toks& w, int j) { return __uint_as_float((&w.r.x)[j] << 16); };
             const float* gvw = reinterpret_cast<const float*>(wb + Cfg::GV) + bb * 64;
 
             // ================================================================ phase 1
@@ -379,10 +442,11 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             float tr[5];
             {
                 float x0 = 1.f, z0 = 0.f, x1 = 0.f, z1 = 1.f, Aq = 1.f;
+                const Toks w = read_toks(std::false_type{});
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int t = 4 * gg + j;
-                    const float av = in_a(t), pv = in_p(t), kv = in_k(t), rv = in_r(t);
+                    const float av = in_a(w, j), pv = in_p(w, j), kv = tok(w.k, j), rv = in_r(w, j);
                     const float a2 = av * av, phi = kv * kv * rv;
                     const float z0n = fmaf(pv, x0, a2 * z0), z1n = fmaf(pv, x1, a2 * z1);
                     const bool ok = FULL || t < nt;
@@ -422,13 +486,15 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             // per token of the group: lam_t, P_t and, for the adjoint walk, 1/P_t, 1/lam_t,
             // rho_t, 1/rho_t = abar^2 + pbar lam_{t-1}, 1/abar
             float lam_r[4], P_r[4], iP_r[4], il_r[4], rho_r[4], den_r[4], ia_r[4];
+            uint2 qh, ql, kh, kl;   // the four tokens' Qp, Kn
+            const Toks w2 = read_toks(std::true_type{});
 #pragma unroll
             for (int j2 = 0; j2 < 2; ++j2) {
                 float qp2[2], kn2[2];
 #pragma unroll
                 for (int e2 = 0; e2 < 2; ++e2) {
                     const int j = 2 * j2 + e2, t = 4 * gg + j;
-                    const float av = in_a(t), pv = in_p(t), kv = in_k(t), qv = in_q(t), rv = in_r(t);
+                    const float av = in_a(w2, j), pv = in_p(w2, j), kv = tok(w2.k, j), qv = tok(w2.q, j), rv = in_r(w2, j);
                     const float kr = kv * rv;
                     const float zn = fmaf(pv, x, av * av * z);
                     const float xn = fmaf(kr * kv, zn, x);
@@ -452,19 +518,14 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                     z = ok ? zn : z;
                     A = ok ? An : A;
                 }
-                uint32_t qh, ql, kh, kl;
-                split2(qp2[0], qp2[1], qh, ql);
-                split2(kn2[0], kn2[1], kh, kl);
-                const int t = 4 * gg + 2 * j2;
-                sQH[t * LQ2 + nl] = static_cast<uint16_t>(qh);
-                sQH[(t + 1) * LQ2 + nl] = static_cast<uint16_t>(qh >> 16);
-                sQL[t * LQ2 + nl] = static_cast<uint16_t>(ql);
-                sQL[(t + 1) * LQ2 + nl] = static_cast<uint16_t>(ql >> 16);
-                sKH[t * LQ2 + nl] = static_cast<uint16_t>(kh);
-                sKH[(t + 1) * LQ2 + nl] = static_cast<uint16_t>(kh >> 16);
-                sKL[t * LQ2 + nl] = static_cast<uint16_t>(kl);
-                sKL[(t + 1) * LQ2 + nl] = static_cast<uint16_t>(kl >> 16);
+                split2(qp2[0], qp2[1], j2 ? qh.y : qh.x, j2 ? ql.y : ql.x);
+                split2(kn2[0], kn2[1], j2 ? kh.y : kh.x, j2 ? kl.y : kl.x);
             }
+            const int e0 = nt_off(nl, 4 * gg);
+            st_b64(sQH + e0, qh.x, qh.y);
+            st_b64(sQL + e0, ql.x, ql.y);
+            st_b64(sKH + e0, kh.x, kh.y);
+            st_b64(sKL + e0, kl.x, kl.y);
             if (gg == NG - 1) sPC[nl] = A * fast_rcp(z);   // the last group ends at the chunk end
             barrier_lds();   // Qp, Kn of every token and P_C are in
 
@@ -483,23 +544,26 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 }
                 {   // chunk total of Qp X0 per slot n = 4 g4 + rr (tokens past the end have Qp = 0)
                     float w[4];
+                    uint2 th[2], tl[2];
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt) {
+                        th[tt] = nt_tr4(sQH, 4 * g4, 16 * tt, l16);
+                        tl[tt] = nt_tr4(sQL, 4 * g4, 16 * tt, l16);
+                    }
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
                         w[rr] = 0.f;
 #pragma unroll
-                        for (int tt = 0; tt < 2; ++tt) {
-                            const int o = (16 * tt + l16) * LQ2 + 4 * g4 + rr;
-                            const float qp = __uint_as_float((uint32_t)sQH[o] << 16) + __uint_as_float((uint32_t)sQL[o] << 16);
-                            w[rr] = fmaf(qp, xacc[tt][rr], w[rr]);
-                        }
+                        for (int tt = 0; tt < 2; ++tt)
+                            w[rr] = fmaf(tok(th[tt], rr) + tok(tl[tt], rr), xacc[tt][rr], w[rr]);
                         w[rr] = row_sum16f(w[rr]);
                     }
                     if (l16 == 0)
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) sWT[4 * g4 + rr] = w[rr];
                 }
-                const bf16x8 knh = lds_tr8(sKH, LQ2, 4 * g4, 16 + 4 * g4, 0, l16);
-                const bf16x8 knl = lds_tr8(sKL, LQ2, 4 * g4, 16 + 4 * g4, 0, l16);
+                const int o0 = nt_off(l16, 4 * g4), o1 = nt_off(l16, 16 + 4 * g4);
+                const bf16x8 knh = lds4x2(sKH + o0, sKH + o1), knl = lds4x2(sKL + o0, sKL + o1);
 #pragma unroll
                 for (int tt = 0; tt < 2; ++tt) {
                     xacc[tt] = mfma3(knh, knl, boh[tt], bol[tt], xacc[tt]);
@@ -527,23 +591,26 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 }
                 {   // chunk total of Kn Yg per slot n = 4 g4 + rr (tokens past the end have Kn = 0)
                     float w[4];
+                    uint2 th[2], tl[2];
+#pragma unroll
+                    for (int jt = 0; jt < 2; ++jt) {
+                        th[jt] = nt_tr4(sKH, 4 * g4, 16 * jt, l16);
+                        tl[jt] = nt_tr4(sKL, 4 * g4, 16 * jt, l16);
+                    }
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr) {
                         w[rr] = 0.f;
 #pragma unroll
-                        for (int jt = 0; jt < 2; ++jt) {
-                            const int o = (16 * jt + l16) * LQ2 + 4 * g4 + rr;
-                            const float kn = __uint_as_float((uint32_t)sKH[o] << 16) + __uint_as_float((uint32_t)sKL[o] << 16);
-                            w[rr] = fmaf(kn, yacc[jt][rr], w[rr]);
-                        }
+                        for (int jt = 0; jt < 2; ++jt)
+                            w[rr] = fmaf(tok(th[jt], rr) + tok(tl[jt], rr), yacc[jt][rr], w[rr]);
                         w[rr] = row_sum16f(w[rr]);
                     }
                     if (l16 == 0)
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) sWT[16 + 4 * g4 + rr] = w[rr];
                 }
-                const bf16x8 qth = lds_tr8(sQH, LQ2, 4 * g4, 16 + 4 * g4, 0, l16);
-                const bf16x8 qtl = lds_tr8(sQL, LQ2, 4 * g4, 16 + 4 * g4, 0, l16);
+                const int o0 = nt_off(l16, 4 * g4), o1 = nt_off(l16, 16 + 4 * g4);
+                const bf16x8 qth = lds4x2(sQH + o0, sQH + o1), qtl = lds4x2(sQL + o0, sQL + o1);
 #pragma unroll
                 for (int jt = 0; jt < 2; ++jt) yacc[jt] = mfma3(qth, qtl, boh[jt], bol[jt], yacc[jt]);
 #pragma unroll
@@ -560,10 +627,11 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             float u_[4], w_[4], al_[4], be_[4], dq_[4], rdk_[4], kr2_[4], ia_[4], a2r2_[4], lp_[4], den_[4], lpr2_[4],
                 kdk_[4], kk_[4];
             float Am = 1.f, Bm = 0.f, Cm = 0.f, Dm = 0.f;
+            const Toks w4 = read_toks(std::true_type{});
 #pragma unroll
             for (int j = 3; j >= 0; --j) {
                 const int t = 4 * gg + j;
-                const float av = in_a(t), pv = in_p(t), kv = in_k(t), qv = in_q(t), rv = in_r(t);
+                const float av = in_a(w4, j), pv = in_p(w4, j), kv = tok(w4.k, j), qv = tok(w4.q, j), rv = in_r(w4, j);
                 const float lam_p = j > 0 ? lam_r[j - 1] : lamq;
                 const float Xv = sX[t * LX + nl], Yv = sY[t * LX + nl];
                 const float rho = rho_r[j], ilam = il_r[j], ia = ia_r[j], den = den_r[j];
@@ -606,18 +674,24 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             }
             if constexpr (E == 1) {
                 // G^T <- dY^T Qp + Gs^T
-                const bf16x8 qbh = lds_tr8(sQH, LQ2, 8 * g4, 8 * g4 + 4, 0, l16);
-                const bf16x8 qbl = lds_tr8(sQL, LQ2, 8 * g4, 8 * g4 + 4, 0, l16);
+                const bf16x8 qbh = nt_row8(sQH, l16, g4), qbl = nt_row8(sQL, l16, g4);
+                auto at = [&](int row, int rd) {
+                    return lds_addr(swz<DV>(sDY, row + (l16 >> 2), 16 * rd + 4 * (l16 & 3)));
+                };
+                static_assert(NRD % 2 == 0, "row tiles in pairs");
 #pragma unroll
-                for (int rd = 0; rd < NRD; ++rd) {
-                    const bf16x8 yt = lds_tr8_swz<DV>(sDY, 8 * g4, 8 * g4 + 4, 16 * rd, l16);
-                    GT[rd] = mfma2b(yt, qbh, qbl, GT[rd]);
+                for (int rd = 0; rd < NRD; rd += 2) {
+                    bf16x8 y0, y1;
+                    tr8x2(at(8 * g4, rd), at(8 * g4 + 4, rd), at(8 * g4, rd + 1), at(8 * g4 + 4, rd + 1), y0, y1);
+                    GT[rd] = mfma2b(y0, qbh, qbl, GT[rd]);
+                    GT[rd + 1] = mfma2b(y1, qbh, qbl, GT[rd + 1]);
                 }
             }
-            qs[(gg * 4 + 0) * 16 + nl] = Am;   // the last chunk's summaries were read before two barriers
-            qs[(gg * 4 + 1) * 16 + nl] = Bm;
-            qs[(gg * 4 + 2) * 16 + nl] = Cm;
-            qs[(gg * 4 + 3) * 16 + nl] = Dm;
+            float* qw = qs + (gg * 16 + nl) * 4;   // the last chunk's summaries were read before two barriers
+            qw[0] = Am;
+            qw[1] = Bm;
+            qw[2] = Cm;
+            qw[3] = Dm;
             barrier_lds();   // the group summaries are in
 
             if constexpr (SPLIT) {
@@ -634,12 +708,12 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 float Ac = 1.f, Bc = 0.f, Cc = 0.f, Dc = 0.f;
 #pragma unroll
                 for (int q2 = NG - 1; q2 >= 0; --q2) {
-                    const float A2 = qs[(q2 * 4 + 0) * 16 + nl], B2 = qs[(q2 * 4 + 1) * 16 + nl];
-                    const float C2 = qs[(q2 * 4 + 2) * 16 + nl], D2 = qs[(q2 * 4 + 3) * 16 + nl];
-                    Cc = fmaf(A2, Cc, fmaf(B2, Dc, C2));
-                    Bc = fmaf(A2, Bc, B2);
-                    Ac *= A2;
-                    Dc += D2;
+                    const float* m = qs + (q2 * 16 + nl) * 4;
+                    const float m0 = m[0], m1 = m[1];
+                    Cc = fmaf(m0, Cc, fmaf(m1, Dc, m[2]));
+                    Bc = fmaf(m0, Bc, m1);
+                    Ac *= m0;
+                    Dc += m[3];
                 }
                 const rsrc_t rc = make_rsrc(coef + (row_c0 + c) * 4 * DK, 4 * DK * 4);
                 const uint32_t vo = g4 == 0 ? (uint32_t)(2 * E * DK + n0w + nl) * 4 : 4 * DK * 4;   // other lanes: dropped
@@ -658,16 +732,15 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                     c_in = cT;
                     S_in = ST;
                 }
-                const float A2 = qs[(q2 * 4 + 0) * 16 + nl], B2 = qs[(q2 * 4 + 1) * 16 + nl];
-                const float C2 = qs[(q2 * 4 + 2) * 16 + nl], D2 = qs[(q2 * 4 + 3) * 16 + nl];
-                const float cn = fmaf(A2, cT, fmaf(B2, ST, C2));
-                ST += D2;
+                const float* m = qs + (q2 * 16 + nl) * 4;
+                const float cn = fmaf(m[0], cT, fmaf(m[1], ST, m[2]));
+                ST += m[3];
                 cT = cn;
             }
             ST = S_out;
             // pass 2: gradients of the group's tokens
             uint16_t* so = s_out + pr * 4 * kC * 16;
-            float* drc = s_drc + pr * kC * 17;
+            float dk4[4], da4[4], dp4[4], dr4[4];
             float cc = c_in, SS = S_in;
 #pragma unroll
             for (int j = 3; j >= 0; --j) {
@@ -678,50 +751,55 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                 const float drho = fmaf(gl, lp_[j], SS * den_[j]);
                 const float dav = fmaf(-a2r2_[j], drho, SS * ia_[j]);
                 const float dpv = -lpr2_[j] * drho;
-                drc[t * 17 + nl] = fmaf(kk_[j], gl, kdk_[j]);
+                dr4[j] = fmaf(kk_[j], gl, kdk_[j]);
                 cc = fmaf(al_[j], gl, -be_[j] * SS);
-                const uint32_t pq = cvt_pk_bf16(dq_[j], dkv);
-                so[(0 * kC + t) * 16 + nl] = static_cast<uint16_t>(pq);
-                so[(1 * kC + t) * 16 + nl] = static_cast<uint16_t>(pq >> 16);
+                dk4[j] = dkv;
                 if constexpr (TI) {
                     if (FULL || t < nt) {
                         sum_da += dav;
                         sum_dp += dpv;
                     }
                 } else {
-                    const uint32_t pa = cvt_pk_bf16(dav, dpv);
-                    so[(2 * kC + t) * 16 + nl] = static_cast<uint16_t>(pa);
-                    so[(3 * kC + t) * 16 + nl] = static_cast<uint16_t>(pa >> 16);
+                    da4[j] = dav;
+                    dp4[j] = dpv;
                 }
             }
+            auto put = [&](int x, const float (&v)[4]) {
+                st_b64(so + x * kC * 16 + nt_off(nl, 4 * gg), cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+            };
+            put(0, dq_);
+            put(1, dk4);
+            if constexpr (!TI) {
+                put(2, da4);
+                put(3, dp4);
+            }
 
-            // ---- stores of this wave's 16 tokens: [t][16] rows of dq, dk, dabar, dpbar (lanes
-            // < 32: t = 16 E + lane / 2, 8 slots) and the pair's dr partial over its 16 slots
-            // (lanes < 16: t = 16 E + lane); the other lanes address the end of the range and
+            // ---- stores of this wave's 16 tokens: rows of 16 slots of dq, dk, dabar, dpbar (lanes
+            // < 32: t = 16 E + lane % 16, 8 slots each) and the pair's dr partial over its 16 slots
+            // (lane j < 4 of a group: its token j); the other lanes address the end of the range and
             // are dropped, as are tokens past the sequence end
             {
-                const int tl = 16 * E + ((lane >> 1) & 15);
+                const int hs = 8 * (g4 & 1);
                 const uint32_t kbytes = (uint32_t)((nt - 1) * H * DK + 16) * 2;
                 const size_t ek = (row0 * H + h) * DK + n0w;
-                const uint32_t koff = lane < 32 ? (uint32_t)tl * tok_k + (lane & 1) * 16 : kbytes;
-                const uint16_t* o = so + tl * 16 + (lane & 1) * 8;
-                buf_st128(*reinterpret_cast<const uint4*>(o + 0 * kC * 16),
-                          make_rsrc(static_cast<uint16_t*>(g.dq) + ek, kbytes), koff);
-                buf_st128(*reinterpret_cast<const uint4*>(o + 1 * kC * 16),
-                          make_rsrc(static_cast<uint16_t*>(g.dk) + ek, kbytes), koff);
-                if constexpr (!TI) {
-                    buf_st128(*reinterpret_cast<const uint4*>(o + 2 * kC * 16),
-                              make_rsrc(static_cast<uint16_t*>(g.da) + ek, kbytes), koff);
-                    buf_st128(*reinterpret_cast<const uint4*>(o + 3 * kC * 16),
-                              make_rsrc(static_cast<uint16_t*>(g.dp) + ek, kbytes), koff);
-                }
-                const int t = 16 * E + l16;
-                float acc = 0.f;
+                const uint32_t koff = lane < 32 ? (uint32_t)(16 * E + l16) * tok_k + hs * 2 : kbytes;
+                const uint32_t oa = lds_addr(so + nt_off(hs + (l16 >> 2), 16 * E + 4 * (l16 & 3)));
+                const uint32_t ob = lds_addr(so + nt_off(hs + 4 + (l16 >> 2), 16 * E + 4 * (l16 & 3)));
+                constexpr uint32_t TB = kC * 16 * 2;   // bytes of one gradient tile
+                auto store2 = [&](int x, void* d0, void* d1) {
+                    bf16x8 v0, v1;
+                    tr8x2(oa + x * TB, ob + x * TB, oa + (x + 1) * TB, ob + (x + 1) * TB, v0, v1);
+                    buf_st128(__builtin_bit_cast(uint4, v0), make_rsrc(static_cast<uint16_t*>(d0) + ek, kbytes), koff);
+                    buf_st128(__builtin_bit_cast(uint4, v1), make_rsrc(static_cast<uint16_t*>(d1) + ek, kbytes), koff);
+                };
+                store2(0, g.dq, g.dk);
+                if constexpr (!TI) store2(2, g.da, g.dp);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc += drc[t * 17 + i];
+                for (int j = 0; j < 4; ++j) dr4[j] = row_sum16f(dr4[j]);
+                const float acc = nl & 2 ? (nl & 1 ? dr4[3] : dr4[2]) : (nl & 1 ? dr4[1] : dr4[0]);
                 float* dst = dr_part + (size_t)(ntile * NP + pr) * nbt + row0 * H + h;
                 const uint32_t dbytes = (uint32_t)((nt - 1) * H + 1) * 4;
-                buf_st32(acc, make_rsrc(dst, dbytes), lane < 16 ? (uint32_t)t * H * 4 : dbytes);
+                buf_st32(acc, make_rsrc(dst, dbytes), nl < 4 ? (uint32_t)(4 * gg + nl) * H * 4 : dbytes);
             }
         };
         if (e == 0) {

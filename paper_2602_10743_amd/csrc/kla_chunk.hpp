@@ -72,6 +72,12 @@ __device__ __forceinline__ bf16x8 nt_tr8(const uint16_t* X, int rowA, int rowB, 
     return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// lane s (of 16) receives X(row + j, t0 + s), j = 0..3, two per word; row a multiple of 4, t0 of 16
+__device__ __forceinline__ uint2 nt_tr4(const uint16_t* X, int row, int t0, int s) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                                         (lds_bf16x4_t*)(X + nt_off(row + (s >> 2), t0 + 4 * (s & 3)))));
+}
+
 // tokens 8 c .. 8 c + 7 of slot n
 __device__ __forceinline__ bf16x8 nt_row8(const uint16_t* X, int n, int c) { return lds8(X + nt_off(n, 8 * c)); }
 
