@@ -7,7 +7,7 @@
 //   gate:  out = y * silu(z)
 //
 // All are bound by HBM: every thread moves 16-byte vectors (8 bf16 or 4 fp32
-// elements) along the contiguous dimension.  Reductions over tokens or rows
+// elements; the conv backward 4 of either) along the contiguous dimension.  Reductions over tokens or rows
 // (the weight gradients) go through per-block parts that a second kernel adds
 // in a fixed order, so results are bitwise reproducible.
 #include "kla_device.hpp"
@@ -55,9 +55,27 @@ struct Vec<f32_t> {
     }
 };
 
+// 8-byte vectors of bf16 (the conv backward: see there)
+struct bf16x4_s {};
+template <>
+struct Vec<bf16x4_s> {
+    static constexpr int N = 4;
+    __device__ static void load(const void* p, size_t i, float* f) {
+        const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p) + i);
+        f[0] = __uint_as_float(u.x << 16);
+        f[1] = __uint_as_float(u.x & 0xffff0000u);
+        f[2] = __uint_as_float(u.y << 16);
+        f[3] = __uint_as_float(u.y & 0xffff0000u);
+    }
+    __device__ static void store(void* p, size_t i, const float* f) {
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p) + i) =
+            make_uint2(cvt_pk_bf16(f[0], f[1]), cvt_pk_bf16(f[2], f[3]));
+    }
+};
+
 __device__ __forceinline__ float sigm(float x) { return __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
 
-// Conv threads: a block is 64 channel groups (16-byte vectors) x kSub token
+// Conv threads: a block is 64 channel groups (one vector each) x kSub token
 // runs of kTT tokens; the backward adds its weight-gradient partials over the
 // kSub runs in LDS before writing one part per block.
 constexpr int kTT = 16;   // tokens per conv thread
@@ -163,6 +181,12 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(int B, int T, int C, cons
 // token from the recomputed pre-activation, dx[t] = sum_j w[j] ds[t+3-j], and
 // the weight / bias gradient of the thread's own tokens, added over the
 // block's token runs into part (b, token block).
+//
+// Four channels per thread in both types: the gradients, taps and windows of eight bf16 channels
+// held 204 registers and 40 KB of LDS per block, two waves per SIMD, too few to cover the loads
+// (79 us at 8 x 2048 tokens of 2048 channels, bytes 39 us at the copy rate); four hold 98, four
+// waves per SIMD, 66 us.  Runs of 32 tokens (fewer halo tokens) gain 1% there and halve the
+// blocks of a short batch.
 template <typename S>
 __global__ __launch_bounds__(256) void conv_bwd_kernel(int B, int T, int C, const void* __restrict__ x,
                                                        const float* __restrict__ w, const float* __restrict__ bias,
@@ -304,20 +328,34 @@ __global__ __launch_bounds__(256) void conv_bwd_kernel(int B, int T, int C, cons
     }
 }
 
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(int nparts, int C, const float* __restrict__ part,
-                                                         float* __restrict__ dw, float* __restrict__ dbias) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;   // c * 5 + j
-    if (i >= C * 5) return;
+// A block sums 64 elements (c, j), a wave each quarter of the parts: with one thread per element
+// 2048 channels were 40 blocks of one serial chain (13.4 us at 8 x 2048 tokens; 5.8 us so).
+constexpr int kWG = 4;   // part groups per block
+
+__global__ __launch_bounds__(64 * kWG) void conv_wgrad_kernel(int nparts, int C, const float* __restrict__ part,
+                                                              float* __restrict__ dw, float* __restrict__ dbias) {
+    __shared__ float s_acc[kWG][64];
+    const int el = threadIdx.x % 64, q = threadIdx.x / 64;
+    const int i = blockIdx.x * 64 + el;   // c * 5 + j
+    const bool live = i < C * 5;
     // eight interleaved partial sums keep eight loads in flight; added in a fixed order
     float a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int p = 0;
-    for (; p + 8 <= nparts; p += 8)
+    const int per = (nparts + kWG - 1) / kWG, p1 = min(nparts, (q + 1) * per);
+    int p = q * per;
+    if (live) {
+        for (; p + 8 <= p1; p += 8)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a8[u] += part[(size_t)(p + u) * C * 5 + i];
+            for (int u = 0; u < 8; ++u) a8[u] += part[(size_t)(p + u) * C * 5 + i];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-        if (p + u < nparts) a8[u] += part[(size_t)(p + u) * C * 5 + i];
-    const float acc = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
+        for (int u = 0; u < 8; ++u)
+            if (p + u < p1) a8[u] += part[(size_t)(p + u) * C * 5 + i];
+    }
+    s_acc[q][el] = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
+    __syncthreads();
+    if (q != 0 || !live) return;
+    float acc = 0.f;
+#pragma unroll
+    for (int u = 0; u < kWG; ++u) acc += s_acc[u][el];
     const int c = i / 5, j = i % 5;
     if (j < 4)
         dw[c * 4 + j] = acc;
@@ -493,16 +531,16 @@ hipError_t launch_conv_fwd(int B, int T, int C, bool bf16, const void* x, const 
 hipError_t launch_conv_bwd(int B, int T, int C, bool bf16, const void* x, const float* w, const float* bias,
                            const void* du, void* dx, float* dw, float* dbias, float* part, hipStream_t st) {
     const int ntb = (T + kTB - 1) / kTB;
-    const unsigned nb = conv_blocks(B, T, C, block_vec(bf16));
+    const unsigned nb = conv_blocks(B, T, C, 4);
     if (nb > 0) {
         if (bf16)
-            hipLaunchKernelGGL(conv_bwd_kernel<bf16_t>, dim3(nb), dim3(256), 0, st, B, T, C, x, w, bias, du, dx, part);
+            hipLaunchKernelGGL(conv_bwd_kernel<bf16x4_s>, dim3(nb), dim3(256), 0, st, B, T, C, x, w, bias, du, dx, part);
         else
             hipLaunchKernelGGL(conv_bwd_kernel<f32_t>, dim3(nb), dim3(256), 0, st, B, T, C, x, w, bias, du, dx, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(conv_wgrad_kernel, dim3(blocks_for((size_t)C * 5)), dim3(256), 0, st, B * ntb, C, part, dw,
+    hipLaunchKernelGGL(conv_wgrad_kernel, dim3((unsigned)(((size_t)C * 5 + 63) / 64)), dim3(64 * kWG), 0, st, B * ntb, C, part, dw,
                        dbias);
     return hipGetLastError();
 }
