@@ -115,7 +115,11 @@ size_t kla_forward_workspace(const kla_desc* desc);
 size_t kla_saved_bytes(const kla_desc* desc);
 
 /* Bytes of device workspace kla_backward needs when it is given a saved
- * context (`with_saved` != 0) or must recompute one (`with_saved` == 0). */
+ * context (`with_saved` != 0) or must recompute one (`with_saved` == 0).  With a
+ * context: at most 256 MiB (bf16, few sequences: segments side by side, in
+ * windows) or 192 MiB (fp32, chunks side by side, in windows), or, where that is
+ * more, what the walk of whole sequences needs per token (bf16: dk / 16 floats
+ * per token and head; fp32 at widths of 64 or 128: dk doubles). */
 size_t kla_backward_workspace(const kla_desc* desc, int with_saved);
 
 /*
@@ -176,8 +180,11 @@ kla_status kla_backward(const kla_desc* desc,
  *   Returns KLA_ERR_WORKSPACE when the shape cannot work in
  *   KLA_NOALLOC_SCRATCH_BYTES (64 MiB: the LM-layer shape B8 T2048 H16 d128 bf16
  *   needs 8 MiB, the state-tracking shape B64 T512 H4 d32 fp32 256 bytes).  The
- *   chunk-parallel fp32 backward, whose kla_backward_workspace(desc, 1) is up to
- *   192 MiB, takes the sequence in smaller windows here.
+ *   segment-parallel bf16 and chunk-parallel fp32 backwards, whose
+ *   kla_backward_workspace(desc, 1) is up to 256 and 192 MiB, take the sequence
+ *   in smaller windows here, with the same results bit for bit; bf16 shapes whose
+ *   segments would be slower so take the walk of whole sequences instead, which
+ *   rounds differently.
  *   Calls that overlap on one GPU share its workspace and race: order them on one
  *   stream.  With KLA_CHECK=1 the call synchronises, which graph capture forbids.
  */

@@ -63,6 +63,7 @@
 // and pbar are formed once per lane and not loaded; dabar and dpbar are not
 // stored per token but summed over the lane's tokens, one part per (batch row,
 // wave of the pair), for the parameter gradients.
+#include <algorithm>
 #include <type_traits>
 
 #include "kla_chunk.hpp"
@@ -179,8 +180,9 @@ __device__ __forceinline__ void buf_st32(float v, rsrc_t r, uint32_t voff) {
 
 // SPLIT (segments of few sequences, which run side by side): the precision adjoint c that a
 // segment starts from is not known yet, so phase 5 is left to bwd_grad_kernel: dqt and dkh go
-// to xy [B H][chunk][2][kC][dk] and the chunk's composed adjoint step, with the exact change
-// of S, to coef [B H][chunk][4][dk].  gend: the adjoints of the segments' last states.
+// to xy [B H][window's chunk][2][kC][dk] and the chunk's composed adjoint step, with the exact
+// change of S, to coef [B H][window's chunk][4][dk].  gend [B H][run]: the adjoints of the last
+// states of the segments run.
 template <int DK, int DV, bool TI, bool YG, bool SPLIT>
 __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, Seg sg, BwdArgs g,
                                                                        const float* __restrict__ saved_lam,
@@ -206,8 +208,8 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     const uint16_t* dy = static_cast<const uint16_t*>(g.dy);
 
     int vi, ntile;
-    xcd_tile_map(blockIdx.x, s.B * s.H * sg.ns, Cfg::NNT, vi, ntile);
-    const int bh = vi / sg.ns, seg = vi % sg.ns;
+    xcd_tile_map(blockIdx.x, s.B * s.H * sg.run, Cfg::NNT, vi, ntile);
+    const int bh = vi / sg.run, seg = sg.first + vi % sg.run;
     const int b = bh / s.H, h = bh % s.H;
     const int c0 = seg * sg.lc, nct = (s.T + kC - 1) / kC;   // this segment's first chunk, the sequence's chunks
     const int H = s.H, T = min(s.T - c0 * kC, sg.lc * kC);
@@ -219,7 +221,9 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
     const int n0w = ntile * Cfg::NTN + 16 * pr;  // the pair's first key slot
     const int nchunk = (T + kC - 1) / kC;
     const size_t seq0 = (size_t)b * s.T + (size_t)c0 * kC;
-    const size_t row_c0 = (size_t)bh * nct + c0;       // the first chunk's row of the per-chunk arrays
+    const size_t row_c0 = (size_t)bh * nct + c0;       // the first chunk's row of the saved walk states
+    // and of the window's work arrays
+    const size_t win_c0 = (size_t)bh * min(sg.run * sg.lc, nct - sg.first * sg.lc) + (c0 - sg.first * sg.lc);
     const size_t slot_c0 = (size_t)bh * (nct + 1) + c0;   // and its slot of the saved states
     const size_t nbt = (size_t)s.B * s.T * H;
     unsigned char* wb = smem + Cfg::PAIR0 + pr * Cfg::PAIR;
@@ -697,7 +701,7 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
             if constexpr (SPLIT) {
                 // dqt, dkh of the lane's tokens, and the chunk's composed step: A, B from wave 0, C and
                 // the change of S from wave 1
-                float* xo = xy + (row_c0 + c) * 2 * kC * DK;
+                float* xo = xy + (win_c0 + c) * 2 * kC * DK;
                 const rsrc_t rx = make_rsrc(xo, 2 * kC * DK * 4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -715,7 +719,7 @@ __global__ __launch_bounds__((DkCfg<DK, DV>::NTHR)) void bwd_dk_kernel(Shape s, 
                     Ac *= m0;
                     Dc += m[3];
                 }
-                const rsrc_t rc = make_rsrc(coef + (row_c0 + c) * 4 * DK, 4 * DK * 4);
+                const rsrc_t rc = make_rsrc(coef + (win_c0 + c) * 4 * DK, 4 * DK * 4);
                 const uint32_t vo = g4 == 0 ? (uint32_t)(2 * E * DK + n0w + nl) * 4 : 4 * DK * 4;   // other lanes: dropped
                 buf_st32s(E == 0 ? Ac : Cc, rc, vo, 0);
                 buf_st32s(E == 0 ? Bc : sWT[nl] - sWT[16 + nl], rc, vo, DK * 4);
@@ -851,7 +855,7 @@ hipError_t launch_dk(const Shape& s, const BwdArgs& a, const float* saved_lam, c
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
     if (attr != hipSuccess) return attr;
     const int nct = (s.T + kC - 1) / kC;
-    hipError_t e = launch_backward_dv(s, 1, nct, false, a, saved_lam, nullptr, nullptr, st);
+    hipError_t e = launch_backward_dv(s, 1, nct, 0, 1, false, a, saved_lam, nullptr, nullptr, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(s.B * s.H * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s, Seg{1, nct, 1},
                        a, saved_lam, saved_H, dr_part, nullptr, nullptr, nullptr);
@@ -867,87 +871,158 @@ hipError_t launch_dk(const Shape& s, const BwdArgs& a, const float* saved_lam, c
 }
 
 // ---- the segment-parallel backward of few sequences
+// A window of segments (all of them where their buffers fit), last window first:
 //   1. every segment's but the first's own contribution to the adjoint of the state before it
 //      (bwd_dv_kernel without dV), 2. their scan to the adjoint of every segment's last state,
-//   3. dV and, in 4., the contractions of the key side over all segments at once (SPLIT),
+//   3. dV and, in 4., the contractions of the key side over the window's segments at once (SPLIT),
 //   5. a scan of the chunks' adjoint steps for (c, S) at the chunk ends, 6. the gradients.
+// The adjoints of the state and of lam, S and the OU sums are carried from window to window as
+// the scans hold them, so the windows do not show in the results.
 struct BwdCut {
-    int ns, lc;
+    int ns, lc;   // segments of lc chunks
+    int w;        // segments per window
 };
+
+// What the segments may use of device memory however long the sequences: 280 bytes per chunk, head
+// and key slot for the chunks of a window, 4 (dv + 1) per segment, head and slot.
+constexpr size_t kSegWork = 256u << 20;
+
+size_t pad256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+// Buffers of a window of w segments of lc chunks, and the carries between windows.
+struct SegBufs {
+    float *gend, *pseg, *xy, *coef, *ous, *cg;
+    double* ccs;
+    size_t bytes;
+    SegBufs(const Shape& s, int w, int lc, void* ws) {
+        const size_t nbh = (size_t)s.B * s.H, nc = (size_t)w * lc;
+        char *p = static_cast<char*>(ws), *p0 = p;
+        auto carve = [&](size_t bytes_) {
+            char* r = p;
+            p += pad256(bytes_);
+            return r;
+        };
+        gend = reinterpret_cast<float*>(carve(nbh * w * s.dk * s.dv * sizeof(float)));
+        pseg = reinterpret_cast<float*>(carve(nbh * w * s.dk * sizeof(float)));
+        xy = reinterpret_cast<float*>(carve(nbh * nc * 2 * kC * s.dk * sizeof(float)));
+        coef = reinterpret_cast<float*>(carve(nbh * nc * 4 * s.dk * sizeof(float)));
+        ous = reinterpret_cast<float*>(carve(nbh * nc * 2 * s.dk * sizeof(float)));
+        cg = reinterpret_cast<float*>(carve(nbh * s.dk * s.dv * sizeof(float)));
+        ccs = reinterpret_cast<double*>(carve(nbh * 2 * s.dk * sizeof(double)));
+        bytes = p - p0;
+    }
+};
+size_t seg_bytes(const Shape& s, int w, int lc) { return SegBufs(s, w, lc, nullptr).bytes; }
 
 // Microseconds per chunk round at 128 x 128: value side 3.3 (3.8 wide), its state-only pass 2.0,
 // key side 7.4 (SPLIT 6.6); the gradient kernel 1.1 ns per token and head; the other kernels and
-// launches 40.  One workgroup per CU, as in the forward.
-BwdCut bwd_cut(const Shape& s) {
+// launches of a window 40.  One workgroup per CU, as in the forward.  ns and lc do not depend on
+// limit (bytes the windows may use), so that the results do not; under a limit that cuts the
+// windows too short to fill the chip the whole walk may be left as the faster one.
+BwdCut bwd_cut(const Shape& s, size_t limit) {
     const int nct = (s.T + kC - 1) / kC, bh = s.B * s.H, nnt = s.dk / 64 > 0 ? s.dk / 64 : 1, ntile = s.dv == 128 ? 2 : 1;
-    BwdCut c{1, nct};
-    if (nct < 4) return c;
+    const BwdCut whole{1, nct, 1};
+    if (nct < 4) return whole;
     auto rounds = [](int wg) { return (wg + 255) / 256; };
     auto dv_us = [&](int ns) { return chunked_wide(s, ns) ? 3.8 * rounds(bh * ns) : 3.3 * rounds(bh * ns * ntile); };
-    double best = 0.92 * nct * (dv_us(1) + 7.4 * rounds(bh * nnt));
+    auto cost = [&](const BwdCut& c) {
+        const int full = c.ns / c.w, rest = c.ns % c.w;
+        auto window = [&](int w) { return c.lc * (2.0 + dv_us(w) + 6.6 * rounds(bh * w * nnt)) + 40.0; };
+        return full * window(c.w) + (rest ? window(rest) : 0.0) + 1.1e-3 * bh * s.T * s.dk / 128;
+    };
+    const double walk = 0.92 * nct * (dv_us(1) + 7.4 * rounds(bh * nnt));
+    double best = walk;
+    BwdCut cut = whole;
     for (int wg : {256 / (bh * ntile), 256 / (bh * nnt), 256 / bh}) {
         if (wg < 2) continue;
-        const int lc = (nct + wg - 1) / wg, ns = (nct + lc - 1) / lc;
+        // as many windows of wg segments as the bound asks for, in equal parts
+        const size_t seg = seg_bytes(s, wg, 0), chunk = (size_t)bh * wg * s.dk * (2 * kC + 6) * sizeof(float);
+        if (seg + chunk > kSegWork) continue;
+        const int most = (int)std::min<size_t>((kSegWork - seg) / chunk, nct);
+        const int nw = ((nct + wg - 1) / wg + most - 1) / most;
+        const int lc = (nct + wg * nw - 1) / (wg * nw), ns = (nct + lc - 1) / lc;
         if (ns < 2) continue;
-        const double cost = lc * (2.0 + dv_us(ns) + 6.6 * rounds(bh * ns * nnt)) + 40.0 + 1.1e-3 * bh * s.T * s.dk / 128;
-        if (cost < best) {
-            best = cost;
-            c = BwdCut{ns, lc};
+        const BwdCut c{ns, lc, std::min(ns, wg)};
+        const double t = cost(c);
+        if (t < best) {
+            best = t;
+            cut = c;
         }
     }
-    return c;
+    if (cut.ns > 1 && seg_bytes(s, cut.w, cut.lc) > limit) {
+        int w = cut.w - 1;
+        while (w > 0 && seg_bytes(s, w, cut.lc) > limit) --w;
+        if (w == 0) return whole;
+        const int nw = (cut.ns + w - 1) / w;
+        cut.w = (cut.ns + nw - 1) / nw;
+        if (cost(cut) > walk) return whole;
+    }
+    return cut;
 }
 
-// Per element: the adjoint of every segment's last state, in place of the segments' own
-// contributions (slots 1 .. ns - 1 of g), from detaT.
-__global__ __launch_bounds__(256) void bwd_state_scan_kernel(int nbh, int DK, int DV, int ns,
+// Per element: the adjoint of the last state of every segment of a window (its w segments from s0
+// on), in place of the segments' own contributions, from detaT (last window) or carry; carry
+// receives the adjoint of the state before the window.
+__global__ __launch_bounds__(256) void bwd_state_scan_kernel(int nbh, int DK, int DV, int s0, int w, bool last,
                                                              const float* __restrict__ pseg,
-                                                             const float* __restrict__ detaT, float* __restrict__ g) {
+                                                             const float* __restrict__ detaT, float* __restrict__ g,
+                                                             float* __restrict__ carry) {
     const size_t per = (size_t)DK * DV, i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)nbh * per) return;
     const size_t e = i % per, bh = i / per;
     const int n = (int)(e / DV);
-    float x = detaT ? detaT[i] : 0.f;
-    float* o = g + bh * ns * per + e;
-    const float* pn = pseg + bh * ns * DK + n;
+    float x = !last ? carry[i] : detaT ? detaT[i] : 0.f;
+    float* o = g + bh * w * per + e;
+    const float* pn = pseg + bh * w * DK + n;
+    const int lo = s0 > 0 ? 0 : min(1, w - 1);   // the sequence's first segment has no contribution
     constexpr int U = 8;
-    for (int s0 = ns - 1; s0 >= 0; s0 -= U) {
+    for (int j0 = w - 1; j0 >= 0; j0 -= U) {
         float u[U], p[U];
 #pragma unroll
         for (int m = 0; m < U; ++m) {
-            const int sgi = max(s0 - m, 1);
-            u[m] = o[(size_t)sgi * per];
-            p[m] = pn[(size_t)sgi * DK];
+            const int j = max(j0 - m, lo);
+            u[m] = o[(size_t)j * per];
+            p[m] = pn[(size_t)j * DK];
         }
 #pragma unroll
         for (int m = 0; m < U; ++m)
-            if (s0 - m >= 0) {
-                o[(size_t)(s0 - m) * per] = x;
+            if (j0 - m >= 0) {
+                o[(size_t)(j0 - m) * per] = x;
                 x = fmaf(p[m], x, u[m]);
             }
     }
+    if (s0 > 0) carry[i] = x;
 }
 
-// (c, S) at the end of every chunk, into rows 0 and 1 of its coef, carried in fp64 along the
-// sequence; from dlamT and sum_d detaT H_T.  One thread per (b, h, slot); the steps of U
+// (c, S) at the end of every chunk of a window, into rows 0 and 1 of its coef, carried in fp64
+// along the sequence; from dlamT and sum_d detaT H_T (hT: the final states, hseq floats apart) in
+// the last window, else from carry [B H][2][dk].  One thread per (b, h, slot); the steps of U
 // chunks are loaded while those of the U after are applied.
-__global__ __launch_bounds__(64) void bwd_carry_kernel(int nbh, int DK, int DV, int nct, float* __restrict__ coef,
-                                                       const float* __restrict__ saved_H,
+__global__ __launch_bounds__(64) void bwd_carry_kernel(int nbh, int DK, int DV, int nc, bool last,
+                                                       float* __restrict__ coef, double* __restrict__ carry,
+                                                       const float* __restrict__ hT, size_t hseq,
                                                        const float* __restrict__ dlamT,
                                                        const float* __restrict__ detaT, float* __restrict__ dlam0) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nbh * DK) return;
     const int n = i % DK, bh = i / DK;
-    double c = dlamT ? (double)dlamT[i] : 0.0, S = 0.0;
-    if (detaT) {
-        const float* hT = saved_H + (((size_t)bh * (nct + 1) + nct) * DK + n) * DV;
-        const float* d = detaT + (size_t)i * DV;
-        for (int m = 0; m < DV; m += 4) {
-            const float4 x = *reinterpret_cast<const float4*>(hT + m), y = *reinterpret_cast<const float4*>(d + m);
-            S += (double)x.x * y.x + (double)x.y * y.y + (double)x.z * y.z + (double)x.w * y.w;
+    double* cr = carry + (size_t)bh * 2 * DK + n;
+    double c = 0.0, S = 0.0;
+    if (!last) {
+        c = cr[0];
+        S = cr[DK];
+    } else {
+        if (dlamT) c = (double)dlamT[i];
+        if (detaT) {
+            const float* h = hT + (size_t)bh * hseq + (size_t)n * DV;
+            const float* d = detaT + (size_t)i * DV;
+            for (int m = 0; m < DV; m += 4) {
+                const float4 x = *reinterpret_cast<const float4*>(h + m), y = *reinterpret_cast<const float4*>(d + m);
+                S += (double)x.x * y.x + (double)x.y * y.y + (double)x.z * y.z + (double)x.w * y.w;
+            }
         }
     }
-    float* cf = coef + (size_t)bh * nct * 4 * DK + n;
+    float* cf = coef + (size_t)bh * nc * 4 * DK + n;
     constexpr int U = 8;
     float b[U][4], nx[U][4];
     auto load = [&](float (&d)[U][4], int j0) {
@@ -956,8 +1031,8 @@ __global__ __launch_bounds__(64) void bwd_carry_kernel(int nbh, int DK, int DV, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) d[u][r] = cf[((size_t)max(j0 - u, 0) * 4 + r) * DK];
     };
-    load(nx, nct - 1);
-    for (int j0 = nct - 1; j0 >= 0; j0 -= U) {
+    load(nx, nc - 1);
+    for (int j0 = nc - 1; j0 >= 0; j0 -= U) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -973,24 +1048,28 @@ __global__ __launch_bounds__(64) void bwd_carry_kernel(int nbh, int DK, int DV, 
                 S += b[u][3];
             }
     }
+    cr[0] = c;
+    cr[DK] = S;
     if (dlam0) dlam0[i] = (float)c;
 }
 
 // The gradients of one chunk's tokens from dqt, dkh and (c, S) at its end: phases 1, 2, 4 and 5
 // of bwd_dk_kernel for lanes = (slot, group of 8 tokens), one workgroup per (b, h, chunk), so
-// dr is complete here.  HBM bound: 24 bytes per (token, slot) with per-token gates.
-// TI: the chunk's sums of the gate gradients go to ous [B H][chunk][2][dk].
+// dr is complete here.  HBM bound: 24 bytes per (token, slot) with per-token gates.  The
+// window's nc chunks from c0 on; xy, coef and ous as in bwd_dk_kernel.
+// TI: the chunk's sums of the gate gradients go to ous [B H][window's chunk][2][dk].
 template <int DK, bool TI, bool YG>
-__global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, BwdArgs g, const float* __restrict__ saved_lam,
+__global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, int c0, int nc, BwdArgs g,
+                                                          const float* __restrict__ saved_lam,
                                                           const float* __restrict__ xy,
                                                           const float* __restrict__ coef, float* __restrict__ ous) {
     constexpr int NG = 4, TPG = 8, NT = NG * DK;
     __shared__ float qs[NG][4][DK];
     __shared__ float sR[kC][DK + 1];
-    const int nct = (s.T + kC - 1) / kC, c = blockIdx.x % nct, bh = blockIdx.x / nct;
+    const int nct = (s.T + kC - 1) / kC, c = c0 + blockIdx.x % nc, bh = blockIdx.x / nc;
     const int H = s.H, b = bh / H, h = bh % H, tid = threadIdx.x, n = tid % DK, gq = tid / DK;
     const int nt = min(kC, s.T - c * kC);
-    const size_t tok0 = (size_t)b * s.T + (size_t)c * kC, row = (size_t)bh * nct + c;
+    const size_t tok0 = (size_t)b * s.T + (size_t)c * kC, row = blockIdx.x;   // row of xy, coef, ous
     const size_t k0 = (tok0 * H + h) * DK;
     const uint32_t kbytes = (uint32_t)((nt - 1) * H * DK + DK) * 2;
     const rsrc_t rk = make_rsrc(static_cast<const uint16_t*>(g.k) + k0, kbytes);
@@ -1018,7 +1097,7 @@ __global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, BwdArgs g, co
         dqt[j] = xo[t * DK + n];
         dkh[j] = xo[(kC + t) * DK + n];
     }
-    const float* lw = saved_lam + row * kLamRows * DK + n;
+    const float* lw = saved_lam + ((size_t)bh * nct + c) * kLamRows * DK + n;
     const bool half = gq >= 2;
     float x = half ? lw[DK] : lw[0], z = 1.f;
     float cc = coef[row * 4 * DK + n], SS = coef[(row * 4 + 1) * DK + n];
@@ -1141,21 +1220,19 @@ __global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, BwdArgs g, co
         if (gq < 2) ous[(row * 2 + gq) * DK + n] = (qs[0][gq][n] + qs[1][gq][n]) + (qs[2][gq][n] + qs[3][gq][n]);
 }
 
-// The two OU parts of a batch row (chunked_ou_parts): the chunk sums of its even and odd chunks.
-__global__ __launch_bounds__(64) void bwd_ou_kernel(int nbh, int H, int B, int DK, int nct,
+// The two OU parts of a batch row (chunked_ou_parts): the chunk sums of its even and odd chunks,
+// later chunks first, those of a window (chunks c0 .. c0 + nc - 1) added to what the later windows left.
+__global__ __launch_bounds__(64) void bwd_ou_kernel(int nbh, int H, int B, int DK, int c0, int nc, bool last,
                                                     const float* __restrict__ ous, float* __restrict__ part) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nbh * 4 * DK) return;
     const int n = i % DK, q = i / DK % 2, par = i / (2 * DK) % 2, bh = i / (4 * DK), b = bh / H, h = bh % H;
-    float acc = 0.f;
+    float* o = part + (size_t)q * 2 * nbh * DK + ((size_t)(par * B + b) * H + h) * DK + n;
+    float acc = last ? 0.f : *o;
+    const int j1 = nc - 1 - ((c0 + nc - 1 - par) & 1);   // the window's last chunk of this parity
 #pragma unroll 8
-    for (int c = par; c < nct; c += 2) acc += ous[(((size_t)bh * nct + c) * 2 + q) * DK + n];
-    part[(size_t)q * 2 * nbh * DK + ((size_t)(par * B + b) * H + h) * DK + n] = acc;
-}
-
-size_t seg_bytes(const Shape& s, const BwdCut& c) {
-    const size_t nbh = (size_t)s.B * s.H, nct = (s.T + kC - 1) / kC, f = sizeof(float);
-    return nbh * c.ns * s.dk * (s.dv + 1) * f + nbh * nct * s.dk * (2 * kC + 4 + 2) * f + 5 * 256;
+    for (int j = j1; j >= 0; j -= 2) acc += ous[(((size_t)bh * nc + j) * 2 + q) * DK + n];
+    *o = acc;
 }
 
 template <int DK, int DV, bool TI, bool YG>
@@ -1167,38 +1244,39 @@ hipError_t launch_seg(const Shape& s, const BwdCut& cut, const BwdArgs& a, const
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
     if (attr != hipSuccess) return attr;
     const int nbh = s.B * s.H, nct = (s.T + kC - 1) / kC;
-    auto carve = [&](size_t count) {
-        float* p = static_cast<float*>(ws);
-        ws = static_cast<char*>(ws) + (count * sizeof(float) + 255) / 256 * 256;
-        return p;
-    };
-    float* gend = carve((size_t)nbh * cut.ns * DK * DV);
-    float* pseg = carve((size_t)nbh * cut.ns * DK);
-    float* xy = carve((size_t)nbh * nct * 2 * kC * DK);
-    float* coef = carve((size_t)nbh * nct * 4 * DK);
-    float* ous = carve((size_t)nbh * nct * 2 * DK);
-    hipError_t e = launch_backward_dv(s, cut.ns, cut.lc, true, a, saved_lam, gend, pseg, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bwd_state_scan_kernel, dim3((unsigned)(((size_t)nbh * DK * DV + 255) / 256)), dim3(256), 0, st,
-                       nbh, DK, DV, cut.ns, pseg, a.detaT, gend);
-    if ((e = launch_backward_dv(s, cut.ns, cut.lc, false, a, saved_lam, gend, pseg, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(nbh * cut.ns * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s,
-                       Seg{cut.ns, cut.lc, cut.ns}, a, saved_lam, saved_H, nullptr, gend, xy, coef);
-    hipLaunchKernelGGL(bwd_carry_kernel, dim3((unsigned)((nbh * DK + 63) / 64)), dim3(64), 0, st, nbh, DK, DV, nct, coef,
-                       saved_H, a.dlamT, a.detaT, a.dlam0);
-    hipLaunchKernelGGL((bwd_grad_kernel<DK, TI, YG>), dim3((unsigned)(nbh * nct)), dim3(4 * DK), 0, st, s, a, saved_lam,
-                       xy, coef, ous);
-    if (TI)
-        hipLaunchKernelGGL(bwd_ou_kernel, dim3((unsigned)((nbh * 4 * DK + 63) / 64)), dim3(64), 0, st, nbh, s.H, s.B, DK,
-                           nct, ous, static_cast<float*>(a.ou_part));
-    return hipGetLastError();
+    const SegBufs f(s, cut.w, cut.lc, ws);
+    const size_t hseq = (size_t)(nct + 1) * DK * DV;
+    hipError_t e;
+    for (int s1 = cut.ns; s1 > 0; s1 -= cut.w) {   // the window's segments s0 .. s1 - 1
+        const int s0 = std::max(s1 - cut.w, 0), w = s1 - s0;
+        const int c0 = s0 * cut.lc, nc = std::min(w * cut.lc, nct - c0);
+        const bool last = s1 == cut.ns;
+        if (s1 > 1 && (e = launch_backward_dv(s, cut.ns, cut.lc, s0, w, true, a, saved_lam, f.gend, f.pseg, st)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(bwd_state_scan_kernel, dim3((unsigned)(((size_t)nbh * DK * DV + 255) / 256)), dim3(256), 0, st,
+                           nbh, DK, DV, s0, w, last, f.pseg, a.detaT, f.gend, f.cg);
+        if ((e = launch_backward_dv(s, cut.ns, cut.lc, s0, w, false, a, saved_lam, f.gend, f.pseg, st)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(nbh * w * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s,
+                           Seg{cut.ns, cut.lc, w, s0}, a, saved_lam, saved_H, nullptr, f.gend, f.xy, f.coef);
+        hipLaunchKernelGGL(bwd_carry_kernel, dim3((unsigned)((nbh * DK + 63) / 64)), dim3(64), 0, st, nbh, DK, DV, nc, last,
+                           f.coef, f.ccs, saved_H + (size_t)nct * DK * DV, hseq, a.dlamT, a.detaT,
+                           s0 == 0 ? a.dlam0 : nullptr);
+        hipLaunchKernelGGL((bwd_grad_kernel<DK, TI, YG>), dim3((unsigned)(nbh * nc)), dim3(4 * DK), 0, st, s, c0, nc, a,
+                           saved_lam, f.xy, f.coef, f.ous);
+        if (TI)
+            hipLaunchKernelGGL(bwd_ou_kernel, dim3((unsigned)((nbh * 4 * DK + 63) / 64)), dim3(64), 0, st, nbh, s.H, s.B,
+                               DK, c0, nc, last, f.ous, static_cast<float*>(a.ou_part));
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int DK, int DV, bool TI, bool YG>
 hipError_t launch_either(const Shape& s, const BwdArgs& a, const float* saved_lam, const float* saved_H, void* ws,
                          size_t limit, hipStream_t st) {
-    const BwdCut cut = bwd_cut(s);
-    if (cut.ns > 1 && seg_bytes(s, cut) <= limit) return launch_seg<DK, DV, TI, YG>(s, cut, a, saved_lam, saved_H, ws, st);
+    const BwdCut cut = bwd_cut(s, limit);
+    if (cut.ns > 1) return launch_seg<DK, DV, TI, YG>(s, cut, a, saved_lam, saved_H, ws, st);
     return launch_dk<DK, DV, TI, YG>(s, a, saved_lam, saved_H, static_cast<float*>(ws), st);
 }
 
@@ -1211,11 +1289,8 @@ int chunked_ou_parts(const Shape& s) { return 2 * s.B; }
 
 // the segment-parallel form's buffers, or per-pair dr partials: dk / 16 of them per token
 size_t chunked_bwd_workspace(const Shape& s, size_t limit) {
-    const BwdCut cut = bwd_cut(s);
-    if (cut.ns > 1) {
-        const size_t b = seg_bytes(s, cut);
-        if (b <= limit) return b;
-    }
+    const BwdCut cut = bwd_cut(s, limit);
+    if (cut.ns > 1) return seg_bytes(s, cut.w, cut.lc);
     return (size_t)(s.dk / 16) * s.B * s.T * s.H * sizeof(float);
 }
 

@@ -24,12 +24,12 @@
 namespace kla {
 namespace {
 
-// With ns > 1 segments G starts from gend [B H ns][dk][dv], the adjoint of each segment's
-// last state, and the first segment leaves deta0.  NODV: the adjoint a segment adds on its
-// own (from zero) to the state before it goes to gend instead, with its gate product to
-// pseg [B H ns][dk]; no dV.
+// With ns > 1 segments G starts from gend [B H][w][dk][dv], the adjoint of the last state of
+// each of a window's segments s0 .. s0 + w - 1, and the first segment leaves deta0.  NODV: the
+// adjoint a segment adds on its own (from zero) to the state before it goes to gend instead, with
+// its gate product to pseg [B H][w][dk]; no dV.
 template <int DK, int DV, bool WIDE, bool TI, bool NODV>
-__global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void bwd_dv_kernel(Shape s, Seg sg, BwdArgs g,
+__global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void bwd_dv_kernel(Shape s, Seg sg, int s0, int w, BwdArgs g,
                                                                             const float* __restrict__ saved_lam,
                                                                             float* __restrict__ gend,
                                                                             float* __restrict__ pseg) {
@@ -44,7 +44,7 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void bwd_dv_kernel(
     const int b = bh / s.H, h = bh % s.H;
     const int c0 = seg * sg.lc, nct = (s.T + kC - 1) / kC;   // this segment's first chunk, the sequence's chunks
     const int H = s.H, T = min(s.T - c0 * kC, sg.lc * kC);
-    const size_t vs = (size_t)bh * sg.ns + seg;
+    const size_t vs = (size_t)bh * w + (seg - s0);           // row of gend, pseg
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform role
     const int l16 = lane & 15, g4 = lane >> 4;
@@ -211,39 +211,40 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void bwd_dv_kernel(
 }
 
 template <int DK, int DV, bool WIDE, bool TI, bool NODV>
-hipError_t launch_dv(const Shape& s, const Seg& sg, const BwdArgs& a, const float* saved_lam, float* gend, float* pseg,
-                     hipStream_t st) {
+hipError_t launch_dv(const Shape& s, const Seg& sg, int s0, int w, const BwdArgs& a, const float* saved_lam, float* gend,
+                     float* pseg, hipStream_t st) {
     using Cfg = ChunkCfg<DK, DV, WIDE>;
     auto kern = bwd_dv_kernel<DK, DV, WIDE, TI, NODV>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::BYTES);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3((unsigned)(s.B * s.H * sg.run * Cfg::NTILE)), dim3(Cfg::NTHR), Cfg::BYTES, st, s, sg,
-                       a, saved_lam, gend, pseg);
+                       s0, w, a, saved_lam, gend, pseg);
     return hipGetLastError();
 }
 
 template <int DK, int DV, bool WIDE>
-hipError_t launch_dv_ti(const Shape& s, const Seg& sg, bool nodv, const BwdArgs& a, const float* saved_lam,
-                        float* gend, float* pseg, hipStream_t st) {
+hipError_t launch_dv_ti(const Shape& s, const Seg& sg, int s0, int w, bool nodv, const BwdArgs& a,
+                        const float* saved_lam, float* gend, float* pseg, hipStream_t st) {
     if (nodv)
-        return a.ou_a ? launch_dv<DK, DV, WIDE, true, true>(s, sg, a, saved_lam, gend, pseg, st)
-                      : launch_dv<DK, DV, WIDE, false, true>(s, sg, a, saved_lam, gend, pseg, st);
-    return a.ou_a ? launch_dv<DK, DV, WIDE, true, false>(s, sg, a, saved_lam, gend, pseg, st)
-                  : launch_dv<DK, DV, WIDE, false, false>(s, sg, a, saved_lam, gend, pseg, st);
+        return a.ou_a ? launch_dv<DK, DV, WIDE, true, true>(s, sg, s0, w, a, saved_lam, gend, pseg, st)
+                      : launch_dv<DK, DV, WIDE, false, true>(s, sg, s0, w, a, saved_lam, gend, pseg, st);
+    return a.ou_a ? launch_dv<DK, DV, WIDE, true, false>(s, sg, s0, w, a, saved_lam, gend, pseg, st)
+                  : launch_dv<DK, DV, WIDE, false, false>(s, sg, s0, w, a, saved_lam, gend, pseg, st);
 }
 
 }  // namespace
 
-hipError_t launch_backward_dv(const Shape& s, int ns, int lc, bool nodv, const BwdArgs& a, const float* saved_lam,
-                              float* gend, float* pseg, hipStream_t st) {
-    const Seg sg = nodv ? Seg{ns, lc, ns - 1, 1} : Seg{ns, lc, ns, 0};
+hipError_t launch_backward_dv(const Shape& s, int ns, int lc, int s0, int w, bool nodv, const BwdArgs& a,
+                              const float* saved_lam, float* gend, float* pseg, hipStream_t st) {
+    const int skip = nodv && s0 == 0 ? 1 : 0;   // the first segment's contribution goes nowhere
+    const Seg sg{ns, lc, w - skip, s0 + skip};
     if (chunked_wide(s, sg.run)) {
-        if (s.dk == 64) return launch_dv_ti<64, 128, true>(s, sg, nodv, a, saved_lam, gend, pseg, st);
-        if (s.dk == 128) return launch_dv_ti<128, 128, true>(s, sg, nodv, a, saved_lam, gend, pseg, st);
+        if (s.dk == 64) return launch_dv_ti<64, 128, true>(s, sg, s0, w, nodv, a, saved_lam, gend, pseg, st);
+        if (s.dk == 128) return launch_dv_ti<128, 128, true>(s, sg, s0, w, nodv, a, saved_lam, gend, pseg, st);
     }
 #define KLA_DV_CASE(DK_, DV_) \
-    if (s.dk == DK_ && s.dv == DV_) return launch_dv_ti<DK_, DV_, false>(s, sg, nodv, a, saved_lam, gend, pseg, st);
+    if (s.dk == DK_ && s.dv == DV_) return launch_dv_ti<DK_, DV_, false>(s, sg, s0, w, nodv, a, saved_lam, gend, pseg, st);
 #define KLA_DV_ROW(DK_) KLA_DV_CASE(DK_, 32) KLA_DV_CASE(DK_, 64) KLA_DV_CASE(DK_, 128)
     KLA_DV_ROW(32) KLA_DV_ROW(64) KLA_DV_ROW(128)
 #undef KLA_DV_ROW

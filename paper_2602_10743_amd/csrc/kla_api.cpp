@@ -110,8 +110,8 @@ size_t kla_saved_bytes(const kla_desc* desc) {
 
 namespace {
 
-// Bytes the chunked backward may take for running segments side by side; the allocation-free
-// entry point has its static workspace (less the flags).
+// Bytes the chunked backward may take for running segments side by side, below its own bound
+// of 256 MiB; the allocation-free entry point has its static workspace (less the flags).
 size_t bwd_limit(bool least) { return least ? (size_t)KLA_NOALLOC_SCRATCH_BYTES - kAlign : SIZE_MAX; }
 
 // What the per-channel forwards ask for: the validation flag (and, for bf16 shapes, no less

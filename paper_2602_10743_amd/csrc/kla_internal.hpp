@@ -96,7 +96,8 @@ bool chunked_supported(const Shape& s);
 size_t chunked_saved_bytes(const Shape& s);
 hipError_t launch_forward_chunked(const Shape& s, const FwdArgs& a, void* saved, hipStream_t st);
 bool chunked_bwd_supported(const Shape& s);
-// limit: bytes the segment-parallel form of few sequences may use (else the whole walk is taken)
+// limit: bytes the segment-parallel form of few sequences may use: shorter windows, or the whole
+// walk where those would be slower
 size_t chunked_bwd_workspace(const Shape& s, size_t limit);
 hipError_t launch_backward_chunked(const Shape& s, const BwdArgs& a, const void* saved, void* ws, size_t limit,
                                    hipStream_t st);
@@ -116,11 +117,12 @@ hipError_t launch_forward_segmented(const Shape& s, const FwdArgs& a, void* save
 size_t backward_least_workspace(const kla_desc* desc);
 kla_status backward_least(const kla_desc* desc, const BwdArgs& a, const void* saved, void* ws, size_t ws_bytes,
                           hipStream_t stream);
-// value side of the chunked backward (dv, deta0) over ns segments of lc chunks (ns > 1: from the
-// adjoints gend of their last states); nodv: every segment's but the first's own contribution to
-// the adjoint before it into gend, with its gate product into pseg.  saved_lam: the saved walk states
-hipError_t launch_backward_dv(const Shape& s, int ns, int lc, bool nodv, const BwdArgs& a, const float* saved_lam,
-                              float* gend, float* pseg, hipStream_t st);
+// value side of the chunked backward (dv, deta0) over the window s0 .. s0 + w - 1 of ns segments
+// of lc chunks (ns > 1: from the adjoints gend [B H][w] of their last states); nodv: every
+// segment's but the sequence's first's own contribution to the adjoint before it into gend, with
+// its gate product into pseg.  saved_lam: the saved walk states
+hipError_t launch_backward_dv(const Shape& s, int ns, int lc, int s0, int w, bool nodv, const BwdArgs& a,
+                              const float* saved_lam, float* gend, float* pseg, hipStream_t st);
 // token-sum parts of the OU gate gradients that the chunked / recurrent backward leave
 int chunked_ou_parts(const Shape& s);
 int recurrent_ou_parts(const Shape& s);

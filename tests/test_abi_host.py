@@ -240,3 +240,16 @@ def test_chunk_parallel_fp32_contexts_and_workspaces(lib):
         assert lib.kla_backward_noalloc(ctypes.byref(near), *ptrs, None) != 5
     over = K._Desc(1, 66000, 1, 128, 128, 0)
     assert lib.kla_backward_noalloc(ctypes.byref(over), *ptrs, None) == 5        # KLA_ERR_WORKSPACE, as before
+
+
+def test_segment_backward_workspace_is_bounded(lib):
+    """bf16, few sequences: the segments side by side take at most 256 MiB however long the
+    sequences (beside them only the whole walk's dr parts may be larger)."""
+    import paper_2602_10743_amd as K
+    for B, T, H, dk, dv in ((4, 8192, 16, 128, 128), (1, 65536, 16, 128, 128), (1, 1 << 22, 1, 128, 128),
+                            (1, 1 << 20, 4, 32, 32), (2, 100000, 3, 64, 128)):
+        walk = dk // 16 * B * T * H * 4
+        got = K.kla_backward_workspace(_desc(B, T, H, dk, dv, 1), True)
+        assert 0 < got <= max(256 << 20, walk) + 2048, f"B{B} T{T} H{H}: {got >> 20} MiB"
+        ou = K.kla_backward_ou_workspace(_desc(B, T, H, dk, dv, 1), True)
+        assert ou <= max(256 << 20, walk) + 2048 + 16 * B * H * dk

@@ -83,3 +83,66 @@ def test_against_oracle(kla, B, T, H, dk, dv, ou):
             for n in ("da", "dp", "ddelta"):
                 e = rel_err_sum(to_np(got[n]), rg[n], rg["mass_" + n])
                 assert e <= TOL["bf16"], f"{n}: {e:.2e}"
+
+
+def _lm(B, T, H, dk, dv, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    z = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    x = dict(q=z(B, T, H, dk), k=torch.nn.functional.normalize(z(B, T, H, dk), dim=-1), v=z(B, T, H, dv),
+             r=0.1 + z(B, T, H).abs(), a=torch.sigmoid(z(B, T, H, dk) + 3), p=0.05 * z(B, T, H, dk).abs(),
+             dy=z(B, T, H, dv))
+    x = {n: t.bfloat16() for n, t in x.items()}
+    x.update(lam0=0.5 + torch.rand(B, H, dk, generator=g, device=DEV), eta0=z(B, H, dk, dv), dlamT=z(B, H, dk),
+             detaT=z(B, H, dk, dv), dyvar=z(B, T, H))
+    return x, z
+
+
+# the allocation-free backward works in 64 MiB: the same segments in windows, bit for bit
+@pytest.mark.parametrize("B,T,H,dk,dv", [(2, 2048, 16, 128, 128), (1, 30011, 8, 32, 64), (1, 20000, 5, 64, 128)])
+def test_windows_agree(kla, B, T, H, dk, dv):
+    log(f"segment windows B{B} T{T} H{H} {dk} x {dv}")
+    x, _ = _lm(B, T, H, dk, dv, T)
+    fa = [x[n] for n in TOKEN] + [x["lam0"], x["eta0"]]
+    saved = kla.kla_forward(*fa, save=True)["saved"]
+    args = fa + [x["dy"], x["dlamT"], x["detaT"]]
+    ref = kla.kla_backward(*args, saved=saved, dyvar=x["dyvar"])
+    got = kla.kla_backward_noalloc(*args, saved=saved, dyvar=x["dyvar"])
+    torch.cuda.synchronize()
+    for n in ("dq", "dk", "dv", "da", "dp", "dr", "dlam0", "deta0"):
+        assert torch.equal(got[n], ref[n]), n
+
+
+def test_ou_windows_agree_with_halves(kla):
+    """A sequence whose segments need two windows against its halves (one window each), joined
+    through the belief and its gradient.  Both round the same fp32 sums in another order; per token
+    by at most one bf16 rounding more (2^-8)."""
+    T, H, d, m = 24000, 16, 128, 12000
+    log(f"OU segment windows T{T} H{H} {d} x {d}")
+    x, z = _lm(1, T, H, d, d, 7)
+    gates = [1 + 15 * torch.rand(H, d, device=DEV), z(H, d).abs() + 1, 0.001 + 0.05 * torch.rand(H, d, device=DEV)]
+
+    def run(s, lam0, eta0):
+        return [x[n][:, s].contiguous() for n in ("q", "k", "v")] + gates + [x["r"][:, s].contiguous(), lam0, eta0]
+
+    def grads(fa, s, dlamT, detaT, saved):
+        return kla.kla_backward_ou(*fa, x["dy"][:, s].contiguous(), dlamT, detaT, saved=saved,
+                                   dyvar=x["dyvar"][:, s].contiguous())
+
+    every, one, two = slice(0, T), slice(0, m), slice(m, T)
+    fa = run(every, x["lam0"], x["eta0"])
+    ref = grads(fa, every, x["dlamT"], x["detaT"], kla.kla_forward_ou(*fa, save=True)["saved"])
+    f1 = run(one, x["lam0"], x["eta0"])
+    o1 = kla.kla_forward_ou(*f1, save=True)
+    f2 = run(two, o1["lamT"], o1["etaT"])
+    g2 = grads(f2, two, x["dlamT"], x["detaT"], kla.kla_forward_ou(*f2, save=True)["saved"])
+    g1 = grads(f1, one, g2["dlam0"], g2["deta0"], o1["saved"])
+    for n in ("dq", "dk", "dv", "dr"):
+        e = rel_err(to_np(torch.cat([g1[n], g2[n]], 1)), to_np(ref[n]))
+        assert e <= TOL["bf16"], f"{n}: {e:.2e}"
+    for n in ("dlam0", "deta0"):
+        e = rel_err(to_np(g1[n]), to_np(ref[n]))
+        assert e <= TOL["bf16"], f"{n}: {e:.2e}"
+    for n in ("da", "dp", "ddelta"):
+        a, b = (g1[n] + g2[n]).double(), ref[n].double()
+        e = float((a - b).norm() / b.norm())
+        assert e <= 1e-3, f"{n}: {e:.2e}"
