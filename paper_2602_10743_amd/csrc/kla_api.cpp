@@ -110,6 +110,8 @@ size_t kla_saved_bytes(const kla_desc* desc) {
 
 namespace {
 
+size_t max_size(size_t a, size_t b) { return a > b ? a : b; }
+
 // Bytes the chunked backward may take for running segments side by side, below its own bound
 // of 256 MiB; the allocation-free entry point has its static workspace (less the flags).
 size_t bwd_limit(bool least) { return least ? (size_t)KLA_NOALLOC_SCRATCH_BYTES - kAlign : SIZE_MAX; }
@@ -128,13 +130,14 @@ size_t backward_workspace(const kla_desc* desc, int with_saved, bool least) {
         size_t work = kla::c64p_bwd_workspace(s, least);
         if (with_saved) return kAlign + round_up(work);
         // the context is recomputed: saved states plus a scratch output, the forward's work memory shared
-        const size_t fwd = kla::c64p_fwd_workspace(s, true);
-        if (fwd > work) work = fwd;
+        work = max_size(work, kla::c64p_fwd_workspace(s, true));
         return kAlign + round_up(work) + round_up(kla::c64p_saved_bytes(s)) +
                round_up((size_t)s.B * s.T * s.H * s.dv * sizeof(float));
     }
     if (kla::chunked_bwd_supported(s)) {
-        size_t bytes = kAlign + round_up(kla::chunked_bwd_workspace(s, bwd_limit(least)));
+        size_t work = kla::chunked_bwd_workspace(s, bwd_limit(least));
+        if (!with_saved) work = max_size(work, kla::forward_segmented_workspace(s));
+        size_t bytes = kAlign + round_up(work);
         if (!with_saved) {  // the context is recomputed: saved states plus a scratch output
             const size_t elt = s.bf16 ? 2 : 4;
             bytes += round_up(kla::chunked_saved_bytes(s)) + round_up((size_t)s.B * s.T * s.H * s.dv * elt);
@@ -162,6 +165,12 @@ extern "C" size_t kla_backward_workspace(const kla_desc* desc, int with_saved) {
 }
 
 namespace {
+
+// The chunked bf16 forward, in segments where there are few sequences.
+hipError_t forward_chunked(const kla::Shape& s, const kla::FwdArgs& a, void* saved, void* work, hipStream_t stream) {
+    return kla::forward_segments(s) > 1 ? kla::launch_forward_segmented(s, a, saved, work, stream)
+                                        : kla::launch_forward_chunked(s, a, saved, stream);
+}
 
 // The forward of the chunk-parallel fp64 path.  At widths above 32 the token-recurrent
 // forward is launched behind it: it overwrites everything if a chunk left the walk's range,
@@ -202,10 +211,8 @@ kla_status forward_impl(const kla_desc* desc, const kla::FwdArgs& a, bool ou, vo
     // layout the backward reads (saves_chunked)
     const bool chunked = saved ? saves_chunked(s) : kla::chunked_supported(s);
     const bool c64 = kla::c64_supported(s);
-    if (chunked && kla::forward_segments(s) > 1)
-        e = kla::launch_forward_segmented(s, fa, saved, static_cast<char*>(ws) + kAlign, stream);
-    else if (chunked)
-        e = kla::launch_forward_chunked(s, fa, saved, stream);
+    if (chunked)
+        e = forward_chunked(s, fa, saved, static_cast<char*>(ws) + kAlign, stream);
     else if (kla::c64p_supported(s))
         e = forward_c64p(s, fa, saved, static_cast<char*>(ws) + kAlign, static_cast<int*>(ws) + 16, stream);
     else if (c64)
@@ -256,20 +263,20 @@ kla_status backward_impl(const kla_desc* desc, kla::BwdArgs a, bool ou, const vo
     char* work = static_cast<char*>(ws) + kAlign;
     hipError_t e;
     if (kla::chunked_bwd_supported(s)) {
-        if (!saved) {
-            char* ctx = work + round_up(kla::chunked_bwd_workspace(s, bwd_limit(least)));
+        if (!saved) {   // by the forward's own kernels, whose work memory the backward's takes the place of
+            char* ctx = work + round_up(max_size(kla::chunked_bwd_workspace(s, bwd_limit(least)),
+                                                 kla::forward_segmented_workspace(s)));
             void* yscratch = ctx + round_up(kla::chunked_saved_bytes(s));
             kla::FwdArgs f{a.q, a.k, a.v, a.a, a.p, a.r, a.lam0, a.eta0, yscratch, nullptr, nullptr, nullptr,
                            a.ou_a, a.ou_p, a.ou_d, a.range_flag};
-            e = kla::launch_forward_chunked(s, f, ctx, stream);
+            e = forward_chunked(s, f, ctx, work, stream);
             if (e != hipSuccess) return KLA_ERR_HIP;
             saved = ctx;
         }
         e = kla::launch_backward_chunked(s, a, saved, work, bwd_limit(least), stream);
     } else if (kla::c64p_supported(s)) {
         if (!saved) {   // the forward's work memory comes before the context, the backward's takes its place
-            const size_t fwd = kla::c64p_fwd_workspace(s, true), bwd = kla::c64p_bwd_workspace(s, false);
-            char* ctx = work + round_up(fwd > bwd ? fwd : bwd);
+            char* ctx = work + round_up(max_size(kla::c64p_fwd_workspace(s, true), kla::c64p_bwd_workspace(s, false)));
             void* yscratch = ctx + round_up(kla::c64p_saved_bytes(s));
             kla::FwdArgs f{a.q, a.k, a.v, a.a, a.p, a.r, a.lam0, a.eta0, yscratch, nullptr, nullptr, nullptr,
                            a.ou_a, a.ou_p, a.ou_d, a.range_flag};

@@ -152,3 +152,24 @@ def test_ou_windows_agree_with_halves(kla):
         a, b = (g1[n] + g2[n]).double(), ref[n].double()
         e = float((a - b).norm() / b.norm())
         assert e <= 1e-3, f"{n}: {e:.2e}"
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv", [(1, 2011, 4, 128, 128), (1, 1500, 3, 64, 32)])
+@pytest.mark.parametrize("ou", [False, True])
+def test_recomputed_context_agrees(kla, B, T, H, dk, dv, ou):
+    """Without a saved context the backward forms it by the forward's own (segmented) kernels:
+    the same gradients bit for bit."""
+    log(f"recomputed context B{B} T{T} H{H} {dk} x {dv} ou={ou}")
+    x, z = _lm(B, T, H, dk, dv, T)
+    if ou:
+        gates = _gates(z, H, dk)
+        fa = [x["q"], x["k"], x["v"], *gates, x["r"], x["lam0"], x["eta0"]]
+        fwd, bwd = kla.kla_forward_ou, kla.kla_backward_ou
+    else:
+        fa = [x[n] for n in TOKEN] + [x["lam0"], x["eta0"]]
+        fwd, bwd = kla.kla_forward, kla.kla_backward
+    args = fa + [x["dy"], x["dlamT"], x["detaT"]]
+    ref = bwd(*args, saved=fwd(*fa, save=True)["saved"], dyvar=x["dyvar"])
+    got = bwd(*args, dyvar=x["dyvar"])
+    for n in ref:
+        assert torch.equal(got[n], ref[n]), n
