@@ -4,7 +4,9 @@
 //
 // A training step of a few sequences is bound by the host: through ctypes and torch.empty the
 // forward took 21 us and the backward 33 us of it, more than their kernels.  Functions return the
-// output tensors, or the status code when the library refuses the call.
+// output tensors, or the status code when the library refuses the call.  Past the checks they give
+// up the interpreter lock, as ctypes does: allocations and a full launch queue can block, and under
+// KLA_CHECK=1 the library waits for the stream.
 #include <array>
 #include <string>
 
@@ -95,23 +97,27 @@ py::object forward(const Tensor& q, const Tensor& k, const Tensor& v, const Tens
         check_f32(delta, {d.H, d.dk}, q, "delta");
     }
     check_belief(d, lam0, eta0, q, "lam0", "eta0");
-    const auto f32 = q.options().dtype(at::kFloat);
-    Tensor y = y_in ? *y_in : at::empty({d.B, d.T, d.H, d.dv}, q.options());
+    Tensor y;
     Opt yvar, lamT, etaT, saved;
-    if (want_var) yvar = at::empty({d.B, d.T, d.H}, f32);
-    if (want_state) {
-        lamT = at::empty({d.B, d.H, d.dk}, f32);
-        etaT = at::empty({d.B, d.H, d.dk, d.dv}, f32);
+    kla_status st;
+    {
+        py::gil_scoped_release unlocked;
+        const auto f32 = q.options().dtype(at::kFloat);
+        y = y_in ? *y_in : at::empty({d.B, d.T, d.H, d.dv}, q.options());
+        if (want_var) yvar = at::empty({d.B, d.T, d.H}, f32);
+        if (want_state) {
+            lamT = at::empty({d.B, d.H, d.dk}, f32);
+            etaT = at::empty({d.B, d.H, d.dk, d.dv}, f32);
+        }
+        const size_t ns = save ? kla_saved_bytes(&d) : 0, nw = kla_forward_workspace(&d);
+        if (ns) saved = bytes(ns, q);
+        const Tensor ws = bytes(nw, q);
+        st = ou ? kla_forward_ou(&d, ptr(q), ptr(k), ptr(v), (const float*)ptr(a), (const float*)ptr(p), fptr(delta),
+                                 ptr(r), fptr(lam0), fptr(eta0), ptr(y), fptr(yvar), fptr(lamT), fptr(etaT), ptr(saved),
+                                 ptr(ws), nw, stream_of(q))
+                : kla_forward(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(y),
+                              fptr(yvar), fptr(lamT), fptr(etaT), ptr(saved), ptr(ws), nw, stream_of(q));
     }
-    const size_t ns = save ? kla_saved_bytes(&d) : 0, nw = kla_forward_workspace(&d);
-    if (ns) saved = bytes(ns, q);
-    const Tensor ws = bytes(nw, q);
-    const kla_status st =
-        ou ? kla_forward_ou(&d, ptr(q), ptr(k), ptr(v), (const float*)ptr(a), (const float*)ptr(p), fptr(delta), ptr(r),
-                            fptr(lam0), fptr(eta0), ptr(y), fptr(yvar), fptr(lamT), fptr(etaT), ptr(saved), ptr(ws), nw,
-                            stream_of(q))
-           : kla_forward(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(y), fptr(yvar),
-                         fptr(lamT), fptr(etaT), ptr(saved), ptr(ws), nw, stream_of(q));
     if (st != KLA_OK) return py::int_((int)st);
     return py::make_tuple(y, obj(yvar), obj(lamT), obj(etaT), obj(saved));
 }
@@ -133,33 +139,37 @@ py::object backward(const Tensor& q, const Tensor& k, const Tensor& v, const Ten
     check_f32(dyvar, {d.B, d.T, d.H}, q, "dyvar");
     if (dy.sizes() != at::IntArrayRef({d.B, d.T, d.H, d.dv}) || dy.scalar_type() != q.scalar_type() || !dy.is_contiguous())
         value_error("dy must be a contiguous [B, T, H, dv] tensor in the input dtype");
-    const auto f32 = q.options().dtype(at::kFloat);
-    const Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v), dr = at::empty_like(r);
-    const Tensor da = at::empty_like(a), dp = at::empty_like(p);   // OU: [H, dk] fp32, as the parameters
+    Tensor dq, dk, dv, da, dp, dr;
     Opt ddelta, dlam0, deta0;
-    if (ou) ddelta = at::empty_like(*delta);
-    if (want_init) {
-        dlam0 = at::empty({d.B, d.H, d.dk}, f32);
-        deta0 = at::empty({d.B, d.H, d.dk, d.dv}, f32);
-    }
     kla_status st;
-    if (noalloc) {
-        st = kla_backward_noalloc(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(saved),
-                                  ptr(dy), fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq), ptr(dk), ptr(dv), ptr(da),
-                                  ptr(dp), ptr(dr), fptr(dlam0), fptr(deta0), stream_of(q));
-    } else if (ou) {
-        const size_t nw = kla_backward_ou_workspace(&d, saved.has_value());
-        const Tensor ws = bytes(nw, q);
-        st = kla_backward_ou(&d, ptr(q), ptr(k), ptr(v), (const float*)ptr(a), (const float*)ptr(p), fptr(delta), ptr(r),
-                             fptr(lam0), fptr(eta0), ptr(saved), ptr(dy), fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq),
-                             ptr(dk), ptr(dv), (float*)ptr(da), (float*)ptr(dp), fptr(ddelta), ptr(dr), fptr(dlam0),
-                             fptr(deta0), ptr(ws), nw, stream_of(q));
-    } else {
-        const size_t nw = kla_backward_workspace(&d, saved.has_value());
-        const Tensor ws = bytes(nw, q);
-        st = kla_backward(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(saved), ptr(dy),
-                          fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq), ptr(dk), ptr(dv), ptr(da), ptr(dp), ptr(dr),
-                          fptr(dlam0), fptr(deta0), ptr(ws), nw, stream_of(q));
+    {
+        py::gil_scoped_release unlocked;
+        const auto f32 = q.options().dtype(at::kFloat);
+        dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v), dr = at::empty_like(r);
+        da = at::empty_like(a), dp = at::empty_like(p);   // OU: [H, dk] fp32, as the parameters
+        if (ou) ddelta = at::empty_like(*delta);
+        if (want_init) {
+            dlam0 = at::empty({d.B, d.H, d.dk}, f32);
+            deta0 = at::empty({d.B, d.H, d.dk, d.dv}, f32);
+        }
+        if (noalloc) {
+            st = kla_backward_noalloc(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(saved),
+                                      ptr(dy), fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq), ptr(dk), ptr(dv), ptr(da),
+                                      ptr(dp), ptr(dr), fptr(dlam0), fptr(deta0), stream_of(q));
+        } else if (ou) {
+            const size_t nw = kla_backward_ou_workspace(&d, saved.has_value());
+            const Tensor ws = bytes(nw, q);
+            st = kla_backward_ou(&d, ptr(q), ptr(k), ptr(v), (const float*)ptr(a), (const float*)ptr(p), fptr(delta), ptr(r),
+                                 fptr(lam0), fptr(eta0), ptr(saved), ptr(dy), fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq),
+                                 ptr(dk), ptr(dv), (float*)ptr(da), (float*)ptr(dp), fptr(ddelta), ptr(dr), fptr(dlam0),
+                                 fptr(deta0), ptr(ws), nw, stream_of(q));
+        } else {
+            const size_t nw = kla_backward_workspace(&d, saved.has_value());
+            const Tensor ws = bytes(nw, q);
+            st = kla_backward(&d, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam0), fptr(eta0), ptr(saved), ptr(dy),
+                              fptr(dyvar), fptr(dlamT), fptr(detaT), ptr(dq), ptr(dk), ptr(dv), ptr(da), ptr(dp), ptr(dr),
+                              fptr(dlam0), fptr(deta0), ptr(ws), nw, stream_of(q));
+        }
     }
     if (st != KLA_OK) return py::int_((int)st);
     if (ou) return py::make_tuple(dq, dk, dv, da, dp, dr, obj(dlam0), obj(deta0), *ddelta);
@@ -191,15 +201,20 @@ py::object decode_step(const Tensor& q, const Tensor& k, const Tensor& v, const 
     }
     check_f32(lam, {S, H, dk}, q, "lam");
     check_f32(eta, {S, H, dk, dv}, q, "eta");
-    Tensor y = y_in ? *y_in : at::empty({S, H, dv}, q.options());
-    Opt yvar;
-    if (want_var) yvar = at::empty({S, H}, q.options().dtype(at::kFloat));
     const kla_dtype dt = (kla_dtype)dtype_of(q);
-    const kla_status st =
-        ou ? kla_decode_step_ou(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), (const float*)ptr(a), (const float*)ptr(p),
-                                fptr(delta), ptr(r), (float*)ptr(lam), (float*)ptr(eta), ptr(y), fptr(yvar), stream_of(q))
-           : kla_decode_step(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), (float*)ptr(lam),
-                             (float*)ptr(eta), ptr(y), fptr(yvar), stream_of(q));
+    Tensor y;
+    Opt yvar;
+    kla_status st;
+    {
+        py::gil_scoped_release unlocked;
+        y = y_in ? *y_in : at::empty({S, H, dv}, q.options());
+        if (want_var) yvar = at::empty({S, H}, q.options().dtype(at::kFloat));
+        st = ou ? kla_decode_step_ou(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), (const float*)ptr(a),
+                                     (const float*)ptr(p), fptr(delta), ptr(r), (float*)ptr(lam), (float*)ptr(eta),
+                                     ptr(y), fptr(yvar), stream_of(q))
+                : kla_decode_step(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), (float*)ptr(lam),
+                                  (float*)ptr(eta), ptr(y), fptr(yvar), stream_of(q));
+    }
     if (st != KLA_OK) return py::int_((int)st);
     return py::make_tuple(y, obj(yvar));
 }

@@ -67,3 +67,45 @@ def test_unused_outputs_have_no_gradient():
     both = torch.autograd.grad(y.sum() + lamT.sum(), x)
     for a, b, c in zip(gy, gl, both):
         assert torch.allclose(a + b, c, rtol=1e-5, atol=1e-5 * float(c.abs().max() + 1))
+
+
+@pytest.mark.gpu
+def test_other_threads_run_during_a_call(monkeypatch):
+    """The interpreter lock is given up in a call: under KLA_CHECK=1 it waits for the stream,
+    here behind some 0.3 s of other work, and another thread goes on meanwhile."""
+    import threading
+    import time
+
+    import paper_2602_10743_amd as K
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = _inputs("cuda:0")
+    monkeypatch.setenv("KLA_CHECK", "1")
+    K.kla_forward(*x)
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record()
+    torch.cuda._sleep(10_000_000)
+    end.record()
+    torch.cuda.synchronize()
+    cycles = int(10_000_000 * 300.0 / start.elapsed_time(end))
+    calls = [lambda: K.kla_forward(*x), lambda: K.kla_backward(*x, None, None, x[2])]
+    for call in calls:
+        torch.cuda._sleep(cycles)
+        took = []
+
+        def work():
+            t0 = time.perf_counter()
+            call()
+            took.append(time.perf_counter() - t0)
+
+        t = threading.Thread(target=work)
+        last, gap = time.perf_counter(), 0.0
+        t.start()
+        while t.is_alive():
+            time.sleep(0.001)
+            now = time.perf_counter()
+            last, gap = now, max(gap, now - last)
+        t.join()
+        torch.cuda.synchronize()
+        assert took[0] > 0.1, "the call did not wait for the stream"
+        assert gap < 0.5 * took[0], f"held the interpreter lock for {gap:.2f} of {took[0]:.2f} s"
