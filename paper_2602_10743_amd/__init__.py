@@ -186,7 +186,7 @@ def kla_forward(q, k, v, a, p, r, lam0=None, eta0=None, *, want_var: bool = Fals
     r: [B, T, H] (all one dtype, fp32 or bf16).  lam0 [B, H, dk], eta0
     [B, H, dk, dv] fp32 or None (prior 1 and 0).  Returns y and, as asked,
     yvar, the final belief (lamT, etaT) and the saved context for backward."""
-    out = _native().forward(q, k, v, a, p, None, r, lam0, eta0, y, want_var, want_state, save)
+    out = _native().forward(q, k, v, a, p, None, r, lam0, eta0, y, want_var, want_state, save, False)
     return _outputs(out, "kla_forward")
 
 
@@ -212,7 +212,8 @@ def kla_backward(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=None, *, sa
     (dy, dyvar [B, T, H] fp32 or None, dlamT, detaT); returns dq, dk, dv, da, dp,
     dr in the input dtype and, when asked, dlam0 [B, H, dk] and deta0
     [B, H, dk, dv] in fp32."""
-    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False)
+    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False,
+                             False)
     return _grads(out, "kla_backward")
 
 
@@ -221,14 +222,15 @@ def kla_backward_noalloc(q, k, v, a, p, r, lam0, eta0, dy, dlamT=None, detaT=Non
     """kla_backward through the library's per-GPU static workspace (the entry point for
     callers that cannot allocate; only the outputs are allocated here, by torch).  A saved
     context from kla_forward(save=True) is required."""
-    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, True)
+    out = _native().backward(q, k, v, a, p, None, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, True,
+                             False)
     return _grads(out, "kla_backward_noalloc")
 
 
 def kla_decode_step(q, k, v, a, p, r, lam, eta, *, want_var: bool = False, y=None) -> dict:
     """One token for S sequences: q, k, a, p [S, H, dk]; v [S, H, dv]; r [S, H];
     lam [S, H, dk] and eta [S, H, dk, dv] fp32 are updated in place."""
-    out = _native().decode_step(q, k, v, a, p, None, r, lam, eta, y, want_var)
+    out = _native().decode_step(q, k, v, a, p, None, r, lam, eta, y, want_var, False)
     if isinstance(out, int):
         raise KLAError(out, "kla_decode_step")
     return {"y": out[0], "yvar": out[1], "lam": lam, "eta": eta}
@@ -284,7 +286,7 @@ def kla_backward_ou_workspace(desc: _Desc, with_saved: bool) -> int:
 def kla_forward_ou(q, k, v, a, p, delta, r, lam0=None, eta0=None, *, want_var: bool = False,
                    want_state: bool = True, save: bool = False, y=None) -> dict:
     """kla_forward with the gates of the OU parameters a, p, delta [H, dk] fp32."""
-    out = _native().forward(q, k, v, a, p, delta, r, lam0, eta0, y, want_var, want_state, save)
+    out = _native().forward(q, k, v, a, p, delta, r, lam0, eta0, y, want_var, want_state, save, True)
     return _outputs(out, "kla_forward_ou")
 
 
@@ -292,13 +294,14 @@ def kla_backward_ou(q, k, v, a, p, delta, r, lam0, eta0, dy, dlamT=None, detaT=N
                     want_init_grads: bool = True, dyvar=None) -> dict:
     """Gradients of kla_forward_ou (dyvar as in kla_backward): dq, dk, dv, dr in
     the input dtype; da, dp, ddelta [H, dk] fp32; dlam0, deta0 in fp32 when asked."""
-    out = _native().backward(q, k, v, a, p, delta, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False)
+    out = _native().backward(q, k, v, a, p, delta, r, lam0, eta0, dy, dlamT, detaT, saved, want_init_grads, dyvar, False,
+                             True)
     return _grads(out, "kla_backward_ou")
 
 
 def kla_decode_step_ou(q, k, v, a, p, delta, r, lam, eta, *, want_var: bool = False, y=None) -> dict:
     """kla_decode_step with the gates of the OU parameters a, p, delta [H, dk] fp32."""
-    out = _native().decode_step(q, k, v, a, p, delta, r, lam, eta, y, want_var)
+    out = _native().decode_step(q, k, v, a, p, delta, r, lam, eta, y, want_var, True)
     if isinstance(out, int):
         raise KLAError(out, "kla_decode_step_ou")
     return {"y": out[0], "yvar": out[1], "lam": lam, "eta": eta}

@@ -79,23 +79,32 @@ void check_belief(const kla_desc& d, const Opt& lam, const Opt& eta, const Tenso
     check_f32(eta, {d.B, d.H, d.dk, d.dv}, q, en);
 }
 
+void check_ou(const Opt& a, const Opt& p, const Opt& delta, int64_t H, int64_t dk, const Tensor& q) {
+    check_f32(a, {H, dk}, q, "a");
+    check_f32(p, {H, dk}, q, "p");
+    check_f32(delta, {H, dk}, q, "delta");
+}
+
+// a per-token gate tensor, which has to be there (none with OU gates)
+const Tensor* per_token(const Opt& t, bool ou, const char* name) {
+    if (ou) return nullptr;
+    if (!t) throw py::type_error(std::string(name) + " must be a tensor");
+    return &*t;
+}
+
 Tensor bytes(size_t n, const Tensor& q) {
     return at::empty({(int64_t)(n > 1 ? n : 1)}, q.options().dtype(at::kByte));
 }
 
 py::object obj(const Opt& t) { return t ? py::cast(*t) : py::none(); }
 
-// (y, yvar, lamT, etaT, saved) or a status.  OU gates: a, p, delta [H, dk] fp32.
-py::object forward(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& a, const Tensor& p,
-                   const Opt& delta, const Tensor& r, const Opt& lam0, const Opt& eta0, const Opt& y_in,
-                   bool want_var, bool want_state, bool save) {
-    const bool ou = delta.has_value();
-    const kla_desc d = check_inputs(q, k, v, ou ? nullptr : &a, ou ? nullptr : &p, r);
-    if (ou) {
-        check_f32(a, {d.H, d.dk}, q, "a");
-        check_f32(p, {d.H, d.dk}, q, "p");
-        check_f32(delta, {d.H, d.dk}, q, "delta");
-    }
+// (y, yvar, lamT, etaT, saved) or a status.  ou: OU gates, a, p, delta [H, dk] fp32 (the library
+// refuses the call when one is absent).
+py::object forward(const Tensor& q, const Tensor& k, const Tensor& v, const Opt& a, const Opt& p, const Opt& delta,
+                   const Tensor& r, const Opt& lam0, const Opt& eta0, const Opt& y_in, bool want_var, bool want_state,
+                   bool save, bool ou) {
+    const kla_desc d = check_inputs(q, k, v, per_token(a, ou, "a"), per_token(p, ou, "p"), r);
+    if (ou) check_ou(a, p, delta, d.H, d.dk, q);
     check_belief(d, lam0, eta0, q, "lam0", "eta0");
     Tensor y;
     Opt yvar, lamT, etaT, saved;
@@ -123,17 +132,11 @@ py::object forward(const Tensor& q, const Tensor& k, const Tensor& v, const Tens
 }
 
 // (dq, dk, dv, da, dp, dr, dlam0, deta0[, ddelta]) or a status
-py::object backward(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& a, const Tensor& p,
-                    const Opt& delta, const Tensor& r, const Opt& lam0, const Opt& eta0, const Tensor& dy,
-                    const Opt& dlamT, const Opt& detaT, const Opt& saved, bool want_init, const Opt& dyvar,
-                    bool noalloc) {
-    const bool ou = delta.has_value();
-    const kla_desc d = check_inputs(q, k, v, ou ? nullptr : &a, ou ? nullptr : &p, r);
-    if (ou) {
-        check_f32(a, {d.H, d.dk}, q, "a");
-        check_f32(p, {d.H, d.dk}, q, "p");
-        check_f32(delta, {d.H, d.dk}, q, "delta");
-    }
+py::object backward(const Tensor& q, const Tensor& k, const Tensor& v, const Opt& a, const Opt& p, const Opt& delta,
+                    const Tensor& r, const Opt& lam0, const Opt& eta0, const Tensor& dy, const Opt& dlamT,
+                    const Opt& detaT, const Opt& saved, bool want_init, const Opt& dyvar, bool noalloc, bool ou) {
+    const kla_desc d = check_inputs(q, k, v, per_token(a, ou, "a"), per_token(p, ou, "p"), r);
+    if (ou) check_ou(a, p, delta, d.H, d.dk, q);
     check_belief(d, lam0, eta0, q, "lam0", "eta0");
     check_belief(d, dlamT, detaT, q, "dlamT", "detaT");
     check_f32(dyvar, {d.B, d.T, d.H}, q, "dyvar");
@@ -146,8 +149,9 @@ py::object backward(const Tensor& q, const Tensor& k, const Tensor& v, const Ten
         py::gil_scoped_release unlocked;
         const auto f32 = q.options().dtype(at::kFloat);
         dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v), dr = at::empty_like(r);
-        da = at::empty_like(a), dp = at::empty_like(p);   // OU: [H, dk] fp32, as the parameters
-        if (ou) ddelta = at::empty_like(*delta);
+        da = ou ? at::empty({d.H, d.dk}, f32) : at::empty_like(*a);
+        dp = ou ? at::empty({d.H, d.dk}, f32) : at::empty_like(*p);
+        if (ou) ddelta = at::empty({d.H, d.dk}, f32);
         if (want_init) {
             dlam0 = at::empty({d.B, d.H, d.dk}, f32);
             deta0 = at::empty({d.B, d.H, d.dk, d.dv}, f32);
@@ -177,28 +181,23 @@ py::object backward(const Tensor& q, const Tensor& k, const Tensor& v, const Ten
 }
 
 // (y, yvar) or a status; lam, eta updated in place
-py::object decode_step(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& a, const Tensor& p,
-                       const Opt& delta, const Tensor& r, const Tensor& lam, const Tensor& eta, const Opt& y_in,
-                       bool want_var) {
+py::object decode_step(const Tensor& q, const Tensor& k, const Tensor& v, const Opt& a, const Opt& p,
+                       const Opt& delta, const Tensor& r, const Opt& lam, const Opt& eta, const Opt& y_in,
+                       bool want_var, bool ou) {
     if (!q.is_cuda() || (q.scalar_type() != at::kFloat && q.scalar_type() != at::kBFloat16))
         value_error("decode inputs must be fp32/bf16 GPU tensors");
     if (q.dim() != 3) value_error("q must be [S, H, dk]");
-    const bool ou = delta.has_value();
     const int64_t S = q.size(0), H = q.size(1), dk = q.size(2), dv = v.size(-1);
     const std::array<int64_t, 3> ks{S, H, dk}, vs{S, H, dv};
     const std::array<int64_t, 2> rs{S, H};
-    const Tensor* t[6] = {&q, &k, &v, ou ? nullptr : &a, ou ? nullptr : &p, &r};
+    const Tensor* t[6] = {&q, &k, &v, per_token(a, ou, "a"), per_token(p, ou, "p"), &r};
     for (int i : {1, 3, 4, 2, 5}) {
         if (!t[i]) continue;
         const at::IntArrayRef want = i == 2 ? at::IntArrayRef(vs) : i == 5 ? at::IntArrayRef(rs) : at::IntArrayRef(ks);
         if (t[i]->sizes() != want || t[i]->scalar_type() != q.scalar_type() || !t[i]->is_contiguous())
             value_error(std::string(kNames[i]) + " must be a contiguous " + shape_str(want) + " tensor in q's dtype");
     }
-    if (ou) {
-        check_f32(a, {H, dk}, q, "a");
-        check_f32(p, {H, dk}, q, "p");
-        check_f32(delta, {H, dk}, q, "delta");
-    }
+    if (ou) check_ou(a, p, delta, H, dk, q);
     check_f32(lam, {S, H, dk}, q, "lam");
     check_f32(eta, {S, H, dk, dv}, q, "eta");
     const kla_dtype dt = (kla_dtype)dtype_of(q);
@@ -210,10 +209,10 @@ py::object decode_step(const Tensor& q, const Tensor& k, const Tensor& v, const 
         y = y_in ? *y_in : at::empty({S, H, dv}, q.options());
         if (want_var) yvar = at::empty({S, H}, q.options().dtype(at::kFloat));
         st = ou ? kla_decode_step_ou(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), (const float*)ptr(a),
-                                     (const float*)ptr(p), fptr(delta), ptr(r), (float*)ptr(lam), (float*)ptr(eta),
+                                     (const float*)ptr(p), fptr(delta), ptr(r), fptr(lam), fptr(eta),
                                      ptr(y), fptr(yvar), stream_of(q))
-                : kla_decode_step(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), (float*)ptr(lam),
-                                  (float*)ptr(eta), ptr(y), fptr(yvar), stream_of(q));
+                : kla_decode_step(S, H, dk, dv, dt, ptr(q), ptr(k), ptr(v), ptr(a), ptr(p), ptr(r), fptr(lam),
+                                  fptr(eta), ptr(y), fptr(yvar), stream_of(q));
     }
     if (st != KLA_OK) return py::int_((int)st);
     return py::make_tuple(y, obj(yvar));

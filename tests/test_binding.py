@@ -55,6 +55,30 @@ def test_bad_tensors_are_refused():
 
 
 @pytest.mark.gpu
+def test_absent_ou_parameters_are_refused():
+    """An OU entry point without one of a, p, delta is refused, and per-token gates are not taken
+    in their place."""
+    import paper_2602_10743_amd as K
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    q, k, v, a, p, r = _inputs("cuda:0")
+    par = [torch.ones(2, 32, device="cuda:0") for _ in range(3)]
+    lam, eta = torch.ones(1, 2, 32, device="cuda:0"), torch.zeros(1, 2, 32, 16, device="cuda:0")
+    one = [t[:, 0].contiguous() for t in (q, k, v, r)]
+    for i in range(3):
+        some = [None if j == i else t for j, t in enumerate(par)]
+        for call in (lambda: K.kla_forward_ou(q, k, v, *some, r), lambda: K.kla_backward_ou(q, k, v, *some, r, None, None, v),
+                     lambda: K.kla_decode_step_ou(*one[:3], *some, one[3], lam, eta)):
+            with pytest.raises(K.KLAError) as e:
+                call()
+            assert e.value.status == 1   # KLA_ERR_NULL
+    with pytest.raises(ValueError, match="a must be a contiguous float32"):
+        K.kla_forward_ou(q, k, v, a, p, None, r)
+    with pytest.raises(K.KLAError):
+        K.kla_decode_step_ou(*one[:3], *par, one[3], None, eta)
+
+
+@pytest.mark.gpu
 def test_unused_outputs_have_no_gradient():
     """Gradients through y alone, through lamT alone and through both agree with their sum."""
     import paper_2602_10743_amd as K
