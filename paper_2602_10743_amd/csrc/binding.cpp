@@ -34,7 +34,7 @@ std::string shape_str(at::IntArrayRef s) {
 int dtype_of(const Tensor& q) {
     if (q.scalar_type() == at::kFloat) return KLA_F32;
     if (q.scalar_type() == at::kBFloat16) return KLA_BF16;
-    throw py::type_error(std::string("unsupported dtype torch.") + c10::toString(q.scalar_type()) +
+    throw py::type_error("unsupported dtype " + std::string(py::str(py::cast(q).attr("dtype"))) +
                          "; use float32 or bfloat16");
 }
 
