@@ -19,7 +19,9 @@
 // token-recurrent kernels take without such a limit, every walk tests it, and a chunk
 // that leaves it sets a flag on the device; the token-recurrent kernels are launched
 // behind this path, return at once while the flag is clear, and otherwise overwrite
-// every output and the saved context with theirs.
+// every output and the saved context with theirs.  A q or v that is not finite sets the flag
+// too: the products with the zeros above the diagonal of the chunk's masked matrices would carry
+// it to earlier tokens (v into y; q, in the backward, into the gradients of later ones).
 //
 // Saved context: that of chunk64.hip (lam at every chunk start [BH][nchunk][dk], the
 // states at every chunk start and after the last token [BH][nchunk+1][dk][dv]), followed
@@ -103,6 +105,9 @@ struct Range {
         if (flag && (WIDE ? bad : !(fabs(sum) <= 1.0e300))) *flag = 1;
     }
 };
+
+// four values of a tile, whose sum is finite exactly while they are
+__device__ __forceinline__ bool all_finite(const d4& x) { return fabs((x[0] + x[1]) + (x[2] + x[3])) <= 1.0e300; }
 
 // Per token of a lane, what its walk leaves for the adjoint walk.
 template <int TPG>
@@ -208,7 +213,8 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_state_kernel(Shape s, Win w, 
     __syncthreads();
     double x, z, A;
     chain_start<DK, G>(qs, gq, n, lam0, x, z, A);
-    Range<(DK > 32 || DV > 32)> range;
+    constexpr bool WIDE = DK > 32 || DV > 32;
+    Range<WIDE> range;
 #pragma unroll
     for (int j = 0; j < TPG; ++j) {
         const double av = in.A(j), kv = in.K(j);
@@ -236,6 +242,7 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_state_kernel(Shape s, Win w, 
     constexpr int WD = W / NTN > 0 ? W / NTN : 1;   // waves per 16 key slots
     const rsrc_t rv = make_rsrc(val + (t.tok0 * H + t.h) * DV, (uint32_t)((t.nt - 1) * H * DV + DV) * 4);
     double* out = st.base + (size_t)t.i * st.seq + (size_t)(ADJ ? t.j : t.j + 1) * DK * DV;
+    bool finite = true;
     double av[C / 4];
 #pragma unroll
     for (int k4 = 0; k4 < C / 4; ++k4) av[k4] = sM[(4 * k4 + lk) * PQ + 16 * tn + li];
@@ -246,12 +253,14 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_state_kernel(Shape s, Win w, 
         d4 acc = zero_d4();
 #pragma unroll
         for (int k4 = 0; k4 < C / 4; ++k4) acc = mfma64(av[k4], (double)bv[k4], acc);
+        if constexpr (WIDE && !ADJ) finite = finite && all_finite(acc);   // a v that is not shows in every slot
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = 16 * tn + drow(r, lane);
             out[(size_t)row * DV + 16 * td + li] = ADJ ? acc[r] : acc[r] * sPC[row];
         }
     }
+    if (flag && !finite) *flag = 1;
 }
 
 // Scan of the states along the window's chunks, one thread per element.
@@ -303,7 +312,8 @@ __global__ __launch_bounds__(256) void par_scan_kernel(Win w, int dk, int dv, co
 template <int DK, int DV, bool TI>
 __global__ __launch_bounds__(Par<DK>::NT) void par_out_kernel(Shape s, Win w, Ins g, const float* __restrict__ val,
                                                               const double* __restrict__ lam, size_t lseq, States st,
-                                                              float* __restrict__ y, float* __restrict__ yvar) {
+                                                              float* __restrict__ y, float* __restrict__ yvar,
+                                                              int* flag) {
     using P = Par<DK>;
     constexpr int PQ = P::PQ, TPG = P::TPG, G = P::G, W = P::W, NTD = DV / 16, PS = C + 1, NT = P::NT;
     __shared__ double sQp[C * PQ], sKn[C * PQ], sS[C * PS];
@@ -318,9 +328,11 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_out_kernel(Shape s, Win w, In
     __syncthreads();
     double x, z, A, wv[TPG];
     chain_start<DK, G>(qs, gq, n, lam0, x, z, A);
+    float q0 = 0.f;   // zero exactly while every q is finite
 #pragma unroll
     for (int j = 0; j < TPG; ++j) {
         const double av = in.A(j), kv = in.K(j), qv = in.Q(j);
+        q0 = fmaf(in.q[j], 0.f, q0);
         const double kr = kv * in.R(j);
         const double zn = fma(in.P(j), x, av * av * z);
         const double xn = fma(kr * kv, zn, x);
@@ -391,6 +403,8 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_out_kernel(Shape s, Win w, In
                 bst32(ry, (uint32_t)((16 * ti + drow(r, lane)) * H * DV + 16 * td + li) * 4, (float)acc[m][r]);
         }
     }
+    if constexpr (DK > 32 || DV > 32)   // at the end: before the walk the branch costs registers, and waves
+        if (flag && !(q0 == 0.f)) *flag = 1;
 }
 
 // ---------------------------------------------------------------- backward, contractions and adjoint summary
@@ -549,6 +563,7 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_adj_kernel(Shape s, Win w, In
     // ---- dV, 16 tokens x 16 channels at a time
     {
         const rsrc_t rdv = make_rsrc(dv + v0, vbytes);
+        double sum = 0.0;   // of all outputs: finite exactly while they are
         constexpr int NI = NTD >= W ? 2 : 1, NJ = NTD * 2 / NI;
 #pragma unroll 1
         for (int job = wave; job < NJ; job += W) {
@@ -569,8 +584,23 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_adj_kernel(Shape s, Win w, In
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     bst32(rdv, (uint32_t)((16 * tj + drow(r, lane)) * H * DV + 16 * td + li) * 4, (float)acc[r]);
+                sum += (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
         }
+        // a dY that is not finite has met the zeros of S: the wave's tiles again without them, so that
+        // it stays out of the tokens after its own
+        if (__any(!(fabs(sum) <= 1.0e300)))
+#pragma unroll 1
+            for (int e = 0; e < (NJ - wave + W - 1) / W * NI * 4; ++e) {
+                const int job = wave + e / (NI * 4) * W, tj = NI == 2 ? e / 4 % 2 : job / NTD;
+                const int j = 16 * tj + drow(e % 4, lane), d = 16 * (job % NTD) + li;
+                double x = 0.0;
+#pragma unroll 1   // here and below: unrolled, the registers of this rare path cost the kernel a wave per SIMD
+                for (int m = 0; m < DK; ++m) x = fma(sKn[j * PQ + m], G0[(size_t)m * DV + d] * sPC[m], x);
+#pragma unroll 1
+                for (int i = j; i < C; ++i) x = fma(sS[i * PS + j], (double)sD[i * PD + d], x);
+                bst32(rdv, (uint32_t)(j * H * DV + d) * 4, (float)x);
+            }
     }
     // ---- X, Y: wave's key-slot tile nn and token tiles tq0 .. tq0 + NX - 1
     constexpr int NX = 2 * NTN >= 2 * W ? 2 : 1;
@@ -943,7 +973,7 @@ hipError_t fwd_par(const Shape& s, const FwdArgs& a, void* saved, void* ws, int*
             hipLaunchKernelGGL(par_scan_kernel<false>, blocks(w.nb * ST, 256), dim3(256), 0, st, w, DK, DV, pc, sts,
                                c0 == 0, a.eta0, cst, last ? a.etaT : nullptr);
             hipLaunchKernelGGL((par_out_kernel<DK, DV, TI>), grid, dim3(NT), 0, st, s, w, in, v, lam, lseq, sts,
-                               static_cast<float*>(a.y), a.yvar);
+                               static_cast<float*>(a.y), a.yvar, flag);
         }
     return hipGetLastError();
 }

@@ -159,3 +159,40 @@ def test_forward_windows_agree(kla):
     torch.cuda.synchronize()
     for n in ("y", "yvar", "lamT", "etaT"):
         assert torch.equal(one[n], two[n]), n
+
+
+# A value that is not finite reaches the tokens that the recursion carries it to and no other: y
+# and yvar of its own and later tokens, gradients of its own and earlier ones (dv and dr after it,
+# and everything else there, stay those of the oracle).  150 tokens: the second of three tiles of
+# 16 in its chunk, with whole chunks on both sides.
+@pytest.mark.parametrize("name", ["v", "q", "dy", "dyvar"])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 16)])
+def test_non_finite_values_stay_causal(kla, name, bad, dk, dv):
+    log(f"non-finite {name} {bad} {dk} x {dv}")
+    B, T, H, t = 2, 150, 2, 53
+    case = K.random_case(B, T, H, dk, dv, "f32", seed=9, dist="lm")
+    e = _extras(B, T, H, dk, dv, 9)
+    c = {n: case[n].copy() for n in TOKEN + ("dy",)}
+    c["dyvar"] = e["dyvar"].copy()
+    c[name][(1, t, 1) if name == "dyvar" else (1, t, 1, 3)] = bad
+    x = {n: to_torch(c[n], "f32", DEV) for n in TOKEN + ("dy",)}
+    d = {n: _f32(v) for n, v in dict(e, dyvar=c["dyvar"]).items()}
+    args = tuple(x[n] for n in TOKEN) + (d["lam0"], d["eta0"])
+    out = kla.kla_forward(*args, want_var=True, save=True)
+    free = kla.kla_forward(*args, want_var=True)
+    got = kla.kla_backward(*args, x["dy"], d["dlamT"], d["detaT"], saved=out["saved"], dyvar=d["dyvar"])
+    again = kla.kla_backward(*args, x["dy"], d["dlamT"], d["detaT"], dyvar=d["dyvar"])
+    oa = tuple(c[n] for n in TOKEN) + (e["lam0"], e["eta0"])
+    with np.errstate(all="ignore"):
+        ref = oracle.forward(*oa)
+        rg = oracle.backward(*oa, c["dy"], e["dlamT"], e["detaT"], dyvar=c["dyvar"])
+    for res, want, names in ((out, ref, ("y", "yvar", "lamT", "etaT")), (free, ref, ("y", "yvar", "lamT", "etaT")),
+                             (got, rg, ("dq", "dk", "dv", "da", "dp", "dr")), (again, rg, ("dq", "dk", "dv", "da", "dp", "dr"))):
+        for n in names:
+            o, w = to_np(res[n]), np.asarray(want[n])
+            keep = np.isfinite(w)
+            assert keep.mean() > 0.5, n
+            assert np.all(np.isfinite(o[keep])), f"{n}: not finite at {np.argwhere(keep & ~np.isfinite(o))[:4].tolist()}"
+            err = rel_err(o[keep], w[keep])
+            assert err <= 1e-4, f"{n}: {err:.2e}"   # as the token-recurrent kernels' (see above)
