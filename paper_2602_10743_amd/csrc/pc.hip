@@ -348,9 +348,17 @@ hipError_t dispatch_pc(const Shape& s, A&&... args) {
     return hipErrorInvalidValue;
 }
 
-// Whether the channels of all heads leave the chip's 1024 SIMDs short of a wave each at 8 lanes
-// per channel.
-bool few_channels(const Shape& s) { return (long)s.B * s.H * s.dv * 8 < 64 * 1024; }
+// Whether the channels of all heads leave the chip short of waves at 8 lanes per channel.  The
+// lines lie where the two forms cross (256 tokens, few against many, us): up to 32 key slots past
+// 7680 channels (dk = 32: 77 against 80; at 8192 every SIMD has a wave at 8 lanes), fp32 at dk = 32
+// at 6400 (6144: 104 against 113, 6400: 127 against 111); above, where a channel takes 64 lanes,
+// bf16 at 4608 (64 x 64: 4096: 109 against 133, 5120: 147 against 133; 128 x 128: 213 against 244,
+// 270 against 237; 7680: 403 against 247), fp32 at 5632 (128 x 128: 359 against 450, 6400: 471
+// against 459).
+bool few_channels(const Shape& s) {
+    const long most = s.dk == 16 || (s.dk == 32 && s.bf16) ? 8192 : s.bf16 ? 4608 : s.dk == 32 ? 6400 : 5632;
+    return (long)s.B * s.H * s.dv < most;
+}
 
 template <typename S, int DK, int DV>
 struct FwdPc {
