@@ -91,9 +91,13 @@ struct PcFwd {
 // workgroups hide the wait and the registers are better spent on them); the elements are updated,
 // the partial readouts summed over the lanes of a channel and y, yvar written from LDS.
 // Bound by VALU issue where the channels fill the chip (18 slots per element) and by the
-// latency of a token's step where they do not: B2 T1024 H8 64 x 64 on 8 lanes per channel (128
+// latency of a token's step where they do not (LEAN, fp64 at dk = 128 with more than one workgroup
+// per CU: the variance's sums are formed also when nobody asks for them, since put off behind that
+// question they hold every element's factors, 310 registers and one wave per SIMD against 228 and
+// two: 200 heads of 128 x 128 over 256 tokens 1476 -> 1256 us, but 128 heads of 128 x 64, one workgroup
+// per CU, 389 -> 470): B2 T1024 H8 64 x 64 on 8 lanes per channel (128
 // waves, loads waited for in every block) 838 us, on 32 lanes 229, on 64 193 us.
-template <typename S, int DK, int DV, bool TI, bool FEW>
+template <typename S, int DK, int DV, bool TI, bool FEW, bool LEAN>
 __global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shape s, FwdArgs g,
                                                                          typename acc<S>::type* ck) {
     using T_ = typename storage<S>::type;
@@ -207,7 +211,7 @@ __global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shap
             ya = lane_sum<LG>(ya);
             // every lane writes (no lane mask): the channel's last lane its sums, the others a junk slot
             *(ng == LG - 1 ? &s_y[bb][t][c] : &s_junk[0][tid]) = (float)ya;
-            if (want_w) {
+            if (LEAN || want_w) {
                 wa = lane_sum<LG>(wa);
                 *(ng == LG - 1 ? &s_w[bb][t][c] : &s_junk[1][tid]) = (float)wa;
             }
@@ -362,16 +366,22 @@ bool few_channels(const Shape& s) {
 
 template <typename S, int DK, int DV>
 struct FwdPc {
-    template <bool TI, bool FEW>
+    template <bool TI, bool FEW, bool LEAN = false>
     static hipError_t go(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
         using P = PcFwd<DK, DV, FEW>;
-        hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, TI, FEW>), dim3((unsigned)(s.B * s.H * (DV / P::CT))),
+        hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, TI, FEW, LEAN>), dim3((unsigned)(s.B * s.H * (DV / P::CT))),
                            dim3(P::NTHR), 0, st, s, a, static_cast<typename acc<S>::type*>(ck));
         return hipGetLastError();
     }
+    template <bool TI>
+    static hipError_t run_ti(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
+        if (few_channels(s)) return go<TI, true>(s, a, ck, st);
+        if constexpr (DK == 128 && std::is_same<S, f32_t>::value)
+            if (s.B * s.H * (DV / PcFwd<DK, DV, false>::CT) > 256) return go<TI, false, true>(s, a, ck, st);
+        return go<TI, false>(s, a, ck, st);
+    }
     static hipError_t run(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
-        if (few_channels(s)) return a.ou_a ? go<true, true>(s, a, ck, st) : go<false, true>(s, a, ck, st);
-        return a.ou_a ? go<true, false>(s, a, ck, st) : go<false, false>(s, a, ck, st);
+        return a.ou_a ? run_ti<true>(s, a, ck, st) : run_ti<false>(s, a, ck, st);
     }
 };
 
