@@ -405,17 +405,23 @@ struct FwdPc {
 // joint sum per segment 477, with a branch-free walk of whole segments 408 us.
 template <int DK, int DV, bool FEW, typename A = float>
 struct PcLanes {
-    static constexpr int LMAX = FEW ? 64 : 32;
-    static constexpr int LPC = DK < LMAX ? DK : LMAX;
-    static constexpr int NPER = DK / LPC;
     // fp64 arithmetic doubles the trajectory registers: 16 channels from dk = 64 on
     static constexpr int CBMAX = DK == 128 || (DK == 64 && sizeof(A) == 8) ? 16 : 32;
     static constexpr int CBFEW = DV / 8 > 8 ? DV / 8 : 8;
+    // and no 1024 threads of 128 registers, which spill (4 heads of 128 x 128 over 256 tokens on 64
+    // lanes 624 us, on 32 551; of 64 x 128 303 and 257)
+    static constexpr int LMAX = FEW && (sizeof(A) == 4 || CBFEW * 64 <= 512) ? 64 : 32;
+    static constexpr int LPC = DK < LMAX ? DK : LMAX;
+    static constexpr int NPER = DK / LPC;
     static constexpr int CB = FEW ? CBFEW : DV < CBMAX ? DV : CBMAX;
     static constexpr int NTHR = LPC * CB;
     // tokens whose key-slot values are held for one joint sum: a whole segment where they fit
     // 64 KiB (two otherwise, in turn): one barrier per segment instead of one per token
     static constexpr int NRED = FEW && CB * 4 * DK * 4 * kCK <= 64 * 1024 ? kCK : 2;
+    // fp64 at dk = 128 spills its trajectory: one walk with guards for whole and short segments, and a
+    // uniform token in the sums, leave it the most registers (200 heads of 128 x 128 over 256 tokens
+    // 4925 -> 4701 us; the other widths lose 1 to 3% by either)
+    static constexpr bool TIGHT = NRED == 2 && sizeof(A) == 8 && DK == 128;
 };
 
 template <typename S, int DK, int DV, bool TI, bool FEW>
@@ -518,8 +524,8 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
             constexpr int PER = NQ * DK, RPT = ((NRED == kCK ? kCK : 1) * PER + NTHR - 1) / NTHR;
 #pragma unroll
             for (int m = 0; m < RPT; ++m) {
-                const int it = tid + NTHR * m, j = j0 + it / PER, idx = it % PER;
-                if (j >= j0 + n) continue;
+                const int it = tid + NTHR * m, j = PL::TIGHT ? j0 : j0 + it / PER, idx = PL::TIGHT ? it : it % PER;
+                if (PL::TIGHT ? RPT * NTHR != PER && idx >= PER : j >= j0 + n) continue;
                 float acc = 0.f;
 #pragma unroll
                 for (int cc = 0; cc < CB; ++cc) acc += (&s_red[j % NRED][cc][0][0])[idx];
@@ -603,7 +609,7 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
                 }
             }
         };
-        if (nt == kCK)
+        if (!PL::TIGHT && nt == kCK)
             walk(std::true_type{});
         else
             walk(std::false_type{});

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,dk,dv,dtype", [(19, 16, 128, "bf16"), (8, 128, 128, "bf16"), (33, 64, 64, "f32"),
-                                           (17, 32, 32, "bf16"), (9, 128, 16, "f32")])
+                                           (17, 32, 32, "bf16"), (9, 128, 16, "f32"),
+                                           (11, 128, 128, "f32"), (10, 64, 128, "f32")])
 @pytest.mark.parametrize("ou", [False, True])
 def test_few_and_many_channels_agree(T, dk, dv, dtype, ou):
     if not torch.cuda.is_available():
