@@ -1038,6 +1038,8 @@ hipError_t bwd_par(const Shape& s, const BwdArgs& a, const void* saved, void* ws
 //   never (163 against 255 us at 16).
 bool c64p_supported(const Shape& s) {
     if (s.bf16 || s.T <= 2 * C) return false;
+    // a chunk's rows lie within 32 bits of byte offsets
+    if ((size_t)s.H * (s.dk > s.dv ? s.dk : s.dv) * C * sizeof(float) > (size_t)1 << 32) return false;
     if (wide(s)) return true;
     return chunks_of(s) * (8.3 - (s.dk == 16 ? 0.034 : 0.055) * s.B * s.H) > 33.0;
 }

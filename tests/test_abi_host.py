@@ -242,6 +242,17 @@ def test_chunk_parallel_fp32_contexts_and_workspaces(lib):
     assert lib.kla_backward_noalloc(ctypes.byref(over), *ptrs, None) == 5        # KLA_ERR_WORKSPACE, as before
 
 
+def test_very_many_heads_stay_token_recurrent(lib):
+    """The chunk-parallel path addresses a chunk's 32 rows by 32-bit byte offsets; the token-recurrent
+    kernels go further, so past 2^32 bytes of heads the call is theirs (its context says so)."""
+    import paper_2602_10743_amd as K
+    B, T, dk, dv = 1, 65, 128, 64
+    for H, par in ((262144, True), (262145, False)):
+        rec = (B * T * H * dk + B * H * 2 * dk * dv) * 8
+        assert (K.kla_saved_bytes(_desc(B, T, H, dk, dv, 0)) != rec) == par
+        assert (K.kla_forward_workspace(_desc(B, T, H, dk, dv, 0)) > 256) == par
+
+
 def test_segment_backward_workspace_is_bounded(lib):
     """bf16, few sequences: the segments side by side take at most 256 MiB however long the
     sequences (beside them only the whole walk's dr parts may be larger)."""
