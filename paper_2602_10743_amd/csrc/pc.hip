@@ -403,17 +403,20 @@ struct FwdPc {
 // more parts to combine (4 channels gain in the kernel what the combine then loses).  B2 T1024 H8
 // 64 x 64: 32 workgroups of 32 channels 1009 us, 128 of 8 (32 lanes) 583, on 64 lanes with one
 // joint sum per segment 477, with a branch-free walk of whole segments 408 us.
+// fp64 arithmetic doubles the trajectory registers: 16 channels from dk = 64 on.
+constexpr int pc_channels(int dk, int dv, bool fp64, bool few) {
+    const int most = few ? (dv / 8 > 8 ? dv / 8 : 8) : dk == 128 || (dk == 64 && fp64) ? 16 : 32;
+    return dv < most ? dv : most;
+}
+
 template <int DK, int DV, bool FEW, typename A = float>
 struct PcLanes {
-    // fp64 arithmetic doubles the trajectory registers: 16 channels from dk = 64 on
-    static constexpr int CBMAX = DK == 128 || (DK == 64 && sizeof(A) == 8) ? 16 : 32;
-    static constexpr int CBFEW = DV / 8 > 8 ? DV / 8 : 8;
-    // and no 1024 threads of 128 registers, which spill (4 heads of 128 x 128 over 256 tokens on 64
-    // lanes 624 us, on 32 551; of 64 x 128 303 and 257)
-    static constexpr int LMAX = FEW && (sizeof(A) == 4 || CBFEW * 64 <= 512) ? 64 : 32;
+    static constexpr int CB = pc_channels(DK, DV, sizeof(A) == 8, FEW);
+    // no 1024 threads of 128 registers for fp64 arithmetic, they spill (4 heads of 128 x 128 over 256
+    // tokens on 64 lanes 624 us, on 32 551; of 64 x 128 303 and 257)
+    static constexpr int LMAX = FEW && (sizeof(A) == 4 || CB * 64 <= 512) ? 64 : 32;
     static constexpr int LPC = DK < LMAX ? DK : LMAX;
     static constexpr int NPER = DK / LPC;
-    static constexpr int CB = FEW ? CBFEW : DV < CBMAX ? DV : CBMAX;
     static constexpr int NTHR = LPC * CB;
     // tokens whose key-slot values are held for one joint sum: a whole segment where they fit
     // 64 KiB (two otherwise, in turn): one barrier per segment instead of one per token
@@ -667,13 +670,9 @@ __global__ __launch_bounds__(256) void pc_key_combine_kernel(const float* __rest
     }
 }
 
-// channels per workgroup of the backward by default (PcLanes), and whether it takes fewer
-int pc_cb(const Shape& s) {
-    const int cbmax = s.dk == 128 || (s.dk == 64 && !s.bf16) ? 16 : 32;
-    return s.dv < cbmax ? s.dv : cbmax;
-}
+// whether the backward takes fewer channels per workgroup than its default
 bool few_bwd(const Shape& s) {
-    return s.B * s.H * (s.dv / pc_cb(s)) < 128;
+    return s.B * s.H * (s.dv / pc_channels(s.dk, s.dv, !s.bf16, false)) < 128;
 }
 
 template <typename S, int DK, int DV>
@@ -729,7 +728,7 @@ size_t pc_ou_part_bytes(const Shape& s) {
 }
 
 size_t pc_bwd_workspace(const Shape& s) {
-    const int cb = few_bwd(s) ? (s.dv / 8 > 8 ? s.dv / 8 : 8) : pc_cb(s);
+    const int cb = pc_channels(s.dk, s.dv, !s.bf16, few_bwd(s));   // as BwdPc::go: one part per tile of them
     return (size_t)(s.dv / cb) * 4 * part_stride((size_t)s.B * s.T * s.H * s.dk) * sizeof(float);
 }
 
