@@ -117,7 +117,7 @@ struct Kept {
 
 // ---------------------------------------------------------------- forward, precision
 // The chunk's 2x2 map of (x, z) (images of (1, 0) and (0, 1), scaled by the largest entry
-// after each group: the map is projective) and its abar product, scaled alike.
+// after each group: the map is projective).
 template <int DK, bool TI>
 __global__ __launch_bounds__(Par<DK>::NT) void par_map_kernel(Shape s, Win w, Ins g, double* __restrict__ map) {
     using P = Par<DK>;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_map_kernel(Shape s, Win w, In
     group_transfer(in, qs, gq, n);
     __syncthreads();
     if (gq) return;
-    double x0 = qs[0 * DK + n], z0 = qs[1 * DK + n], x1 = qs[2 * DK + n], z1 = qs[3 * DK + n], A = qs[4 * DK + n];
+    double x0 = qs[0 * DK + n], z0 = qs[1 * DK + n], x1 = qs[2 * DK + n], z1 = qs[3 * DK + n];
 #pragma unroll
     for (int g2 = 1; g2 < P::G; ++g2) {
         const double* m = qs + g2 * 5 * DK;
@@ -141,14 +141,12 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_map_kernel(Shape s, Win w, In
         z0 = nz0 * sc;
         x1 = nx1 * sc;
         z1 = nz1 * sc;
-        A *= m[4 * DK + n] * sc;
     }
-    double* o = map + ((size_t)t.i * w.nc + t.j) * 5 * DK + n;
+    double* o = map + ((size_t)t.i * w.nc + t.j) * 4 * DK + n;
     o[0 * DK] = x0;
     o[1 * DK] = z0;
     o[2 * DK] = x1;
     o[3 * DK] = z1;
-    o[4 * DK] = A;
 }
 
 // lam at the window's chunk starts, lam[(i lseq + j) dk + n]; carry[bh dk + n]: lam at the
@@ -163,7 +161,7 @@ __global__ __launch_bounds__(64) void par_lam_kernel(Win w, int dk, const double
     const int n = i % dk, il = i / dk;
     const size_t e = (size_t)w.bh0 * dk + i;
     double x = w.c0 ? carry[i] : lam0 ? (double)lam0[e] : 1.0;
-    const double* m = map + (size_t)il * w.nc * 5 * dk + n;
+    const double* m = map + (size_t)il * w.nc * 4 * dk + n;
     double* o = lam + (size_t)il * lseq + n;
     constexpr int U = 8;   // the maps of U chunks are loaded while those of the U before are applied
     double b[U][4], nx[U][4];
@@ -171,7 +169,7 @@ __global__ __launch_bounds__(64) void par_lam_kernel(Win w, int dk, const double
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) d[u][r] = m[((size_t)min(j0 + u, w.nc - 1) * 5 + r) * dk];
+            for (int r = 0; r < 4; ++r) d[u][r] = m[((size_t)min(j0 + u, w.nc - 1) * 4 + r) * dk];
     };
     load(nx, 0);
     for (int j0 = 0; j0 < w.nc; j0 += U) {
@@ -409,9 +407,8 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_out_kernel(Shape s, Win w, In
 
 // ---------------------------------------------------------------- backward, contractions and adjoint summary
 // The lane's walk with everything the adjoint needs kept (see chunk64.hip).
-template <int DK, int TPG, bool TI, typename F>
-__device__ __forceinline__ void walk_kept(const WalkIn<DK, TPG, TI>& in, double x, double z, double A, Kept<TPG>& kp,
-                                          F&& each) {
+template <int DK, int TPG, bool TI>
+__device__ __forceinline__ void walk_kept(const WalkIn<DK, TPG, TI>& in, double x, double z, double A, Kept<TPG>& kp) {
     double izp = rcpa(z);
 #pragma unroll
     for (int j = 0; j < TPG; ++j) {
@@ -421,8 +418,7 @@ __device__ __forceinline__ void walk_kept(const WalkIn<DK, TPG, TI>& in, double 
         const double xn = fma(kr * kv, zn, x);
         const double An = A * av;
         const double R = rcpa(xn * An), iz = rcpa(zn);
-        const double AR = An * R, XR = xn * R;   // 1 / x_t, 1 / A_t
-        each(j, in.Q(j) * An * AR, kr * zn * XR);
+        const double AR = An * R;   // 1 / x_t
         kp.lam_p[j] = x * izp;
         kp.P[j] = An * iz;
         kp.il[j] = zn * AR;
@@ -662,7 +658,7 @@ __global__ __launch_bounds__(Par<DK>::NT) void par_adj_kernel(Shape s, Win w, In
     __syncthreads();
     // ---- the chunk's composed adjoint step
     Kept<TPG> kp;
-    walk_kept(in, x0, z0, A0, kp, [](int, double, double) {});
+    walk_kept(in, x0, z0, A0, kp);
     double dqt[TPG], dkh[TPG];
     double* o = xy + ((size_t)t.i * w.nc + t.j) * 2 * C * DK;
 #pragma unroll
@@ -784,7 +780,7 @@ __global__ __launch_bounds__((Par<DK, true>::NT)) void par_grad_kernel(Shape s, 
     double x, z, A;
     chain_start<DK, G>(qs, gq, n, lam0, x, z, A);
     Kept<TPG> kp;
-    walk_kept(in, x, z, A, kp, [](int, double, double) {});
+    walk_kept(in, x, z, A, kp);
     adjoint_summary(in, kp, dqt, dkh, gv, qa, gq, n);
     __syncthreads();
 #pragma unroll
@@ -902,7 +898,7 @@ bool wide(const Shape& s) { return s.dk > 32 || s.dv > 32; }
 
 Plan fwd_plan(const Shape& s, bool save, size_t limit) {
     const size_t d = sizeof(double), st = (size_t)s.dk * s.dv * d;
-    const size_t chunk = (6 + (save ? 0 : 1)) * s.dk * d + (save ? 0 : st);   // map, P_C, lam; states
+    const size_t chunk = (5 + (save ? 0 : 1)) * s.dk * d + (save ? 0 : st);   // map, P_C, lam; states
     auto seq = [&](int) { return s.dk * d + st + (save ? 0 : st); };          // lam and state carries, one more slot
     return plan(s.B * s.H, chunks_of(s), chunk, seq, limit);
 }
@@ -950,7 +946,7 @@ hipError_t fwd_par(const Shape& s, const FwdArgs& a, void* saved, void* ws, int*
     const float* v = static_cast<const float*>(a.v);
     Carver carve{static_cast<char*>(ws)};
     constexpr size_t ST = (size_t)DK * DV;
-    double* map = carve((size_t)pl.nb * pl.nc * 5 * DK);
+    double* map = carve((size_t)pl.nb * pl.nc * 4 * DK);
     double* pc = carve((size_t)pl.nb * pl.nc * DK);
     double* clam = carve((size_t)pl.nb * DK);
     double* cst = carve((size_t)pl.nb * ST);
