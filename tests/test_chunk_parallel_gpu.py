@@ -161,10 +161,58 @@ def test_forward_windows_agree(kla):
         assert torch.equal(one[n], two[n]), n
 
 
+# OU gates, whose sums are carried over windows and placed by batches, with a belief, its gradient
+# and dyvar: a sequence of two windows against its halves (joined through fp32 values, so to TOL),
+# and two batches of sequences against each sequence alone (the same kernels on the same chunks,
+# bit for bit; the parameters' sums over the sequences to TOL).
+@pytest.mark.parametrize("B,T,halves", [(1, 48000, True), (6, 9600, False)])
+def test_ou_windows_and_batches_agree(kla, B, T, halves):
+    log(f"OU windows B{B} T{T} 128 x 128")
+    d = 128
+    g = torch.Generator(device=DEV).manual_seed(8)
+    z = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    x = dict(q=z(B, T, 1, d), k=torch.nn.functional.normalize(z(B, T, 1, d), dim=-1), v=z(B, T, 1, d),
+             r=0.1 + z(B, T, 1).abs(), dy=z(B, T, 1, d), dyvar=z(B, T, 1))
+    par = [1 + 2 * torch.sigmoid(z(1, d)), z(1, d).abs() + 1, 0.001 + 0.03 * z(1, d).abs()]
+    lam0, eta0, dlamT, detaT = z(B, 1, d).abs() + 0.5, z(B, 1, d, d), z(B, 1, d), z(B, 1, d, d)
+
+    def fwd(b, t, l0, e0):
+        ins = [x[n][b, t].contiguous() for n in ("q", "k", "v")] + par + [x["r"][b, t].contiguous(), l0, e0]
+        return ins, kla.kla_forward_ou(*ins, save=True)
+
+    def bwd(ins, out, b, t, dl, de):
+        return kla.kla_backward_ou(*ins, x["dy"][b, t].contiguous(), dl, de, saved=out["saved"],
+                                   dyvar=x["dyvar"][b, t].contiguous())
+
+    every, m = slice(0, T), T // 2 // 32 * 32
+    ref = bwd(*fwd(slice(0, B), every, lam0, eta0), slice(0, B), every, dlamT, detaT)
+    params = ("da", "dp", "ddelta")
+    if halves:
+        one, two, b = slice(0, m), slice(m, T), slice(0, B)
+        i1, o1 = fwd(b, one, lam0, eta0)
+        g2 = bwd(*fwd(b, two, o1["lamT"], o1["etaT"]), b, two, dlamT, detaT)
+        g1 = bwd(i1, o1, b, one, g2["dlam0"], g2["deta0"])
+        got = {n: torch.cat([g1[n], g2[n]], 1) for n in ("dq", "dk", "dv", "dr")}
+        got.update(dlam0=g1["dlam0"], deta0=g1["deta0"], **{n: g1[n] + g2[n] for n in params})
+        for n in got:
+            a, w = got[n].double(), ref[n].double()
+            assert float((a - w).norm() / w.norm()) <= TOL, n
+    else:
+        parts = []
+        for i in range(B):
+            b = slice(i, i + 1)
+            parts.append(bwd(*fwd(b, every, lam0[b], eta0[b]), b, every, dlamT[b], detaT[b]))
+        for n in ("dq", "dk", "dv", "dr", "dlam0", "deta0"):
+            assert torch.equal(torch.cat([p[n] for p in parts]), ref[n]), n
+        for n in params:
+            a, w = sum(p[n].double() for p in parts), ref[n].double()
+            assert float((a - w).norm() / w.norm()) <= TOL, n
+
+
 # A value that is not finite reaches the tokens that the recursion carries it to and no other: y
 # and yvar of its own and later tokens, gradients of its own and earlier ones (dv and dr after it,
-# and everything else there, stay those of the oracle).  150 tokens: the second of three tiles of
-# 16 in its chunk, with whole chunks on both sides.
+# and everything else there, stay those of the oracle).  Token 53 of 150: in the second of its
+# chunk's two tiles of 16, with tokens of the tile and whole chunks on both sides.
 @pytest.mark.parametrize("name", ["v", "q", "dy", "dyvar"])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 16)])
