@@ -174,23 +174,34 @@ __global__ __launch_bounds__(256) void seg_state_scan_kernel(int nbh, int DK, in
 
 // The cut of a shape.  One workgroup fills a CU, so segments are added until every CU has
 // one (as many workgroups as fit 256, one per head and segment where dv = 128 runs wide).
-// Microseconds, measured at 128 x 128: a chunk round of the exact pass 3.1 (3.6 wide), of the
-// state-only pass 1.7; the four kernels around them and their launches 25.  Against the whole
-// walk: 3001 tokens of 16 heads 238 -> 75 us, with OU gates and a saved context (B2 T2048 H16)
-// 167 -> 85 us; 65536 tokens, 8 segments of two 64-channel tiles -> 16 wide ones, 1460 -> 1067 us
-// (kernel times).
+// The costs (us per chunk round, and of the four kernels around the passes and their launches) are
+// those with which the rule chose best over 1 to 128 heads, 128 to 8192 tokens and ten pairs of
+// widths, each timed whole and cut: at most 4% (32 x 128, 80 heads: 7%) from the better of the
+// two.  With one set of rounds for all widths, those of few workgroups, 100 heads of 64 x 64 over 2048
+// tokens took two segments, 148 us against 135, and 128 of 128 x 128 over 4096 with a saved context
+// 589 against 446.
+// Against the whole walk: 3001 tokens of 16 heads 238 -> 75 us, with OU gates and a saved context
+// (B2 T2048 H16) 167 -> 85 us; 65536 tokens, 8 segments of two 64-channel tiles -> 16 wide ones,
+// 1460 -> 1067 us (kernel times).
 Cut cut_of(const Shape& s) {
     const int nct = (s.T + kCS - 1) / kCS, bh = s.B * s.H;
     Cut c{1, nct, 1, 1};
     if (!chunked_supported(s) || nct < 4) return c;
     const int ntile = s.dv == 128 ? 2 : 1;
-    auto rounds = [&](int wg) { return (wg + 255) / 256; };
-    double best = 0.92 * nct * (chunked_wide(s, 1) ? 3.6 * rounds(bh) : 3.1 * rounds(bh * ntile));
+    struct Us {
+        double walk, exact, wide, state, fixed;   // whole walk, exact pass (wide), state-only pass
+    };
+    const Us us = s.dk == 128 ? Us{2.5, 2.8, 4.6, 1.7, 20.0}
+                  : s.dk == 64 ? Us{1.8, 2.0, 3.0, 1.5, 19.0}
+                               : Us{1.65, 1.6, 1.6, 1.5, 15.0};
+    auto rounds = [](int wg) { return (wg + 255) / 256; };
+    double best = nct * us.walk;
     for (int wg : {256 / (bh * ntile), 256 / bh}) {
         if (wg < 2) continue;
         const int lc = (nct + wg - 1) / wg, ns = (nct + lc - 1) / lc;
         if (ns < 2) continue;
-        const double cost = lc * (1.7 + (chunked_wide(s, ns) ? 3.6 * rounds(bh * ns) : 3.1 * rounds(bh * ns * ntile))) + 25.0;
+        const double exact = chunked_wide(s, ns) ? us.wide * rounds(bh * ns) : us.exact * rounds(bh * ns * ntile);
+        const double cost = lc * (us.state + exact) + us.fixed;
         if (cost < best) {
             best = cost;
             c.ns = ns;
