@@ -916,7 +916,9 @@ size_t seg_bytes(const Shape& s, int w, int lc) { return SegBufs(s, w, lc, nullp
 
 // Microseconds per chunk round at 128 x 128: value side 3.3 (3.8 wide), its state-only pass 2.0,
 // key side 7.4 (SPLIT 6.6); the gradient kernel 1.1 ns per token and head; the other kernels and
-// launches of a window 40.  One workgroup per CU, as in the forward.  ns and lc do not depend on
+// launches of a window 40.  With dk = 128 and dv <= 64 the contractions take less of it all and the
+// rest more, 1.6 ns and 28 (with the figures of 128 x 128, 80 heads of 128 x 32 over 2048 tokens took
+// three segments, 472 us against 419).  One workgroup per CU, as in the forward.  ns and lc do not depend on
 // limit (bytes the windows may use), so that the results do not; under a limit that cuts the
 // windows too short to fill the chip the whole walk may be left as the faster one.
 BwdCut bwd_cut(const Shape& s, size_t limit) {
@@ -925,10 +927,12 @@ BwdCut bwd_cut(const Shape& s, size_t limit) {
     if (nct < 4) return whole;
     auto rounds = [](int wg) { return (wg + 255) / 256; };
     auto dv_us = [&](int ns) { return chunked_wide(s, ns) ? 3.8 * rounds(bh * ns) : 3.3 * rounds(bh * ns * ntile); };
+    const bool lean = s.dk == 128 && s.dv <= 64;
+    const double grad_us = lean ? 1.6e-3 : 1.1e-3, fixed_us = lean ? 28.0 : 40.0;
     auto cost = [&](const BwdCut& c) {
         const int full = c.ns / c.w, rest = c.ns % c.w;
-        auto window = [&](int w) { return c.lc * (2.0 + dv_us(w) + 6.6 * rounds(bh * w * nnt)) + 40.0; };
-        return full * window(c.w) + (rest ? window(rest) : 0.0) + 1.1e-3 * bh * s.T * s.dk / 128;
+        auto window = [&](int w) { return c.lc * (2.0 + dv_us(w) + 6.6 * rounds(bh * w * nnt)) + fixed_us; };
+        return full * window(c.w) + (rest ? window(rest) : 0.0) + grad_us * bh * s.T * s.dk / 128;
     };
     const double walk = 0.92 * nct * (dv_us(1) + 7.4 * rounds(bh * nnt));
     double best = walk;
