@@ -64,9 +64,9 @@ SUMMARY_KEY = "traffic_bytes_per_call"
 DIGEST_SOURCES = ("kla_api.cpp", "kla_internal.hpp", "kla_device.hpp", "kla_buf.hpp", "kla_mfma.hpp",
                   "kla_chunk.hpp", "chunk_fwd.hip", "chunk_bwd_dv.hip", "chunk_bwd_dk.hip", "ou.hip",
                   "validate.hip")
-# ... and of the token-recurrent kernels (the state-tracking workload)
-DIGEST_SOURCES_A5 = ("kla_api.cpp", "kla_internal.hpp", "kla_device.hpp", "kla_buf.hpp", "chunk64.hip",
-                     "validate.hip")
+# ... and of the chunked fp64 kernels (the state-tracking workload)
+DIGEST_SOURCES_A5 = ("kla_api.cpp", "kla_internal.hpp", "kla_device.hpp", "kla_buf.hpp", "kla_chunk64.hpp",
+                     "chunk64.hip", "validate.hip")
 
 
 def code_text(text: str) -> str:

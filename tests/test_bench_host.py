@@ -9,6 +9,7 @@
 """
 import importlib.util
 import os
+import re
 import subprocess
 import sys
 
@@ -69,6 +70,15 @@ def test_digest_sources_exist(names):
     for name in names:
         assert os.path.exists(os.path.join(ROOT, "paper_2602_10743_amd", "csrc", name)), name
     assert "chunk64.hip" in traffic.DIGEST_SOURCES_A5 and "chunk64.hip" not in traffic.DIGEST_SOURCES
+
+
+@pytest.mark.parametrize("names", [traffic.DIGEST_SOURCES, traffic.DIGEST_SOURCES_A5])
+def test_digest_holds_the_headers_of_its_sources(names):
+    csrc = os.path.join(ROOT, "paper_2602_10743_amd", "csrc")
+    for name in names:
+        for inc in re.findall(r'#include "([^"]+)"', open(os.path.join(csrc, name)).read()):
+            if inc != "kla.h":
+                assert inc in names, f"{name} includes {inc}"
 
 
 def test_digest_ignores_comments_only():
