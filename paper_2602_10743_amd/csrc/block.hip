@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(int B, int T, int C, cons
 // Four channels per thread in both types: the gradients, taps and windows of eight bf16 channels
 // held 204 registers and 40 KB of LDS per block, two waves per SIMD, too few to cover the loads
 // (79 us at 8 x 2048 tokens of 2048 channels, bytes 39 us at the copy rate); four hold 98, four
-// waves per SIMD, 66 us.  Runs of 32 tokens (fewer halo tokens) gain 1% there and halve the
+// waves per SIMD, 66 us (73 and 60 with part of the inputs in the Infinity Cache).  Runs of 32 tokens (fewer halo tokens) gain 1% there and halve the
 // blocks of a short batch.
 template <typename S>
 __global__ __launch_bounds__(256) void conv_bwd_kernel(int B, int T, int C, const void* __restrict__ x,

@@ -468,8 +468,8 @@ __device__ __forceinline__ void load_gv(float (&gv)[TPG], const float* dyvar, co
 // xy [2][C][dk] for par_grad_kernel.  X and Y stay in the accumulators until every wave is
 // done with Qp and Kn and then take their place in LDS.  The state operands of X and Y run
 // along a row of H_c / G_c per lane (lane group g takes channels g dv / 4 ..; the
-// contraction index may be permuted), so each lane reads whole cache lines; 672 products of
-// 64 cycles over four matrix cores at 64 x 64, 4.5 us.
+// contraction index may be permuted), so each lane reads whole cache lines; 624 products of
+// 64 cycles over four matrix cores at 64 x 64, 4.2 us.
 template <int DK, int DV, bool TI>
 __global__ __launch_bounds__(Par<DK>::NT) void par_adj_kernel(Shape s, Win w, Ins g, const float* __restrict__ val,
                                                               const float* __restrict__ dy,
@@ -749,7 +749,8 @@ __global__ __launch_bounds__(64) void par_carry_kernel(Win w, int dk, int dv, bo
 // The gradients of a chunk's tokens from dqt, dkh and (c, S) at its end: the walk, the
 // groups' summaries chained from the chunk end, and adjoint pass 2.
 template <int DK, bool TI>
-__global__ __launch_bounds__((Par<DK, true>::NT)) void par_grad_kernel(Shape s, Win w, Ins g, const float* __restrict__ dyvar,
+__global__ __launch_bounds__((Par<DK, true>::NT)) void par_grad_kernel(Shape s, Win w, Ins g,
+                                                               const float* __restrict__ dyvar,
                                                                const double* __restrict__ lam, size_t lseq,
                                                                const double* __restrict__ xy,
                                                                const double* __restrict__ coef, float* __restrict__ dq,
@@ -1011,8 +1012,8 @@ hipError_t bwd_par(const Shape& s, const BwdArgs& a, const void* saved, void* ws
                                sh, sg, static_cast<float*>(a.dv), xy, coef, flag);
             hipLaunchKernelGGL(par_carry_kernel, blocks((size_t)w.nb * DK, 64), dim3(64), 0, st, w, DK, DV, last, coef,
                                ccs, a.dlamT, a.detaT, sh.base + (size_t)w.nc * ST, sh.seq, first ? a.dlam0 : nullptr);
-            hipLaunchKernelGGL((par_grad_kernel<DK, TI>), grid, dim3((Par<DK, true>::NT)), 0, st, s, w, in, a.dyvar, lam, lseq, xy, coef,
-                               static_cast<float*>(a.dq), static_cast<float*>(a.dk), static_cast<float*>(a.da),
+            hipLaunchKernelGGL((par_grad_kernel<DK, TI>), grid, dim3((Par<DK, true>::NT)), 0, st, s, w, in, a.dyvar, lam,
+                               lseq, xy, coef, static_cast<float*>(a.dq), static_cast<float*>(a.dk), static_cast<float*>(a.da),
                                static_cast<float*>(a.dp), static_cast<float*>(a.dr), ous);
             if (TI)
                 hipLaunchKernelGGL(par_ou_kernel, blocks((size_t)w.nb * 2 * DK, 64), dim3(64), 0, st, w, DK, BH, last,
@@ -1023,7 +1024,9 @@ hipError_t bwd_par(const Shape& s, const BwdArgs& a, const void* saved, void* ws
 
 }  // namespace
 
-// Against the kernels it replaces, forward + backward on one MI355X:
+// Against the kernels it replaces, forward + backward on one MI355X (a forward alone is slower
+// here only with 128 value channels: 16 x 128 over 65 to 128 tokens 22 against 15 to 19 us,
+// 64 x 128 over 65 tokens 26 against 22):
 //   widths of 64 and 128 (token-recurrent, about 1.3 us per token at any batch up to the
 //   chip's width): always from the third chunk on (2825 -> 240 us at B1 T2048 H15 64 x 64);
 //   up to 64 tokens the recurrent walk is as fast as the launches here;

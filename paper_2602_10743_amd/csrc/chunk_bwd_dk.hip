@@ -56,8 +56,8 @@
 // group summaries are one vector per slot, and the sum over slots for dr is taken in registers:
 // 746 -> 418 LDS instructions in the 128 x 128 kernel.  Reads whose bytes came by direct loads
 // are written out in asm with their own wait, since for the builtin the compiler also waits for
-// every request in flight.  8 sequences of 2048, 16 heads of 128 x 128: 485 -> 440 us; the
-// split kernel at 2 sequences: 95 -> 89 us.
+// every request in flight.  8 sequences of 2048, 16 heads of 128 x 128: 447 -> 427 us; the
+// split kernel at 2 sequences: 95 -> 89 us (with OU gates 85).
 //
 // TI (gates from OU parameters, the same for every token of a key slot): abar
 // and pbar are formed once per lane and not loaded; dabar and dpbar are not
@@ -1078,8 +1078,9 @@ __global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, int c0, int n
     const uint32_t kbytes = (uint32_t)((nt - 1) * H * DK + DK) * 2;
     const rsrc_t rk = make_rsrc(static_cast<const uint16_t*>(g.k) + k0, kbytes);
     const rsrc_t rq = make_rsrc(static_cast<const uint16_t*>(g.q) + k0, kbytes);
-    const rsrc_t ra = make_rsrc(TI ? static_cast<const uint16_t*>(g.k) : static_cast<const uint16_t*>(g.a) + k0, TI ? 0u : kbytes);
-    const rsrc_t rp = make_rsrc(TI ? static_cast<const uint16_t*>(g.k) : static_cast<const uint16_t*>(g.p) + k0, TI ? 0u : kbytes);
+    const uint32_t gbytes = TI ? 0u : kbytes;   // of the per-token gates and their gradients
+    const rsrc_t ra = make_rsrc(static_cast<const uint16_t*>(TI ? g.k : g.a) + k0, gbytes);
+    const rsrc_t rp = make_rsrc(static_cast<const uint16_t*>(TI ? g.k : g.p) + k0, gbytes);
     const rsrc_t rr = make_rsrc(static_cast<const uint16_t*>(g.r) + tok0 * H + h, (uint32_t)((nt - 1) * H + 1) * 2);
     const rsrc_t rg = make_rsrc(YG ? g.dyvar + tok0 * H + h : nullptr, YG ? (uint32_t)((nt - 1) * H + 1) * 4 : 0u);
     float ca = 0.f, cp = 0.f;
@@ -1176,9 +1177,10 @@ __global__ __launch_bounds__(4 * DK) void bwd_grad_kernel(Shape s, int c0, int n
         SS = use ? SS + qs[g2][3][n] : SS;
     }
     // pass 2
-    const rsrc_t oq = make_rsrc(static_cast<uint16_t*>(g.dq) + k0, kbytes), ok_ = make_rsrc(static_cast<uint16_t*>(g.dk) + k0, kbytes);
-    const rsrc_t oa = make_rsrc(TI ? static_cast<uint16_t*>(g.dq) : static_cast<uint16_t*>(g.da) + k0, TI ? 0u : kbytes);
-    const rsrc_t op = make_rsrc(TI ? static_cast<uint16_t*>(g.dq) : static_cast<uint16_t*>(g.dp) + k0, TI ? 0u : kbytes);
+    const rsrc_t oq = make_rsrc(static_cast<uint16_t*>(g.dq) + k0, kbytes);
+    const rsrc_t ok_ = make_rsrc(static_cast<uint16_t*>(g.dk) + k0, kbytes);
+    const rsrc_t oa = make_rsrc(static_cast<uint16_t*>(TI ? g.dq : g.da) + k0, gbytes);
+    const rsrc_t op = make_rsrc(static_cast<uint16_t*>(TI ? g.dq : g.dp) + k0, gbytes);
     float sum_da = 0.f, sum_dp = 0.f;
 #pragma unroll
     for (int j = TPG - 1; j >= 0; --j) {
@@ -1255,12 +1257,12 @@ hipError_t launch_seg(const Shape& s, const BwdCut& cut, const BwdArgs& a, const
         const int s0 = std::max(s1 - cut.w, 0), w = s1 - s0;
         const int c0 = s0 * cut.lc, nc = std::min(w * cut.lc, nct - c0);
         const bool last = s1 == cut.ns;
-        if (s1 > 1 && (e = launch_backward_dv(s, cut.ns, cut.lc, s0, w, true, a, saved_lam, f.gend, f.pseg, st)) != hipSuccess)
-            return e;
+        e = s1 > 1 ? launch_backward_dv(s, cut.ns, cut.lc, s0, w, true, a, saved_lam, f.gend, f.pseg, st) : hipSuccess;
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(bwd_state_scan_kernel, dim3((unsigned)(((size_t)nbh * DK * DV + 255) / 256)), dim3(256), 0, st,
                            nbh, DK, DV, s0, w, last, f.pseg, a.detaT, f.gend, f.cg);
-        if ((e = launch_backward_dv(s, cut.ns, cut.lc, s0, w, false, a, saved_lam, f.gend, f.pseg, st)) != hipSuccess)
-            return e;
+        e = launch_backward_dv(s, cut.ns, cut.lc, s0, w, false, a, saved_lam, f.gend, f.pseg, st);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3((unsigned)(nbh * w * Cfg::NNT)), dim3(Cfg::NTHR), Cfg::BYTES, st, s,
                            Seg{cut.ns, cut.lc, w, s0}, a, saved_lam, saved_H, nullptr, f.gend, f.xy, f.coef);
         hipLaunchKernelGGL(bwd_carry_kernel, dim3((unsigned)((nbh * DK + 63) / 64)), dim3(64), 0, st, nbh, DK, DV, nc, last,

@@ -12,8 +12,8 @@
 //
 // One workgroup per (batch, head, segment of the sequence, value tile).  The scan
 // waves redo the precision walk of each chunk, each half of it from its saved
-// start state (lam_0; lam_16 and P_16), and stage the chunk's dY tile; the MFMA waves (16 value channels each, G[dk, 16]
-// in registers) consume the previous round's chunk:
+// start state (lam_0; lam_16 and P_16), and stage the chunk's dY tile; the MFMA waves (16 value
+// channels each, G[dk, 16] in registers; wide 32) consume the previous round's chunk:
 //   dV^T[d, j] = sum_i dY^T[d, i] A[i, j] + sum_n Gs^T[d, n] Kn^T[n, j]
 //   G[n, d]   += sum_t Qp^T[n, t] dY[t, d]
 // with the operands that run across tile rows (dY^T, Qp^T) read by
@@ -68,7 +68,8 @@ __global__ __launch_bounds__((ChunkCfg<DK, DV, WIDE>::NTHR)) void bwd_dv_kernel(
     const int dm0 = tile * DVT + dl0;       // its first value channel
 
     // G[n, d] for n = 16 rt + 4 g4 + rr, d = dm0 + 16 dt + l16
-    const float* gsrc = NODV ? nullptr : sg.ns > 1 ? gend + vs * DK * DV : g.detaT ? g.detaT + (size_t)bh * DK * DV : nullptr;
+    const float* gsrc = sg.ns > 1 ? gend + vs * DK * DV : g.detaT ? g.detaT + (size_t)bh * DK * DV : nullptr;
+    if (NODV) gsrc = nullptr;
     constexpr int NPP = (DK + 63) / 64;
     float pp[NPP];   // NODV: the segment's gate product of slots lane + 64 i (one wave stores it)
 #pragma unroll

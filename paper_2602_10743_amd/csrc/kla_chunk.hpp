@@ -56,8 +56,8 @@ constexpr int kC = 32;   // tokens per chunk
 // or 16 per 8, those whose lanes run along the slots use the transposing read (nt_tr8).
 // Token-major tiles took a 2-byte write per element, four times the LDS instructions of the
 // whole walk: forward 266 -> 259 us, value-side backward 230 -> 213 us (B8 T2048 H16 128 x
-// 128), state-only pass, which is bound by the walk, 544 -> 435 us (65536 tokens).  The 16-byte pieces of a row are swizzled by the slot: eight lanes writing or
-// reading the same piece of eight consecutive slots, and the four rows of a transposing
+// 128), state-only pass, which is bound by the walk, 544 -> 435 us (65536 tokens).  The 16-byte
+// pieces of a row are swizzled by the slot: eight lanes writing or reading the same piece of eight consecutive slots, and the four rows of a transposing
 // read, fall in distinct banks without padding.
 __device__ __forceinline__ constexpr int nt_off(int n, int t) {
     return n * kC + (((t >> 3) ^ ((n >> 2) & 3)) << 3) + (t & 7);

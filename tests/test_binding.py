@@ -67,7 +67,8 @@ def test_absent_ou_parameters_are_refused():
     one = [t[:, 0].contiguous() for t in (q, k, v, r)]
     for i in range(3):
         some = [None if j == i else t for j, t in enumerate(par)]
-        for call in (lambda: K.kla_forward_ou(q, k, v, *some, r), lambda: K.kla_backward_ou(q, k, v, *some, r, None, None, v),
+        for call in (lambda: K.kla_forward_ou(q, k, v, *some, r),
+                     lambda: K.kla_backward_ou(q, k, v, *some, r, None, None, v),
                      lambda: K.kla_decode_step_ou(*one[:3], *some, one[3], lam, eta)):
             with pytest.raises(K.KLAError) as e:
                 call()
