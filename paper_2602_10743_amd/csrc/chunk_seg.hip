@@ -175,11 +175,12 @@ __global__ __launch_bounds__(256) void seg_state_scan_kernel(int nbh, int DK, in
 // The cut of a shape.  One workgroup fills a CU, so segments are added until every CU has
 // one (as many workgroups as fit 256, one per head and segment where dv = 128 runs wide).
 // The costs (us per chunk round, and of the four kernels around the passes and their launches) are
-// those with which the rule chose best over 1 to 128 heads, 128 to 8192 tokens and ten pairs of
-// widths, each timed whole and cut: at most 4% (32 x 128, 80 heads: 7%) from the better of the
-// two.  With one set of rounds for all widths, those of few workgroups, 100 heads of 64 x 64 over 2048
-// tokens took two segments, 148 us against 135, and 128 of 128 x 128 over 4096 with a saved context
-// 589 against 446.
+// those with which the rule chose best over 1 to 128 heads, 300 to 8192 tokens and eight pairs of
+// widths, each timed whole and in both cuts, with and without a saved context: at most 5% (12% at a
+// few) from the best, but for some of one to four heads with 128 value channels, whose hundreds of
+// segments cost more in the scans than the rule knows.  With one set of rounds for all widths, those
+// of few workgroups, 100 heads of 64 x 64 over 2048 tokens took two segments, 148 us against 135, and
+// 128 of 128 x 128 over 4096 with a saved context 589 against 446.
 // Against the whole walk: 3001 tokens of 16 heads 238 -> 75 us, with OU gates and a saved context
 // (B2 T2048 H16) 167 -> 85 us; 65536 tokens, 8 segments of two 64-channel tiles -> 16 wide ones,
 // 1460 -> 1067 us (kernel times).
@@ -191,9 +192,10 @@ Cut cut_of(const Shape& s) {
     struct Us {
         double walk, exact, wide, state, fixed;   // whole walk, exact pass (wide), state-only pass
     };
-    const Us us = s.dk == 128 ? Us{2.5, 2.8, 4.6, 1.7, 20.0}
-                  : s.dk == 64 ? Us{1.8, 2.0, 3.0, 1.5, 19.0}
-                               : Us{1.65, 1.6, 1.6, 1.5, 15.0};
+    const bool two = ntile == 2;
+    const Us us = s.dk == 128  ? (two ? Us{2.6, 2.25, 4.6, 1.35, 22.0} : Us{2.3, 2.25, 0.0, 1.85, 16.0})
+                  : s.dk == 64 ? (two ? Us{1.95, 1.6, 3.3, 1.2, 17.0} : Us{1.7, 1.6, 0.0, 1.65, 15.0})
+                               : (two ? Us{1.85, 1.45, 0.0, 1.35, 17.0} : Us{1.46, 1.6, 0.0, 1.35, 13.0});
     auto rounds = [](int wg) { return (wg + 255) / 256; };
     double best = nct * us.walk;
     for (int wg : {256 / (bh * ntile), 256 / bh}) {
