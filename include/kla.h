@@ -116,10 +116,11 @@ size_t kla_saved_bytes(const kla_desc* desc);
 
 /* Bytes of device workspace kla_backward needs when it is given a saved
  * context (`with_saved` != 0) or must recompute one (`with_saved` == 0).  With a
- * context: at most 256 MiB (bf16, few sequences: segments side by side, in
- * windows) or 192 MiB (fp32, chunks side by side, in windows), or, where that is
- * more, what the walk of whole sequences needs per token (bf16: dk / 16 floats
- * per token and head; fp32 at widths of 64 or 128: dk doubles). */
+ * context, beside 256 bytes of flags (and the OU parts): at most 256 MiB (bf16,
+ * few sequences: segments side by side, in windows) or 192 MiB (fp32, chunks side
+ * by side, in windows), or, where that is more, what the walk of whole sequences
+ * needs (bf16: dk / 16 floats per token and head; fp32 at widths of 64 or 128: dk
+ * doubles per token and head, and per head). */
 size_t kla_backward_workspace(const kla_desc* desc, int with_saved);
 
 /*
