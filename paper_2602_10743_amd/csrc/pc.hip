@@ -425,6 +425,10 @@ struct PcLanes {
     // uniform token in the sums, leave it the most registers (200 heads of 128 x 128 over 256 tokens
     // 4925 -> 4701 us; the other widths lose 1 to 3% by either)
     static constexpr bool TIGHT = NRED == 2 && sizeof(A) == 8 && DK == 128;
+    // and with 4 elements per lane the OU gates, read twice per token, stay in LDS: 124 registers
+    // spilled -> 58, 200 heads of 128 x 128 over 200 tokens 5106 -> 3780 us (the gates' sums in LDS
+    // instead: 4886; 2 elements spill nothing and lose 5% by it)
+    static constexpr bool LDS_GATES = TIGHT && NPER > 2;
 };
 
 template <typename S, int DK, int DV, bool TI, bool FEW>
@@ -443,6 +447,8 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
     __shared__ float4 s_c[kCK][CB];        // r, v, dy, dyvar
     __shared__ float2 s_o[kCK][CB];        // dv, dr
     __shared__ float s_red[NRED][CB][4][DK];  // per-channel key-slot values of dq, dk, dabar, dpbar
+    constexpr bool GL = TI && PL::LDS_GATES;
+    __shared__ A s_ga[GL ? NPER : 1][GL ? NTHR : 1], s_gp[GL ? NPER : 1][GL ? NTHR : 1];   // a lane's own OU gates
 
     const T_ *q = static_cast<const T_*>(g.q), *k = static_cast<const T_*>(g.k), *v = static_cast<const T_*>(g.v);
     const T_ *a = static_cast<const T_*>(g.a), *p = static_cast<const T_*>(g.p), *r = static_cast<const T_*>(g.r);
@@ -469,8 +475,20 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
         if constexpr (TI) {
             const size_t og = ((size_t)h * DK + ln + LPC * i) * DV + d;
             ou_gates(g.ou_a[og], g.ou_p[og], g.ou_d[og], ga[i], gp[i]);
+            if constexpr (GL) {
+                s_ga[i][tid] = ga[i];
+                s_gp[i][tid] = gp[i];
+            }
         }
     }
+    auto abar = [&](int i, float in) -> A {
+        if constexpr (GL) return s_ga[i][tid];
+        return TI ? ga[i] : (A)in;
+    };
+    auto pbar = [&](int i, float in) -> A {
+        if constexpr (GL) return s_gp[i][tid];
+        return TI ? gp[i] : (A)in;
+    };
     // The inputs of a segment and its checkpoint are fetched into registers one segment
     // ahead (indices clamped to the segment's last token, so every load is issued) and
     // written to LDS at the start of the segment.
@@ -548,7 +566,7 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
 #pragma unroll
                 for (int i = 0; i < NPER; ++i) {
                     const float4 in = s_k[ok ? j : 0][ln + LPC * i];
-                    const A ax = TI ? ga[i] : (A)in.x, py = TI ? gp[i] : (A)in.y, kz = in.z;
+                    const A ax = abar(i, in.x), py = pbar(i, in.y), kz = in.z;
                     const A den = fma(py, lt[j][i], ax * ax);
                     const A num = fma(kz * kz * rc, den, lt[j][i]);
                     const A R = rcpa(den * num);
@@ -568,7 +586,7 @@ __global__ __launch_bounds__((PcLanes<DK, DV, FEW, typename acc<S>::type>::NTHR)
 #pragma unroll
                 for (int i = 0; i < NPER; ++i) {
                     const float4 in = s_k[j][ln + LPC * i];   // abar, pbar, k, q
-                    const A av = TI ? ga[i] : (A)in.x, pv = TI ? gp[i] : (A)in.y, kv = in.z, qv = in.w;
+                    const A av = abar(i, in.x), pv = pbar(i, in.y), kv = in.z, qv = in.w;
                     const A lp = lt[j][i], lc = lt[j + 1][i], ep = et[j][i], ec = et[j + 1][i];
                     const A den = fma(pv, lp, av * av);
                     const A R = rcpa(lc * den);
