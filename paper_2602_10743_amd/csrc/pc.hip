@@ -91,14 +91,17 @@ struct PcFwd {
 // workgroups hide the wait and the registers are better spent on them); the elements are updated,
 // the partial readouts summed over the lanes of a channel and y, yvar written from LDS.
 // Bound by VALU issue where the channels fill the chip (18 slots per element) and by the
-// latency of a token's step where they do not (LEAN, fp64 at dk = 128 with more than one workgroup
-// per CU: the variance's sums are formed also when nobody asks for them, since put off behind that
-// question they hold every element's factors, 310 registers and one wave per SIMD against 228 and
-// two: 200 heads of 128 x 128 over 256 tokens 1476 -> 1256 us, but 128 heads of 128 x 64, one workgroup
-// per CU, 389 -> 470): B2 T1024 H8 64 x 64 on 8 lanes per channel (128
+// latency of a token's step where they do not: B2 T1024 H8 64 x 64 on 8 lanes per channel (128
 // waves, loads waited for in every block) 838 us, on 32 lanes 229, on 64 193 us.
-template <typename S, int DK, int DV, bool TI, bool FEW, bool LEAN>
-__global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shape s, FwdArgs g,
+// WPS, the waves per SIMD that the registers leave room for, is 1 unless fp64 at dk = 128 has more
+// than one wave for each: there the variance's sums are formed also when nobody asks for them (put
+// off behind that question they hold every element's factors, 310 registers), OU gates are squared
+// anew for every token, and for 3 waves the staging's addresses are formed anew in every block.
+// 200 tokens, the forms for 1, 2 and 3 waves (us): 400 heads of 128 x 16 314, 481 and -; 300 of 128 x
+// 32 -, 500 and 543; 520 of them -, 786 and 708; OU gates, whose state of 128 registers leaves room for
+// two at most: 300 heads of 128 x 32 612 and 494, 200 of 128 x 128 1211 and 1023.
+template <typename S, int DK, int DV, bool TI, bool FEW, int WPS>
+__global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR), WPS) void fwd_pc_kernel(Shape s, FwdArgs g,
                                                                          typename acc<S>::type* ck) {
     using T_ = typename storage<S>::type;
     using A = typename acc<S>::type;
@@ -139,16 +142,18 @@ __global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shap
     float4 nk[KPT];
     float2 nv[VPT];
     auto fetch = [&](int t0) {
+        int ti = tid;
+        if constexpr (WPS == 3) asm volatile("" : "+v"(ti));   // no address is kept over the blocks
         const int tl = min(kTB, s.T - t0) - 1;
 #pragma unroll
         for (int m = 0; m < KPT; ++m) {
-            const int idx = min(tid + NTHR * m, kTB * DK - 1), t = min(idx / DK, tl), n = idx % DK;
+            const int idx = min(ti + NTHR * m, kTB * DK - 1), t = min(idx / DK, tl), n = idx % DK;
             const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DK + n;
             nk[m] = TI ? make_float4(0.f, 0.f, ld(k, o), ld(q, o)) : make_float4(ld(a, o), ld(p, o), ld(k, o), ld(q, o));
         }
 #pragma unroll
         for (int m = 0; m < VPT; ++m) {
-            const int idx = min(tid + NTHR * m, kTB * CT - 1), t = min(idx / CT, tl), cc = idx % CT;
+            const int idx = min(ti + NTHR * m, kTB * CT - 1), t = min(idx / CT, tl), cc = idx % CT;
             const size_t o = (((size_t)b * s.T + t0 + t) * s.H + h) * DV + d0 + cc;
             nv[m] = make_float2(ld(r, o), ld(v, o));
         }
@@ -192,13 +197,17 @@ __global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shap
             if (t0 + kTB < s.T) fetch(t0 + kTB);
         }
         auto token = [&](int t) {
+            int n0 = ng;
+            if constexpr (WPS == 3) asm volatile("" : "+v"(n0));
             const float2 rv = s_v[bb][t][c];
             const A rc = rv.x, krv_s = (A)rv.x * (A)rv.y;   // r v: the evidence k r v over k
             A ya = 0, wa = 0;
 #pragma unroll
             for (int i = 0; i < NPER; ++i) {
-                const float4 in = s_k[bb][t][ng + LG * i];   // abar, pbar, k, q
-                const A ax = TI ? ga[i] : (A)in.x, py = TI ? gp[i] : (A)in.y, kz = in.z, qw = in.w;
+                const float4 in = s_k[bb][t][n0 + LG * i];   // abar, pbar, k, q
+                A ax = TI ? ga[i] : (A)in.x;
+                if constexpr (TI && WPS > 1) asm volatile("" : "+v"(ax));   // its square is not kept over the tokens
+                const A py = TI ? gp[i] : (A)in.y, kz = in.z, qw = in.w;
                 const A den = fma(py, lam[i], ax * ax);
                 const A num = fma(kz * kz * rc, den, lam[i]);
                 const A R = rcpa(den * num);
@@ -211,7 +220,7 @@ __global__ __launch_bounds__((PcFwd<DK, DV, FEW>::NTHR)) void fwd_pc_kernel(Shap
             ya = lane_sum<LG>(ya);
             // every lane writes (no lane mask): the channel's last lane its sums, the others a junk slot
             *(ng == LG - 1 ? &s_y[bb][t][c] : &s_junk[0][tid]) = (float)ya;
-            if (LEAN || want_w) {
+            if (WPS > 1 || want_w) {
                 wa = lane_sum<LG>(wa);
                 *(ng == LG - 1 ? &s_w[bb][t][c] : &s_junk[1][tid]) = (float)wa;
             }
@@ -366,18 +375,23 @@ bool few_channels(const Shape& s) {
 
 template <typename S, int DK, int DV>
 struct FwdPc {
-    template <bool TI, bool FEW, bool LEAN = false>
+    template <bool TI, bool FEW, int WPS = 1>
     static hipError_t go(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
         using P = PcFwd<DK, DV, FEW>;
-        hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, TI, FEW, LEAN>), dim3((unsigned)(s.B * s.H * (DV / P::CT))),
+        hipLaunchKernelGGL((fwd_pc_kernel<S, DK, DV, TI, FEW, WPS>), dim3((unsigned)(s.B * s.H * (DV / P::CT))),
                            dim3(P::NTHR), 0, st, s, a, static_cast<typename acc<S>::type*>(ck));
         return hipGetLastError();
     }
     template <bool TI>
     static hipError_t run_ti(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {
         if (few_channels(s)) return go<TI, true>(s, a, ck, st);
-        if constexpr (DK == 128 && std::is_same<S, f32_t>::value)
-            if (s.B * s.H * (DV / PcFwd<DK, DV, false>::CT) > 256) return go<TI, false, true>(s, a, ck, st);
+        if constexpr (DK == 128 && std::is_same<S, f32_t>::value) {
+            using P = PcFwd<DK, DV, false>;
+            const long waves = (long)s.B * s.H * (DV / P::CT) * (P::NTHR / 64);   // 1024 SIMDs
+            if constexpr (!TI)
+                if (waves > 2048) return go<TI, false, 3>(s, a, ck, st);
+            if (waves > 1024) return go<TI, false, 2>(s, a, ck, st);
+        }
         return go<TI, false>(s, a, ck, st);
     }
     static hipError_t run(const Shape& s, const FwdArgs& a, void* ck, hipStream_t st) {

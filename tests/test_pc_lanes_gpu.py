@@ -51,3 +51,30 @@ def test_few_and_many_channels_agree(T, dk, dv, dtype, ou):
     for n in names:
         e = rel_err(to_np(gf[n]), to_np(gm[n][one]))
         assert e <= (tol if gf[n].dtype == t else 1e-4), f"{n}: {e:.2e}"
+
+
+# the fp64 forward at 128 key slots by its waves per SIMD: one, two and three (two with OU gates)
+@pytest.mark.parametrize("heads,dv", [(512, 16), (520, 16), (1040, 16), (256, 32), (258, 32), (514, 32), (172, 128)])
+@pytest.mark.parametrize("ou", [False, True])
+def test_waves_per_simd_agree(heads, dv, ou):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_10743_amd as K
+    log(f"per-channel forward, {heads} heads of 128 x {dv} ou={ou}")
+    B, T, H, dk = heads // 2, 19, 2, 128
+    g = torch.Generator(device="cuda").manual_seed(heads + dv)
+    z = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, k, v, r = z(B, T, H, dk), z(B, T, H, dk) / dk ** 0.5, z(B, T, H, dv), 0.1 + z(B, T, H, dv).abs()
+    if ou:
+        gates = [1 + 15 * torch.rand(H, dk, dv, generator=g, device="cuda"), z(H, dk, dv).abs() + 1,
+                 0.001 + 0.1 * torch.rand(H, dk, dv, generator=g, device="cuda")]
+        fwd = lambda s, **kw: K.kla_forward_pc_ou(q[s], k[s], v[s], *gates, r[s], save=True, **kw)
+    else:
+        a, p = torch.sigmoid(z(B, T, H, dk) + 3), 0.05 * z(B, T, H, dk).abs()
+        fwd = lambda s, **kw: K.kla_forward_pc(q[s], k[s], v[s], a[s], p[s], r[s], save=True, **kw)
+    for one in (slice(0, 1), slice(B - 1, B)):
+        om, on, of = fwd(slice(0, B), want_var=True), fwd(slice(0, B)), fwd(one, want_var=True)
+        for n in ("y", "yvar", "lamT", "etaT"):   # fp64 sums of 128 terms in another order, stored in fp32
+            e = rel_err(to_np(of[n]), to_np(om[n][one]))
+            assert e <= 1e-4, f"{n}: {e:.2e}"
+        assert torch.equal(on["y"], om["y"]) and torch.equal(on["etaT"], om["etaT"])
